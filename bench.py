@@ -162,7 +162,7 @@ def roofline(kind, kt_us, cells, traffic, counters):
         "frac": round(tf / FP64_PEAK_TFLOPS, 5),
         "traffic": None if traffic is None else round(traffic, 1),
         "algorithmic_flops_per_launch": flops,
-        "kernel": ("fused forward step (k_step with the CFL epilogue, march)" if kind == "step"
+        "kernel": ("fused forward step (k_step or k_step_cols with the CFL epilogue, march)" if kind == "step"
                    else "adjoint step (k_adj_a + k_adj_b)"),
         "launch_us": round(kt_us, 3),
         "hbm": {"achieved": round(gb, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gb / HBM_PEAK_GBS, 5),
@@ -228,7 +228,7 @@ def grad_256x512_extra(steps: int = 5, interval: int = 32) -> dict:
                         "steps, one projected-gradient iteration", "grad_iters_per_s": 1.0 / per,
             "cell_updates_per_s": 2.0 * (tot / steps) * cfg.cells / per, "nsteps": tot / steps,
             "fwd_cell_updates_per_s": int(nf.item()) * cfg.cells / t_fwd, "gradient_over_forward": per / t_fwd,
-            "kernel_times_us": {k: round(v, 3) for k, v in kt.items()}, "tile": ctx.tile}
+            "kernel_times_us": {k: round(v, 3) for k, v in kt.items()}, "tile": ctx.kernels}
 
 
 def scale_point(kernel_launches: int = 10) -> dict:
@@ -242,11 +242,13 @@ def scale_point(kernel_launches: int = 10) -> dict:
     U8 = ctx8.init_state(inputs.seed_batch(cfg8, range(8), rms=1e-3))
     kt8 = ctx8.kernel_times(U8, reps=kernel_launches)
     cells8 = cfg8.nx * cfg8.ny * cfg8.batch
-    out = {"workload": "8 x 1024 x 2048, one launch per step", "tile": ctx8.tile}
+    kern = ctx8.kernels
+    out = {"workload": "8 x 1024 x 2048, one launch per step", "tile": kern}
     for key, t_us, tkey, parts in (("step", kt8["step_march_us"], "step_march", ["step_march"]),
                                    ("adjoint", kt8["adjoint_two_kernel_us"], "adjoint", ["adj_a", "adj_b"])):
-        out[key] = roofline(key, t_us, cells8, profiling.traffic_for("step_8x1024x2048", tkey, ctx8.tile),
-                            profiling.counters_for("8x1024x2048", parts, ctx8.tile))
+        out[key] = roofline(key, t_us, cells8,
+                            profiling.traffic_for(profiling.key_for("step_8x1024x2048", kern), tkey, kern),
+                            profiling.counters_for(profiling.key_for("8x1024x2048", kern), parts, kern))
         out[key]["cell_updates_per_s"] = cells8 / (t_us * 1e-6)
     return out
 
@@ -332,11 +334,12 @@ def main():
     fw_total, interval, two = rtcnop.revolve_plan_stats(nt, slots, nt)
     t_fwd = nt * kt["step_march_us"] + (fw_total - nt) * kt["step_given_us"]
     t_adj = nt * kt["adjoint_two_kernel_us"]
-    tkey = "cnop_8x512x1024"
-    adj = roofline("adjoint", kt["adjoint_two_kernel_us"], cells, profiling.traffic_for(tkey, "adjoint", ctx.tile),
-                   profiling.counters_for(tkey, ["adj_a", "adj_b"], ctx.tile))
-    stp = roofline("step", kt["step_march_us"], cells, profiling.traffic_for(tkey, "step_march", ctx.tile),
-                   profiling.counters_for(tkey, ["step_march"], ctx.tile))
+    kern = ctx.kernels
+    tkey = profiling.key_for("cnop_8x512x1024", kern)
+    adj = roofline("adjoint", kt["adjoint_two_kernel_us"], cells, profiling.traffic_for(tkey, "adjoint", kern),
+                   profiling.counters_for(tkey, ["adj_a", "adj_b"], kern))
+    stp = roofline("step", kt["step_march_us"], cells, profiling.traffic_for(tkey, "step_march", kern),
+                   profiling.counters_for(tkey, ["step_march"], kern))
     dom, other = (adj, stp) if t_adj >= t_fwd else (stp, adj)
     per_grad_s = per_iter * args.steps / max(grads_timed, 1)
     dom["fwd_share_of_gradient"] = round(t_fwd * 1e-6 / per_grad_s, 3)
@@ -370,7 +373,7 @@ def main():
             "nx": cfg.nx, "ny": cfg.ny, "batch": B, "groups": len(search.searches), "T": T,
             "nsteps": int(np.mean(nsteps)),
             "pool_slots": slots, "level1_interval": interval, "two_level": two,
-            "forward_steps_per_gradient": fw_total, "tile": ctx.tile,
+            "forward_steps_per_gradient": fw_total, "tile": kern,
         },
         "cnop_iters_per_s": 1.0 / per_iter,
         "gradient_evals_per_iter": grads_timed / args.steps,

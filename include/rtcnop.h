@@ -271,7 +271,7 @@ int rt_axpy(rt_ctx* ctx, const double* x, const double* alpha, const double* y, 
  * pass), 32x16 (512), 16x15 and 15x16 (256, every face loop in one pass);
  * ids 0..11 in that order.  Every variant gives bitwise-identical
  * results.  rt_set_tile selects one variant for both kernels;
- * rt_autotune times every variant on the state U (device) with `reps`
+ * rt_autotune times every variant (and the column kernels) on the state U (device) with `reps`
  * launches each on the context's stream (steps at a given dt and with the
  * CFL reduction; adjoint steps folded and as two kernels), keeps the
  * fastest step variant and the fastest adjoint variant and mode (see
@@ -280,6 +280,15 @@ int rt_axpy(rt_ctx* ctx, const double* x, const double* alpha, const double* y, 
 int rt_set_tile(rt_ctx* ctx, int32_t tile);
 /* Select the step and adjoint variants separately. */
 int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
+/* Column kernels in place of the tile kernels, a mask of RT_COLUMNS_*: one
+ * wavefront marches a strip of columns upward with its rows in registers,
+ * without LDS or barriers.  Results are those of every tile variant to the
+ * bit.  The default: the step beyond three 32x8 blocks per CU of cells in
+ * all; rt_set_tile and rt_set_tiles set the mask to 0, rt_autotune to what
+ * it measures as faster. */
+enum { RT_COLUMNS_STEP = 1 };
+int rt_set_columns(rt_ctx* ctx, int32_t mask);
+int rt_get_columns(const rt_ctx* ctx, int32_t* mask);
 /* The adaptive march replays captured HIP graphs of 48 steps (on = 1, the
  * default) or launches step by step (on = 0); results are identical. */
 int rt_set_graphs(rt_ctx* ctx, int32_t on);

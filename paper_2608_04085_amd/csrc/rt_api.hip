@@ -56,6 +56,8 @@ struct rt_ctx {
   hipStream_t stream;
   int tile;      // tile variant of the step kernel
   int tile_adj;  // tile variant of the adjoint kernel
+  int columns = 0;  // RT_COLUMNS_* kernels that run in place of the tile kernels (same results)
+  int step_variant() const { return (columns & RT_COLUMNS_STEP) ? (int)rtk::TILE_COLUMNS : tile; }
   int red_blocks;
   // workspace
   char* ws = nullptr;
@@ -226,7 +228,7 @@ constexpr long kGraphChunk = 48;
 // launch index (S0 -> S1 -> S0 ...).
 int ensure_chunk_graph(rt_ctx* c, double* pool, int interval, int slots) {
   if (c->chunk_exec && c->chunk_pool == pool && c->chunk_interval == interval && c->chunk_slots == slots &&
-      c->chunk_tile == c->tile)
+      c->chunk_tile == c->step_variant())
     return 0;
   if (c->chunk_exec) {
     RT_HIP(hipGraphExecDestroy(c->chunk_exec));
@@ -240,7 +242,7 @@ int ensure_chunk_graph(rt_ctx* c, double* pool, int interval, int slots) {
     const double* src = (k & 1) ? c->S1 : c->S0;
     double* dst = (k & 1) ? c->S0 : c->S1;
     rtk::StepArgs a = adaptive_args(c, src, dst, k, pool, interval, slots);
-    e = rtk::launch_step(c->P, c->tile, a, c->capture_stream);
+    e = rtk::launch_step(c->P, c->step_variant(), a, c->capture_stream);
   }
   const hipError_t e2 = hipStreamEndCapture(c->capture_stream, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
@@ -256,7 +258,7 @@ int ensure_chunk_graph(rt_ctx* c, double* pool, int interval, int slots) {
   c->chunk_pool = pool;
   c->chunk_interval = interval;
   c->chunk_slots = slots;
-  c->chunk_tile = c->tile;
+  c->chunk_tile = c->step_variant();
   return 0;
 }
 
@@ -299,7 +301,7 @@ int march(rt_ctx* c, double T, double* pool, int interval, int slots) {
       const double* src = (launched & 1) ? c->S1 : c->S0;
       double* dst = (launched & 1) ? c->S0 : c->S1;
       rtk::StepArgs a = adaptive_args(c, src, dst, launched, pool, interval, slots);
-      RT_HIP(rtk::launch_step(P, c->tile, a, c->stream));
+      RT_HIP(rtk::launch_step(P, c->step_variant(), a, c->stream));
       ++launched;
     }
     c->last_launch = launched;
@@ -362,7 +364,13 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   // of 256 threads: every face loop is one pass of the block (255 and 256
   // faces of each direction; the step's single face list two), and four
   // small blocks per CU hide one another's barriers better than two large
-  // ones.  rt_autotune measures instead.
+  // ones.  Beyond one round the step runs the column kernel instead, which
+  // has no barriers and almost no halo work: given dt / march step in us,
+  // tiles against columns, 12.3 / 14.2 against 13.9 / 16.4 at 2 x 256x512,
+  // 17 / 19.5 against 22 / 24.5 at 512x1024, 84 / 94 against 153 / 172 at
+  // 8 x 512x1024; below it a launch lasts as long as one wavefront's chain
+  // of rows and the tiles win (7.7 / 9.1 against 8.4 / 10.2 at 256x512).
+  // rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
   const bool tiny = all_cells < ((size_t)1 << 16);
   int dev = 0, cus = 0;
@@ -373,6 +381,7 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   c->tile = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x16 : rtk::TILE_16x15);
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
   c->fold = tiny;
+  c->columns = one_round ? 0 : RT_COLUMNS_STEP;
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));
   *out = c;
@@ -395,6 +404,20 @@ int rt_set_tile(rt_ctx* c, int32_t tile) {
   if (!c || tile < 0 || tile >= rtk::TILE_COUNT) return fail(RT_EINVAL, "bad tile id");
   c->tile = tile;
   c->tile_adj = tile;
+  c->columns = 0;
+  return 0;
+}
+
+int rt_set_columns(rt_ctx* c, int32_t mask) {
+  if (!c) return fail(RT_EINVAL, "null context");
+  if (mask & ~RT_COLUMNS_STEP) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
+  c->columns = mask;
+  return 0;
+}
+
+int rt_get_columns(const rt_ctx* c, int32_t* mask) {
+  if (!c || !mask) return fail(RT_EINVAL, "null argument");
+  *mask = c->columns;
   return 0;
 }
 
@@ -403,6 +426,7 @@ int rt_set_tiles(rt_ctx* c, int32_t step_tile, int32_t adj_tile) {
     return fail(RT_EINVAL, "bad tile id");
   c->tile = step_tile;
   c->tile_adj = adj_tile;
+  c->columns = 0;
   return 0;
 }
 
@@ -560,8 +584,8 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
 
 }  // namespace
 
-// Autotuner: times every tile variant of the step kernel (given-dt plus
-// adaptive launches) and of the adjoint step (folded and two-kernel) on the
+// Autotuner: times the column kernel and every tile variant of the step
+// (given-dt plus adaptive launches) and every variant of the adjoint step (folded and two-kernel) on the
 // caller's state U (device, [B][4][ny][nx]) with HIP events on the context's
 // stream and keeps the fastest step variant and the fastest adjoint variant
 // of the chosen form.  All variants give bitwise-identical results, so this
@@ -575,9 +599,14 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   hipEvent_t e0, e1;
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
-  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f;
+  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f, best_c = 1e30f;
   int bs = c->tile, bfold = c->tile_adj, bunf = c->tile_adj;
   int rc = 0;
+  {
+    float ms[4];
+    rc = time_kernels(c, U, rtk::TILE_COLUMNS, c->tile_adj, reps, e0, e1, ms);
+    best_c = ms[0] + ms[1];
+  }
   for (int t = 0; t < rtk::TILE_COUNT && rc == 0; ++t) {
     float ms[4];
     rc = time_kernels(c, U, t, t, reps, e0, e1, ms);
@@ -600,6 +629,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   c->tile = bs;
   c->tile_adj = ba;
   c->fold = fold;
+  c->columns = best_c < best_s ? RT_COLUMNS_STEP : 0;
   if (step_tile) *step_tile = bs;
   if (adj_tile) *adj_tile = ba;
   Flags f{};
@@ -619,7 +649,7 @@ int rt_kernel_times(rt_ctx* c, const double* U, int32_t reps, double* out) {
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
   float ms[4] = {0, 0, 0, 0};
-  const int rc = time_kernels(c, U, c->tile, c->tile_adj, reps, e0, e1, ms);
+  const int rc = time_kernels(c, U, c->step_variant(), c->tile_adj, reps, e0, e1, ms);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
@@ -710,7 +740,7 @@ int rt_step(rt_ctx* c, const double* U_in, double* U_out, const double* dt, doub
     RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(acc_out), 0, 2 * c->P.nb, c->stream));
     a.acc_out = acc_out;
   }
-  RT_HIP(rtk::launch_step(c->P, c->tile, a, c->stream));
+  RT_HIP(rtk::launch_step(c->P, c->step_variant(), a, c->stream));
   if (dt_next) RT_HIP(rtk::launch_cfl_from_bits(c->P, acc_out, dt_next, c->stream));
   return 0;
 }
@@ -934,7 +964,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     a.dt_index = n;
     a.nsteps_limit = c->nsteps;
     a.flags = c->flags;
-    RT_HIP(rtk::launch_step(P, c->tile, a, ss));
+    RT_HIP(rtk::launch_step(P, c->step_variant(), a, ss));
     return 0;
   };
   const bool dtd = c->dt_mode == RT_DT_DIFFERENTIATED;
@@ -1139,7 +1169,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dt_index = n;
       a.nsteps_limit = c->nsteps + G.b0;
       a.flags = c->flags;
-      RT_HIP(rtk::launch_step(G.P, c->tile, a, G.st));
+      RT_HIP(rtk::launch_step(G.P, c->step_variant(), a, G.st));
       return 0;
     };
     auto gadjoint = [&](Group& G, const double* Un, int n) -> int {

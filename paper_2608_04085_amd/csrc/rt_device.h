@@ -116,22 +116,23 @@ constexpr double kTieTol = 1e-10;
 
 // MC-limited slope: zero if a*b <= 0 or a difference is negligible, else
 // sign(a) min(2|a|, 2|b|, |a+b|/2), which equals the value of the case
-// (central, 2a or 2b) that the limiter selects.
-RT_DEV double mc_value(double a, double b, bool small_a, bool small_b) {
-  const bool zero = (a * b <= 0.0) || small_a || small_b;
-  const double m = fmin(fmin(2.0 * fabs(a), 2.0 * fabs(b)), fabs(0.5 * (a + b)));
-  return zero ? 0.0 : copysign(m, a);
+// (central, 2a or 2b) that the limiter selects.  m = min(|a|, |b|) and small
+// (m is negligible) come from the caller; a difference above the tolerance
+// is not zero, so a*b <= 0 is a comparison of signs.
+RT_DEV bool mc_zero(double a, double b, bool small) {
+  return small || (__double2hiint(a) ^ __double2hiint(b)) < 0;
+}
+RT_DEV double mc_value(double a, double b, double m, bool small) {
+  const double s = fmin(2.0 * m, fabs(0.5 * (a + b)));
+  return mc_zero(a, b, small) ? 0.0 : copysign(s, a);
 }
 
 // The limiter's case, for the adjoint: 0 zero, 1 central, 2 -> 2a, 3 -> 2b.
 // Where two cases give the same value the central one, then 2a, is taken.
-RT_DEV int mc_code(double a, double b, bool small_a, bool small_b) {
-  const double c = 0.5 * (a + b);
-  const double aa = fabs(a), ab = fabs(b), ac = fabs(c);
-  const bool zero = (a * b <= 0.0) || small_a || small_b;
-  const bool central = (ac <= 2.0 * aa) && (ac <= 2.0 * ab);
-  const bool left = aa <= ab;
-  return zero ? 0 : (central ? 1 : (left ? 2 : 3));
+RT_DEV int mc_code(double a, double b, double m, bool small) {
+  const bool central = fabs(0.5 * (a + b)) <= 2.0 * m;
+  const bool left = fabs(a) <= fabs(b);
+  return mc_zero(a, b, small) ? 0 : (central ? 1 : (left ? 2 : 3));
 }
 
 // Weights (d s/d a, d s/d b) of an MC case.
@@ -141,30 +142,34 @@ RT_DEV void mc_weights(int code, double& wa, double& wb) {
 }
 
 // Slopes of the four primitives (and, if CODES, their cases packed 2 bits
-// per variable).  A difference is negligible below kTieTol times the centre
+// per variable), from the differences a to the cell below and b to the cell
+// above (mc4: from the three cells).  A difference is negligible below kTieTol times the centre
 // cell's density, pressure, or sound speed (velocities: d^2 <= kTieTol^2
 // gamma p / rho).
 template <bool CODES>
-RT_DEV W4 mc4(const Params& P, const W4& m, const W4& c, const W4& p, int& codes) {
+RT_DEV W4 mc4_diff(const Params& P, const W4& c, double ar, double au, double av, double ap, double br, double bu,
+                   double bv, double bp, int& codes) {
   const double tr = kTieTol * c.r, tp = kTieTol * c.p, tv2 = kTieTol * kTieTol * P.gamma * c.p * c.ri;
   W4 s;
-  const double ar = c.r - m.r, br = p.r - c.r;
-  const double au = c.u - m.u, bu = p.u - c.u;
-  const double av = c.v - m.v, bv = p.v - c.v;
-  const double ap = c.p - m.p, bp = p.p - c.p;
-  const bool sar = fabs(ar) <= tr, sbr = fabs(br) <= tr;
-  const bool sau = au * au <= tv2, sbu = bu * bu <= tv2;
-  const bool sav = av * av <= tv2, sbv = bv * bv <= tv2;
-  const bool sap = fabs(ap) <= tp, sbp = fabs(bp) <= tp;
-  s.r = mc_value(ar, br, sar, sbr);
-  s.u = mc_value(au, bu, sau, sbu);
-  s.v = mc_value(av, bv, sav, sbv);
-  s.p = mc_value(ap, bp, sap, sbp);
+  // the smaller difference is negligible if either is (squares round
+  // monotonically)
+  const double mr = fmin(fabs(ar), fabs(br)), mu = fmin(fabs(au), fabs(bu));
+  const double mv = fmin(fabs(av), fabs(bv)), mp = fmin(fabs(ap), fabs(bp));
+  const bool zr = mr <= tr, zu = mu * mu <= tv2, zv = mv * mv <= tv2, zp = mp <= tp;
+  s.r = mc_value(ar, br, mr, zr);
+  s.u = mc_value(au, bu, mu, zu);
+  s.v = mc_value(av, bv, mv, zv);
+  s.p = mc_value(ap, bp, mp, zp);
   s.ri = 0.0;
   if (CODES)
-    codes = mc_code(ar, br, sar, sbr) | (mc_code(au, bu, sau, sbu) << 2) | (mc_code(av, bv, sav, sbv) << 4) |
-            (mc_code(ap, bp, sap, sbp) << 6);
+    codes = mc_code(ar, br, mr, zr) | (mc_code(au, bu, mu, zu) << 2) | (mc_code(av, bv, mv, zv) << 4) |
+            (mc_code(ap, bp, mp, zp) << 6);
   return s;
+}
+template <bool CODES>
+RT_DEV W4 mc4(const Params& P, const W4& m, const W4& c, const W4& p, int& codes) {
+  return mc4_diff<CODES>(P, c, c.r - m.r, c.u - m.u, c.v - m.v, c.p - m.p, p.r - c.r, p.u - c.u, p.v - c.v, p.p - c.p,
+                         codes);
 }
 
 // y slope of the pressure in the well-balanced variant: the cell's own
@@ -175,13 +180,18 @@ RT_DEV W4 mc4(const Params& P, const W4& m, const W4& c, const W4& p, int& codes
 // or differ in sign, so the two pressures at a face agree and the pressure
 // difference across the cell cancels the gravity source.
 template <bool CODES>
-RT_DEV void mc_p_balanced(const Params& P, const W4& m, const W4& c, const W4& p, W4& s, int& codes) {
+RT_DEV void mc_p_balanced_diff(const Params& P, const W4& c, double pa, double pb, W4& s, int& codes) {
   const double h = c.r * (P.g_y * P.dy);
   const double tp = kTieTol * c.p;
-  const double a = (c.p - m.p) - h, b = (p.p - c.p) - h;
-  const bool sa = fabs(a) <= tp, sb = fabs(b) <= tp;
-  s.p = h + mc_value(a, b, sa, sb);
-  if (CODES) codes = (codes & ~(3 << 6)) | (mc_code(a, b, sa, sb) << 6);
+  const double a = pa - h, b = pb - h;
+  const double m = fmin(fabs(a), fabs(b));
+  const bool z = m <= tp;
+  s.p = h + mc_value(a, b, m, z);
+  if (CODES) codes = (codes & ~(3 << 6)) | (mc_code(a, b, m, z) << 6);
+}
+template <bool CODES>
+RT_DEV void mc_p_balanced(const Params& P, const W4& m, const W4& c, const W4& p, W4& s, int& codes) {
+  mc_p_balanced_diff<CODES>(P, c, c.p - m.p, p.p - c.p, s, codes);
 }
 
 // Ghost cells of the y walls: mirror of the adjacent interior cell with the
@@ -274,8 +284,8 @@ RT_DEV HllcCore hllc_core(const Params& P, const FS& L, const FS& R) {
   h.t = h.left ? L.t : R.t;
   h.p = h.left ? L.p : R.p;
   h.S = h.left ? h.SL : h.SR;
-  h.d = h.left ? h.dL : h.dR;
-  h.m = h.left ? h.mL : h.mR;
+  h.d = h.S - h.n;  // dL or dR, mL or mR to the bit
+  h.m = h.r * h.d;
   h.act = h.left ? (h.SL < 0.0) : (h.SR > 0.0);
   h.sig = h.act ? h.S : 0.0;
   h.E = h.p * P.inv_gm1 + 0.5 * h.r * (h.n * h.n + h.t * h.t);

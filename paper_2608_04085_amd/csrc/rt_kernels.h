@@ -121,7 +121,8 @@ enum TileId {
   TILE_32x16 = 9,
   TILE_16x15 = 10,
   TILE_15x16 = 11,
-  TILE_COUNT = 12
+  TILE_COUNT = 12,
+  TILE_COLUMNS = 100  // not a tile: the column kernels (rt_columns.hip), same results
 };
 void tile_dims(int tile, int* tx, int* ty, int* nt);
 int step_blocks(const Params& P, int tile);  // blocks per member
@@ -131,6 +132,8 @@ hipError_t launch_init_state(const Params& P, const double* uv0, double* U, cons
 // Background pressure per row of the well-balanced variant into prow[ny].
 hipError_t launch_background_rows(const Params& P, double* prow, hipStream_t s);
 hipError_t launch_step(const Params& P, int tile, const StepArgs& a, hipStream_t s);
+// The same step by the column kernel (launch_step with TILE_COLUMNS).
+hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s);
 // Adjoint of one step: kernel A (face and predictor adjoints -> Z, codes),
 // then kernel B (limiter gather -> lambda^n), or kernel A alone
 // (gather = false) when the next kernel A folds the gather in.

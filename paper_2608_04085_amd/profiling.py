@@ -1,7 +1,8 @@
 """Counter runs of the hot-path kernels and their summaries.
 
     python -m paper_2608_04085_amd.profiling drive NX NY B K STEP_TILE ADJ_TILE
-        (STEP_TILE "auto": the autotuner's choice, as bench.py makes it.)
+        (STEP_TILE "auto": the autotuner's choice; "default": the
+        context's own, column kernels where it runs them.)
         The library's kernel-timing hook (K launches each of the step at a
         given dt, the march step, the folded adjoint step and the two-kernel
         adjoint step on one grid), then K copies of a 2 GiB buffer: a plain
@@ -39,7 +40,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_device.h", "csrc/rt_kernels.h"]
+KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_columns.hip", "csrc/rt_device.h", "csrc/rt_wave.h",
+                  "csrc/rt_kernels.h"]
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
 COUNTERS_JSON = os.path.join(ROOT, "profiles", "counters.json")
 COPY_BYTES = 2 * 1024**3
@@ -66,10 +68,10 @@ def drive(nx: int, ny: int, B: int, K: int, step_tile: str, adj_tile: str):
     U = rt.init_state(inputs.seed_batch(cfg, range(B), rms=1e-3))
     if step_tile == "auto":
         rt.autotune(U, reps=20)
-    else:
+    elif step_tile != "default":
         rt.set_tiles(step_tile, adj_tile)
     times = rt.kernel_times(U, reps=K)
-    print(json.dumps({"grid": f"{nx}x{ny}x{B}", "tiles": rt.tile, "fold": rt.fold, "times_us": times}), flush=True)
+    print(json.dumps({"grid": f"{nx}x{ny}x{B}", "tiles": rt.kernels, "fold": rt.fold, "times_us": times}), flush=True)
     n = COPY_BYTES // 8
     a = torch.empty(n, dtype=torch.float64, device="cuda").fill_(1.0)
     flush = torch.empty(n, dtype=torch.float64, device="cuda").fill_(2.0)  # evicts a from the last-level cache
@@ -78,7 +80,7 @@ def drive(nx: int, ny: int, B: int, K: int, step_tile: str, adj_tile: str):
         b.copy_(a)
         flush.fill_(3.0)
     torch.cuda.synchronize()
-    print(f"drive done {nx}x{ny}x{B} K={K} tiles={rt.tile} {json.dumps(times)}", flush=True)
+    print(f"drive done {nx}x{ny}x{B} K={K} tiles={rt.kernels} {json.dumps(times)}", flush=True)
 
 
 def _rows(d: str, name: str):
@@ -204,6 +206,13 @@ def summarize(workload: str, trace: str, fetch: str, write: str, req: str | None
     with open(TRAFFIC_JSON, "w") as f:
         json.dump(data, f, indent=1)
     print("\n".join(lines))
+
+
+def key_for(workload: str, kernels: str) -> str:
+    """Where the counters of `workload` stand for the kernels that run
+    ("step/adjoint", Context.kernels): the tile kernels' under the workload's
+    own name, the column kernels' beside them."""
+    return workload + "_columns" if "columns" in kernels else workload
 
 
 def traffic_for(workload: str, kernel: str, tiles: str | None = None) -> float | None:

@@ -22,6 +22,7 @@ LIB_PATH = os.path.join(_HERE, "librtcnop.so")
 STATUS = {0: "RT_OK", -1: "RT_EINVAL", -2: "RT_EHIP", -3: "RT_ENOMEM", -4: "RT_EUNPHYS", -5: "RT_ESTATE"}
 TILES = {"16x16": 0, "32x8": 1, "64x4": 2, "16x16w": 3, "32x8w": 4, "16x8": 5, "8x8": 6, "16x8w": 7, "8x8w": 8, "32x16": 9,
          "16x15": 10, "15x16": 11}
+COLUMNS_STEP = 1
 DT_MODES = {"frozen": 0, "differentiated": 1}
 DT_MODES_BY_ID = {v: k for k, v in DT_MODES.items()}
 
@@ -90,6 +91,8 @@ def load():
         "rt_kernel_times": [_vp, _vp, _i32, ctypes.POINTER(ctypes.c_double)],
         "rt_set_fold": [_vp, _i32],
         "rt_set_tiles": [_vp, _i32, _i32],
+        "rt_set_columns": [_vp, _i32],
+        "rt_get_columns": [_vp, ctypes.POINTER(_i32)],
         "rt_ek_field": [_vp, _vp, _vp],
         "rt_mix_width": [_vp, _vp, _vp],
         "rt_row_spectrum": [_vp, _vp, ctypes.c_int64, _i32, _vp],
@@ -123,7 +126,7 @@ EXPORTED = ["rt_create", "rt_destroy", "rt_set_stream", "rt_workspace_bytes", "r
             "rt_set_tiles", "rt_ek_field", "rt_ek_anomaly", "rt_grad_ek_anomaly",
             "rt_mix_width", "rt_set_dt_mode", "rt_get_dt_mode", "rt_get_tile", "rt_revolve_stats",
             "rt_row_spectrum", "rt_ke_ratio", "rt_revolve_plan_stats", "rt_ke_ratio_noalloc",
-            "rt_power_spectrum_2d"]
+            "rt_power_spectrum_2d", "rt_set_columns", "rt_get_columns"]
 
 
 def _check(rc: int, call: str):
@@ -250,6 +253,22 @@ class Context:
 
     def set_tiles(self, step: str, adjoint: str):
         _check(load().rt_set_tiles(self._h, TILES[step], TILES[adjoint]), "rt_set_tiles")
+
+    @property
+    def columns(self) -> int:
+        """Column kernels in use in place of the tile kernels (a mask of COLUMNS_*)."""
+        m = ctypes.c_int32()
+        _check(load().rt_get_columns(self._h, ctypes.byref(m)), "rt_get_columns")
+        return m.value
+
+    def set_columns(self, mask: int):
+        _check(load().rt_set_columns(self._h, int(mask)), "rt_set_columns")
+
+    @property
+    def kernels(self) -> str:
+        """What runs, "step/adjoint": a tile variant or "columns"."""
+        step, adj = self.tile.split("/")
+        return f"{'columns' if self.columns & COLUMNS_STEP else step}/{adj}"
 
     def set_graphs(self, on: bool):
         _check(load().rt_set_graphs(self._h, 1 if on else 0), "rt_set_graphs")

@@ -1,0 +1,102 @@
+"""GPU: the column kernels against the tile kernels (the same bits: both
+evaluate the same expressions) and against the oracle, at the edges of their
+strips (60 columns), of their row segments and of the grid."""
+import numpy as np
+import pytest
+import torch
+
+from oracle.rto import Oracle
+from paper_2608_04085_amd import inputs
+from paper_2608_04085_amd.config import CKPT_UNIFORM, RECON_BALANCED, RTConfig, paper_preset
+
+pytestmark = pytest.mark.gpu
+
+# one strip with its halos wrapping onto itself, a full strip, one column
+# more, two strips and a bit; segments of one row (small batches), of several
+# rows (64 members), and whole columns (1100 members)
+CASES = [
+    RTConfig(nx=3, ny=2),
+    RTConfig(nx=59, ny=3, batch=2),
+    RTConfig(nx=60, ny=61),
+    RTConfig(nx=61, ny=40, batch=3),
+    RTConfig(nx=130, ny=37, batch=64),
+    RTConfig(nx=5, ny=9, batch=1100),
+    paper_preset(62, batch=40).with_(recon=RECON_BALANCED),
+]
+IDS = [f"{c.nx}x{c.ny}x{c.batch}-{c.recon}" for c in CASES]
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def contexts(cfg, max_steps=256):
+    from paper_2608_04085_amd import rtcnop
+    cols = rtcnop.Context(cfg, max_steps=max_steps)
+    cols.set_columns(rtcnop.COLUMNS_STEP)
+    tiles = rtcnop.Context(cfg, max_steps=max_steps, tile="16x15")
+    assert tiles.columns == 0 and cols.columns == rtcnop.COLUMNS_STEP
+    return cols, tiles
+
+
+def states(cfg):
+    rng = np.random.default_rng(cfg.nx * 1000 + cfg.ny)
+    amp = 3e-2 if cfg.lx == 0.5 else 1e-1
+    uv = amp * rng.standard_normal((cfg.batch, 2, cfg.ny, cfg.nx))
+    return inputs.mask_components(uv, cfg.comp_mask)
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=IDS)
+def test_step_by_columns_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg):
+    cols, tiles = contexts(cfg)
+    U = tiles.init_state(states(cfg))
+    for _ in range(2):
+        U = tiles.step(U)
+    dt = tiles.cfl_dt(U)
+    Uc, nc = cols.step(U, dt, want_next=True)
+    Ut, nt = tiles.step(U, dt, want_next=True)
+    np.testing.assert_array_equal(host(Uc), host(Ut))
+    np.testing.assert_array_equal(host(nc), host(nt))
+    np.testing.assert_array_equal(host(cols.step(U, dt)), host(Ut))
+    cols.check_error()
+    members = sorted({0, cfg.batch - 1})
+    o = Oracle.from_config(cfg.with_(batch=len(members)))
+    want = o.step(np.ascontiguousarray(host(U)[members]), np.ascontiguousarray(host(dt)[members]))
+    for k in range(4):
+        assert np.max(np.abs(host(Uc)[members][:, k] - want[:, k])) <= 1e-13 * np.max(np.abs(want[:, k]))
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[4], CASES[6]], ids=[IDS[1], IDS[4], IDS[6]])
+def test_march_and_gradient_by_columns_have_the_bits_of_the_tiles(cfg):
+    # members of different step counts, the step log, and snapshots written
+    # by the step kernel
+    from paper_2608_04085_amd import rtcnop
+    uv = states(cfg) * np.linspace(0.1, 1.0, cfg.batch)[:, None, None, None]
+    cols, tiles = contexts(cfg, max_steps=512)
+    T = 20.3 * float(host(tiles.cfl_dt(tiles.init_state(uv))).min())
+    a = cols.integrate(cols.init_state(uv), T, log_cap=512)
+    b = tiles.integrate(tiles.init_state(uv), T, log_cap=512)
+    n = host(a[2])
+    np.testing.assert_array_equal(n, host(b[2]))
+    np.testing.assert_array_equal(host(a[0]), host(b[0]))
+    for m in range(cfg.batch):
+        np.testing.assert_array_equal(host(a[3])[m, : n[m]], host(b[3])[m, : n[m]])
+    pol = rtcnop.Policy(CKPT_UNIFORM, 4)
+    Ra, ga, _ = cols.grad_u0(uv, T, pol)
+    Rb, gb, _ = tiles.grad_u0(uv, T, pol)
+    np.testing.assert_array_equal(host(Ra), host(Rb))
+    np.testing.assert_array_equal(host(ga), host(gb))
+
+
+def test_unphysical_state_is_reported_by_the_column_step():
+    from paper_2608_04085_amd import rtcnop
+    cfg = RTConfig(nx=70, ny=20)
+    cols, _ = contexts(cfg)
+    for var, value in ((3, -1.0), (0, -0.5), (0, float("nan")), (2, float("inf"))):
+        U = cols.init_state(states(cfg))
+        U[0, var, 13, 61] = value
+        cols.step(U, torch.tensor([1e-4]))
+        with pytest.raises(rtcnop.RTError) as e:
+            cols.check_error()
+        assert e.value.code == -4
+        cols.check_error()  # the flag is cleared
