@@ -163,7 +163,7 @@ def roofline(kind, kt_us, cells, traffic, counters):
         "traffic": None if traffic is None else round(traffic, 1),
         "algorithmic_flops_per_launch": flops,
         "kernel": ("fused forward step (k_step or k_step_cols with the CFL epilogue, march)" if kind == "step"
-                   else "adjoint step (k_adj_a + k_adj_b)"),
+                   else "adjoint step (k_adj_a + k_adj_b, or k_adj_cols)"),
         "launch_us": round(kt_us, 3),
         "hbm": {"achieved": round(gb, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gb / HBM_PEAK_GBS, 5),
                 "algorithmic_bytes_per_launch": nbytes},
@@ -245,7 +245,8 @@ def scale_point(kernel_launches: int = 10) -> dict:
     kern = ctx8.kernels
     out = {"workload": "8 x 1024 x 2048, one launch per step", "tile": kern}
     for key, t_us, tkey, parts in (("step", kt8["step_march_us"], "step_march", ["step_march"]),
-                                   ("adjoint", kt8["adjoint_two_kernel_us"], "adjoint", ["adj_a", "adj_b"])):
+                                   ("adjoint", kt8["adjoint_two_kernel_us"], "adjoint",
+                                    profiling.adjoint_parts(kern))):
         out[key] = roofline(key, t_us, cells8,
                             profiling.traffic_for(profiling.key_for("step_8x1024x2048", kern), tkey, kern),
                             profiling.counters_for(profiling.key_for("8x1024x2048", kern), parts, kern))
@@ -337,7 +338,7 @@ def main():
     kern = ctx.kernels
     tkey = profiling.key_for("cnop_8x512x1024", kern)
     adj = roofline("adjoint", kt["adjoint_two_kernel_us"], cells, profiling.traffic_for(tkey, "adjoint", kern),
-                   profiling.counters_for(tkey, ["adj_a", "adj_b"], kern))
+                   profiling.counters_for(tkey, profiling.adjoint_parts(kern), kern))
     stp = roofline("step", kt["step_march_us"], cells, profiling.traffic_for(tkey, "step_march", kern),
                    profiling.counters_for(tkey, ["step_march"], kern))
     dom, other = (adj, stp) if t_adj >= t_fwd else (stp, adj)

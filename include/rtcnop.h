@@ -282,11 +282,13 @@ int rt_set_tile(rt_ctx* ctx, int32_t tile);
 int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
 /* Column kernels in place of the tile kernels, a mask of RT_COLUMNS_*: one
  * wavefront marches a strip of columns upward with its rows in registers,
- * without LDS or barriers.  Results are those of every tile variant to the
- * bit.  The default: the step beyond three 32x8 blocks per CU of cells in
- * all; rt_set_tile and rt_set_tiles set the mask to 0, rt_autotune to what
+ * without barriers; the adjoint takes one launch per step and leaves no
+ * intermediates in memory.  Results are those of every tile variant to the
+ * bit.  The adjoint of differentiated time steps and the folded sweep run
+ * the tile kernels either way.  The default: both beyond three 32x8 blocks
+ * per CU of cells in all; rt_set_tile and rt_set_tiles set the mask to 0, rt_autotune to what
  * it measures as faster. */
-enum { RT_COLUMNS_STEP = 1 };
+enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2 };
 int rt_set_columns(rt_ctx* ctx, int32_t mask);
 int rt_get_columns(const rt_ctx* ctx, int32_t* mask);
 /* The adaptive march replays captured HIP graphs of 48 steps (on = 1, the

@@ -58,6 +58,8 @@ struct rt_ctx {
   int tile_adj;  // tile variant of the adjoint kernel
   int columns = 0;  // RT_COLUMNS_* kernels that run in place of the tile kernels (same results)
   int step_variant() const { return (columns & RT_COLUMNS_STEP) ? (int)rtk::TILE_COLUMNS : tile; }
+  // the adjoint step of frozen time steps outside the folded sweep
+  int adj_variant() const { return (columns & RT_COLUMNS_ADJOINT) ? (int)rtk::TILE_COLUMNS : tile_adj; }
   int red_blocks;
   // workspace
   char* ws = nullptr;
@@ -364,12 +366,14 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   // of 256 threads: every face loop is one pass of the block (255 and 256
   // faces of each direction; the step's single face list two), and four
   // small blocks per CU hide one another's barriers better than two large
-  // ones.  Beyond one round the step runs the column kernel instead, which
-  // has no barriers and almost no halo work: given dt / march step in us,
-  // tiles against columns, 12.3 / 14.2 against 13.9 / 16.4 at 2 x 256x512,
-  // 17 / 19.5 against 22 / 24.5 at 512x1024, 84 / 94 against 153 / 172 at
-  // 8 x 512x1024; below it a launch lasts as long as one wavefront's chain
-  // of rows and the tiles win (7.7 / 9.1 against 8.4 / 10.2 at 256x512).
+  // ones.  Beyond one round the column kernels run instead, which have no
+  // barriers, almost no halo work and, in the adjoint, no intermediates in
+  // memory: step at a given dt / march step / adjoint step in us, columns
+  // against tiles, 12 / 14 / 29 against 14 / 16.5 / 28.5 at 2 x 256x512,
+  // 18 / 20 / 41 against 22 / 25 / 46 at 512x1024, 87 / 95 / 201 against
+  // 155 / 172 / 398 at 8 x 512x1024; below it a launch lasts as long as one
+  // wavefront's chain of rows and the tiles win (7.7 / 9.1 / 18.6 against
+  // 8.4 / 10.2 / 28 at 256x512).
   // rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
   const bool tiny = all_cells < ((size_t)1 << 16);
@@ -381,7 +385,7 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   c->tile = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x16 : rtk::TILE_16x15);
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
   c->fold = tiny;
-  c->columns = one_round ? 0 : RT_COLUMNS_STEP;
+  c->columns = one_round ? 0 : RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT;
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));
   *out = c;
@@ -410,7 +414,7 @@ int rt_set_tile(rt_ctx* c, int32_t tile) {
 
 int rt_set_columns(rt_ctx* c, int32_t mask) {
   if (!c) return fail(RT_EINVAL, "null context");
-  if (mask & ~RT_COLUMNS_STEP) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
+  if (mask & ~(RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT)) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
   c->columns = mask;
   return 0;
 }
@@ -543,7 +547,8 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
     return e;
   };
   hipError_t e = rtk::launch_step(P, step_tile, a, s);
-  if (e == hipSuccess) e = rtk::launch_adjoint(P, adj_tile, j, s, false);  // fills Z, codes for the fold
+  const int fold_tile = adj_tile == rtk::TILE_COLUMNS ? c->tile_adj : adj_tile;
+  if (e == hipSuccess) e = rtk::launch_adjoint(P, fold_tile, j, s, false);  // fills Z, codes for the fold
   if (e == hipSuccess) e = timed([&](int) { return rtk::launch_step(P, step_tile, a, s); }, &out[0]);
   if (e == hipSuccess) e = rtk::launch_copy(U, c->S0, se, s);
   if (e == hipSuccess) e = rtk::launch_reduce(P, 0, c->S0, nullptr, c->partial, c->red_blocks, c->sc(0), s);
@@ -574,7 +579,7 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
           f.fold.lam_next = c->L0;
           f.fold.lam_out = c->L1;
           f.fold.dt_index = 0;
-          return rtk::launch_adjoint(P, adj_tile, f, s, false);
+          return rtk::launch_adjoint(P, fold_tile, f, s, false);
         },
         &out[2]);
   if (e == hipSuccess) e = timed([&](int) { return rtk::launch_adjoint(P, adj_tile, j, s); }, &out[3]);
@@ -599,13 +604,14 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   hipEvent_t e0, e1;
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
-  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f, best_c = 1e30f;
+  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f, cols_s = 1e30f, cols_a = 1e30f;
   int bs = c->tile, bfold = c->tile_adj, bunf = c->tile_adj;
   int rc = 0;
   {
-    float ms[4];
-    rc = time_kernels(c, U, rtk::TILE_COLUMNS, c->tile_adj, reps, e0, e1, ms);
-    best_c = ms[0] + ms[1];
+    float ms[4] = {0, 0, 0, 0};
+    rc = time_kernels(c, U, rtk::TILE_COLUMNS, rtk::TILE_COLUMNS, reps, e0, e1, ms);
+    cols_s = ms[0] + ms[1];
+    cols_a = ms[3];
   }
   for (int t = 0; t < rtk::TILE_COUNT && rc == 0; ++t) {
     float ms[4];
@@ -620,7 +626,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   // leaves less room on the CUs for the concurrent re-computation, which
   // costs it about 10% there relative to its time alone; so it is taken
   // only when it is more than 10% faster alone.
-  const bool fold = c->P.recon == RT_RECON_PRIMITIVE && best_f < 0.9f * best_u;
+  const bool fold = c->P.recon == RT_RECON_PRIMITIVE && best_f < 0.9f * std::min(best_u, cols_a);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
@@ -629,7 +635,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   c->tile = bs;
   c->tile_adj = ba;
   c->fold = fold;
-  c->columns = best_c < best_s ? RT_COLUMNS_STEP : 0;
+  c->columns = (cols_s < best_s ? RT_COLUMNS_STEP : 0) | (cols_a < best_u ? RT_COLUMNS_ADJOINT : 0);
   if (step_tile) *step_tile = bs;
   if (adj_tile) *adj_tile = ba;
   Flags f{};
@@ -649,7 +655,7 @@ int rt_kernel_times(rt_ctx* c, const double* U, int32_t reps, double* out) {
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
   float ms[4] = {0, 0, 0, 0};
-  const int rc = time_kernels(c, U, c->step_variant(), c->tile_adj, reps, e0, e1, ms);
+  const int rc = time_kernels(c, U, c->step_variant(), c->adj_variant(), reps, e0, e1, ms);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
@@ -853,7 +859,7 @@ int rt_step_adjoint(rt_ctx* c, const double* U, const double* dt, const double* 
   a.dt_stride = 1;
   a.dt_index = 0;
   a.flags = c->flags;
-  RT_HIP(rtk::launch_adjoint(c->P, c->tile_adj, a, c->stream));
+  RT_HIP(rtk::launch_adjoint(c->P, c->adj_variant(), a, c->stream));
   return 0;
 }
 
@@ -990,7 +996,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dtd.count = rtk::step_blocks(P, c->tile_adj);
       a.dtd.mu_last = c->dtd_mu_last;
     }
-    RT_HIP(rtk::launch_adjoint(P, c->tile_adj, a, s));
+    RT_HIP(rtk::launch_adjoint(P, dtd ? c->tile_adj : c->adj_variant(), a, s));
     if (dtd) RT_HIP(rtk::launch_dt_correct(P, a, s));  // updates lambda^n (a.lam) in place
     std::swap(lam, lam_other);
     return 0;
@@ -1192,7 +1198,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
         a.dtd.count = rtk::step_blocks(G.P, c->tile_adj);
         a.dtd.mu_last = c->dtd_mu_last + G.b0;
       }
-      RT_HIP(rtk::launch_adjoint(G.P, c->tile_adj, a, G.st));
+      RT_HIP(rtk::launch_adjoint(G.P, dtd ? c->tile_adj : c->adj_variant(), a, G.st));
       if (dtd) RT_HIP(rtk::launch_dt_correct(G.P, a, G.st));  // updates lambda^n (a.lam) in place
       std::swap(G.lam, G.lam_other);
       return 0;

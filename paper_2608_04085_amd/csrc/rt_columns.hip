@@ -1,7 +1,7 @@
 // Column kernels: one wavefront marches a strip of columns upward, one cell
 // per lane and one row per iteration, with the rows a stencil needs in
 // registers and x neighbours taken from the next lane (a lane shift of the
-// whole wavefront).  No LDS and no barriers; what the tile kernels compute
+// whole wavefront).  No barriers; what the tile kernels compute
 // again for every tile's halo (primitives 1.58 and predictor 1.28 times per
 // cell on 16x15 tiles) is computed once but for the outer lanes of a strip
 // (4 of 64) and two rows around a segment.  The expressions are those of the
@@ -14,6 +14,18 @@
 // against columns, us: 8 x 1024x2048 550 -> 320 given dt and 590 -> 348 in
 // the march; 8 x 512x1024 153 -> 84 and 172 -> 94; 64 x 128x256 79 -> 58 and
 // 95 -> 63; 1024x2048 68 -> 47 and 77 -> 51.
+//
+// k_adj_cols is the whole adjoint of a step in one launch: about 1100 VALU
+// instructions per row and wavefront, and no intermediates in memory (the
+// tile pair moves 1294 MiB per launch at 8 x 512x1024, most of it between its
+// two kernels).  It is bound by registers and latency: 220 registers per lane
+// leave two wavefronts per SIMD, so what a row hands to the next waits in LDS
+// (36 doubles per lane), is read again by each phase that needs it, and the
+// limiter cases are formed at once (left to the end of the row they keep the
+// 8 slopes' differences in registers: 256 and spills, 227 us against 201 at
+// 8 x 512x1024; with all of it in registers 398).  Tiles against columns, us:
+// 8 x 1024x2048 1530 -> 750, 8 x 512x1024 398 -> 201, 64 x 128x256 198 -> 147,
+// 512x1024 46 -> 41.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,6 +55,9 @@ __device__ __forceinline__ double from_left(double v) {
   const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x138, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
+
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ double uniform(double v) { return read_lane(v, 0); }
 
 struct Raw {
   double r, mx, my, E;
@@ -279,21 +294,299 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   if (last) atomicSub(&a.flags->n_active, 1);
 }
 
-// Row segments of a launch: k wavefronts per SIMD, k = 1, 2 or 3 (the most
-// that fit at their register count), the k with the least of
-// c_k (rows per segment + 2.3).  That is the measured time of a launch less
-// a constant 3 us: a segment costs its rows and the 2.3 rows' worth below and
-// above it, and a row 1.23, 2.10, 3.03 us with 1, 2, 3 wavefronts on a SIMD
-// (512x1024 x 4 and x 8 given dt: 51.2 and 95.9 us with one, 46.8 and 85.2
-// with two, 46.3 and 83.7 with three; 512x1024: 17.7, 17.1, 16.9).
+// Adjoint of one step.  lambda^n of a cell needs the slope cotangents of the
+// cell and its four neighbours, these the cotangents of their faces, these
+// the predicted states across the faces: three columns and three rows to
+// each side in all.
+constexpr int kAdjHalo = 3, kAdjOwn = 64 - 2 * kAdjHalo;
+
+struct Lam {
+  double v[4];
+};
+__device__ __forceinline__ Lam load_lam(const Params& P, const double* Lm, size_t N, int gy, uint32_t col) {
+  const int sy = gy < 0 ? 0 : (gy >= P.ny ? P.ny - 1 : gy);
+  const double* p = Lm + (size_t)sy * P.nx;
+  return Lam{{ldg(p, col), ldg(p + N, col), ldg(p + 2 * N, col), ldg(p + 3 * N, col)}};
+}
+
+// Products of a slope cotangent with the weights of its MC case: pa of the
+// backward difference, pb of the forward one.  The weights are 0, 1/2 or 2,
+// so the products are exact and adding them is what a fused multiply-add of
+// weight and cotangent gives.
+__device__ __forceinline__ void slope_products(const W4& s, int code, double pa[4], double pb[4]) {
+  const double sb[4] = {s.r, s.u, s.v, s.p};
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    double wa, wb;
+    mc_weights((code >> (2 * v)) & 3, wa, wb);
+    pa[v] = wa * sb[v];
+    pb[v] = wb * sb[v];
+  }
+}
+
+// What a row hands on through LDS, each lane its own (registers bound the
+// wavefronts in flight).  Row k = m - 1: slopes, primitives, lambda^{n+1} and
+// the cotangent its lower face gives it.  Row g = m - 2: slope terms so far,
+// direct part, forward products of the y slopes and (u, v, 1/rho).
+enum { kSx = 0, kSy = 4, kPrim = 8, kLam = 13, kYb = 17, kAcc = 21, kDir = 25, kFwd = 29, kVel = 33, kAdjKept = 36 };
+
+// Between the phases of a row: what the next phase needs from LDS is read
+// again there instead of staying in registers.
+__device__ __forceinline__ void phase() { asm volatile("" ::: "memory"); }
+
+template <bool BAL>
+__global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArgs a, int strips, int segs) {
+  __shared__ double sRow[kColWaves][kAdjKept][64];
+  const int lane = threadIdx.x & 63;
+  const int per = strips * segs;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int w = xcd_band((int)blockIdx.x, (int)gridDim.x) * kColWaves + wave;
+  if (w >= per * P.nb) return;
+  const int b = w / per, t = w - b * per;
+  const int seg = t / strips, strip = t - seg * strips;
+  const int nx = P.nx, ny = P.ny;
+  const size_t N = (size_t)nx * ny;
+  const int ys = (int)((long)ny * seg / segs), ye = (int)((long)ny * (seg + 1) / segs);
+  const int x0 = strip * kAdjOwn;
+  const uint32_t col = (uint32_t)wrapx(x0 - kAdjHalo + lane, nx);
+  const bool own = lane >= kAdjHalo && lane < 64 - kAdjHalo && x0 - kAdjHalo + lane < nx;
+  const double* U = a.U + (size_t)b * 4 * N;
+  const double* Lm = a.lam_next + (size_t)b * 4 * N;
+  double* Lo = a.lam + (size_t)b * 4 * N;
+  if (a.nsteps_limit && a.dt_index >= a.nsteps_limit[b]) {
+    // the member finished before step n: lambda^n = lambda^{n+1}
+    for (int j = ys; j < ye; ++j) {
+      const Lam l = load_lam(P, Lm, N, j, col);
+      if (own) {
+        double* o = Lo + (size_t)j * nx;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) stg(o + v * N, col, l.v[v]);
+      }
+    }
+    return;
+  }
+  const int m0 = ys >= 2 ? ys - 2 : 0, m1 = ye + 1 < ny ? ye + 1 : ny;
+  const Raw qm = load_row(P, U, N, m0 - 1, col);
+  const Raw qc = load_row(P, U, N, m0, col);
+  Raw un = load_row(P, U, N, m0 + 1, col);
+  Lam lm = load_lam(P, Lm, N, m0, col);
+  const double dt = uniform(a.dt[(size_t)b * a.dt_stride + a.dt_index]);
+  const double hg = uniform(0.5 * dt * P.g_y), hdtg = hg;
+  const double hx = uniform(0.5 * dt * P.inv_dx), hy = uniform(0.5 * dt * P.inv_dy);
+  const double ax = uniform(dt * P.inv_dx), ay = uniform(dt * P.inv_dy);
+
+  auto kept = [&](int q) __attribute__((always_inline)) -> double& { return sRow[wave][q][lane]; };
+  auto keep4 = [&](int q, const W4& w) __attribute__((always_inline)) {
+    kept(q) = w.r;
+    kept(q + 1) = w.u;
+    kept(q + 2) = w.v;
+    kept(q + 3) = w.p;
+  };
+  auto kept4 = [&](int q) __attribute__((always_inline)) {
+    return W4{kept(q), kept(q + 1), kept(q + 2), kept(q + 3), 0.0};
+  };
+
+  // row m: primitives and the differences across its lower face
+  W4 wc = row_prims(P, qc, m0);
+  D4 da = diff(wc, row_prims(P, qm, m0 - 1));
+  W4 qk{1, 0, 0, 1, 0};  // predicted state and limiter cases of row k
+  int codek = 0;
+  bool unphys = false;
+
+  // lambda^n of row g from its slope terms (the walls' ghosts last; row 0's
+  // backward products wait in its place of lambda^n)
+  auto finish = [&](int g, double acc[4]) __attribute__((always_inline)) {
+    double* o = Lo + (size_t)g * nx;
+    if (g == 0 || g == ny - 1) {
+      double gb[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) gb[v] = g == 0 && own ? -ldg(o + v * N, col) : 0.0;
+      if (g == ny - 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gb[v] += kept(kFwd + v);
+      }
+      const double sgn = g == 0 ? -1.0 : 1.0;
+      acc[0] += gb[0] + sgn * P.g_y * P.dy * gb[3];
+      acc[1] += gb[1];
+      acc[2] -= gb[2];
+      acc[3] += gb[3];
+    }
+    double ub[4];
+    prim_adj(P, W4{1.0, kept(kVel), kept(kVel + 1), 1.0, kept(kVel + 2)}, W4{acc[0], acc[1], acc[2], acc[3]}, ub);
+    if (own) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) stg(o + v * N, col, kept(kDir + v) + ub[v]);
+    }
+  };
+
+  auto row = [&](int m) __attribute__((always_inline)) {
+    const int k = m - 1;
+    const bool complete = m > m0 && k >= ys - 1;
+    // the right face of row k
+    W4 xl{0, 0, 0, 0, 0}, xr{0, 0, 0, 0, 0};
+    if (complete) {
+      const double l2 = kept(kLam + 2);
+      const double lL[4] = {kept(kLam) + hdtg * l2, kept(kLam + 1), l2, kept(kLam + 3)};
+      const double Fb[4] = {ax * (from_right(lL[0]) - lL[0]), ax * (from_right(lL[1]) - lL[1]),
+                            ax * (from_right(lL[2]) - lL[2]), ax * (from_right(lL[3]) - lL[3])};
+      const W4 sxk = kept4(kSx);
+      FS Lb{0, 0, 0, 0}, Rb{0, 0, 0, 0};
+      hllc_adj(P, FS{qk.r + 0.5 * sxk.r, qk.u + 0.5 * sxk.u, qk.v + 0.5 * sxk.v, qk.p + 0.5 * sxk.p},
+               FS{from_right(qk.r - 0.5 * sxk.r), from_right(qk.u - 0.5 * sxk.u), from_right(qk.v - 0.5 * sxk.v),
+                  from_right(qk.p - 0.5 * sxk.p)},
+               Fb, Lb, Rb);
+      xl = W4{from_left(Rb.r), from_left(Rb.n), from_left(Rb.t), from_left(Rb.p), 0.0};
+      xr = W4{Lb.r, Lb.n, Lb.t, Lb.p, 0.0};
+    }
+    phase();
+    // row m's slopes and predicted state
+    const W4 wn = row_prims(P, un, m + 1);
+    const D4 db = diff(wn, wc);
+    const D4 xb = D4{from_right(wc.r) - wc.r, from_right(wc.u) - wc.u, from_right(wc.v) - wc.v, from_right(wc.p) - wc.p};
+    const D4 xa = D4{from_left(xb.r), from_left(xb.u), from_left(xb.v), from_left(xb.p)};
+    int cx = 0, cy = 0;
+    const W4 sx = mc4_diff<true>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, cx);
+    W4 sy = mc4_diff<true>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, cy);
+    if constexpr (BAL) mc_p_balanced_diff<true>(P, wc, da.p, db.p, sy, cy);
+    int code = cx | (cy << 8);
+    asm volatile("" : "+v"(code));  // here, while the differences are at hand
+    const W4 q = predict(P, wc, sx, sy, hx, hy, hg);
+    if (m >= ys && m < ye) {
+      const double hr = 0.5 * fabs(sx.r), hp = 0.5 * fabs(sx.p), vr = 0.5 * fabs(sy.r), vp = 0.5 * fabs(sy.p);
+      unphys |= unphysical(wc) | !(q.r - hr > 0.0) | !(q.p - hp > 0.0) | !(q.r - vr > 0.0) | !(q.p - vp > 0.0);
+    }
+    phase();
+    // the face between rows k and m
+    W4 yt{0, 0, 0, 0, 0}, yb{0, 0, 0, 0, 0};  // what it gives rows k and m
+    const FS above{q.r - 0.5 * sy.r, q.v - 0.5 * sy.v, q.u - 0.5 * sy.u, q.p - 0.5 * sy.p};
+    if (m == 0) {
+      FS T{0, 0, 0, 0};
+      wall_pressure_adj(P, above, false, ay * lm.v[2], T);
+      yb = W4{T.r, T.t, T.n, T.p, 0.0};
+    }
+    if (m > m0) {
+      FS Bb{0, 0, 0, 0}, Tb{0, 0, 0, 0};
+      const W4 syk = kept4(kSy);
+      const FS below{qk.r + 0.5 * syk.r, qk.v + 0.5 * syk.v, qk.u + 0.5 * syk.u, qk.p + 0.5 * syk.p};
+      if (m == ny) {
+        wall_pressure_adj(P, below, true, -ay * kept(kLam + 2), Bb);
+      } else {
+        const double l2 = kept(kLam + 2);
+        const double lB[4] = {kept(kLam) + hdtg * l2, kept(kLam + 1), l2, kept(kLam + 3)};
+        const double lT[4] = {lm.v[0] + hdtg * lm.v[2], lm.v[1], lm.v[2], lm.v[3]};
+        const double g0 = ay * (lT[0] - lB[0]) + hdtg * (lT[3] + lB[3]);
+        const double g1 = ay * (lT[1] - lB[1]);
+        const double g2 = ay * (lT[2] - lB[2]);
+        const double g3 = ay * (lT[3] - lB[3]);
+        const double Fb[4] = {g0, g2, g1, g3};
+        hllc_adj(P, below, above, Fb, Bb, Tb);
+        yb = W4{Tb.r, Tb.t, Tb.n, Tb.p, 0.0};
+      }
+      yt = W4{Bb.r, Bb.t, Bb.n, Bb.p, 0.0};
+    }
+    phase();
+    // the next row's loads, in flight until its slopes
+    const Raw u2 = load_row(P, U, N, m + 2, col);
+    const Lam ln = load_lam(P, Lm, N, m + 1, col);
+    if (complete) {
+      // all that row k's four faces give it
+      const W4 ybk = kept4(kYb), sxk = kept4(kSx), syk = kept4(kSy);
+      W4 wk = kept4(kPrim);
+      wk.ri = kept(kPrim + 4);
+      const W4 qx{xl.r + xr.r, xl.u + xr.u, xl.v + xr.v, xl.p + xr.p, 0.0};
+      W4 sxb{0.5 * (xr.r - xl.r), 0.5 * (xr.u - xl.u), 0.5 * (xr.v - xl.v), 0.5 * (xr.p - xl.p), 0.0};
+      const W4 qb{qx.r + ybk.r + yt.r, qx.u + ybk.u + yt.u, qx.v + ybk.v + yt.v, qx.p + ybk.p + yt.p, 0.0};
+      W4 syb{0.5 * (yt.r - ybk.r), 0.5 * (yt.u - ybk.u), 0.5 * (yt.v - ybk.v), 0.5 * (yt.p - ybk.p), 0.0};
+      W4 wb{0.0, 0.0, 0.0, 0.0, 0.0};
+      predict_adj(P, wk, sxk, syk, hx, hy, qb, wb, sxb, syb);
+      double pa[4], pb[4], ya[4], yf[4];
+      slope_products(sxb, codek & 0xff, pa, pb);
+      slope_products(syb, codek >> 8, ya, yf);
+      double acc[4];
+      if (k > ys) {
+        // row g = k - 1 takes its last term, the backward part of row k
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = kept(kAcc + v) - ya[v];
+        finish(k - 1, acc);
+      }
+      if (k == 0 && ys == 0 && own) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) stg(Lo + v * N, col, ya[v]);
+      }
+      // row k's terms in the order of the gather: the x slopes of its
+      // left neighbour, its own, its right neighbour, then its own y
+      // slopes and those of the row below
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = from_left(pb[v]);
+        s += pa[v] - pb[v];
+        s -= from_right(pa[v]);
+        s += ya[v] - yf[v];
+        acc[v] = s;
+      }
+      if constexpr (BAL) {
+        double wa, wbb;
+        mc_weights((codek >> 14) & 3, wa, wbb);
+        acc[0] += P.g_y * P.dy * (1.0 - wa - wbb) * syb.p;
+      }
+      if (k > 0 && k > ys - 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] += kept(kFwd + v);
+      }
+      double ud[4];
+      prim_adj(P, wk, wb, ud);
+      const double l2 = kept(kLam + 2);
+      kept(kDir) = ud[0] + kept(kLam) + dt * P.g_y * l2;
+      kept(kDir + 1) = ud[1] + kept(kLam + 1);
+      kept(kDir + 2) = ud[2] + l2;
+      kept(kDir + 3) = ud[3] + kept(kLam + 3);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        kept(kAcc + v) = acc[v];
+        kept(kFwd + v) = yf[v];
+      }
+      kept(kVel) = wk.u;
+      kept(kVel + 1) = wk.v;
+      kept(kVel + 2) = wk.ri;
+    }
+    // row m becomes row k
+    keep4(kSx, sx);
+    keep4(kSy, sy);
+    keep4(kPrim, wc);
+    kept(kPrim + 4) = wc.ri;
+    keep4(kYb, yb);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) kept(kLam + v) = lm.v[v];
+    qk = q;
+    codek = code;
+    wc = wn;
+    da = db;
+    un = u2;
+    lm = ln;
+  };
+  for (int m = m0; m <= m1; ++m) row(m);
+  if (ye == ny) {
+    double acc[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = kept(kAcc + v);
+    finish(ny - 1, acc);
+  }
+  if (own && unphys) atomicOr(&a.flags->err_unphys, 1);
+}
+
+// Row segments of a launch: k wavefronts per SIMD, 1 up to the most that fit
+// at the kernel's registers, the k with the least of c_k (rows per segment +
+// over).  That is the measured time of a launch in us less a constant 3: a
+// row costs c_k with k wavefronts on a SIMD, and a segment `over` rows' worth
+// below and above it.
 constexpr int kSimds = 1024;
-int row_segments(int ny, int strips, int nb) {
-  constexpr double c[3] = {1.23, 2.10, 3.03};
+template <int K>
+int row_segments(int ny, int strips, int nb, const double (&c)[K], double over) {
   int best = 1;
   double cost = 1e300;
-  for (int k = 1; k <= 3; ++k) {
+  for (int k = 1; k <= K; ++k) {
     const int segs = std::min(ny, std::max(1, (int)((long)k * kSimds / ((long)strips * nb))));
-    const double t = c[k - 1] * ((ny + segs - 1) / segs + 2.3);
+    const double t = c[k - 1] * ((ny + segs - 1) / segs + over);
     if (t < cost) {
       cost = t;
       best = segs;
@@ -301,18 +594,37 @@ int row_segments(int ny, int strips, int nb) {
   }
   return best;
 }
+// 512x1024, x 4 and x 8 members, given dt: 51.2 and 95.9 us with one
+// wavefront per SIMD, 46.8 and 85.2 with two, 46.3 and 83.7 with three;
+// 512x1024 alone 17.7, 17.1, 16.9.
+constexpr double kStepRow[3] = {1.23, 2.10, 3.03}, kStepOver = 2.3;
+// 512x1024 x 4 and x 8: 122.5 and 234 us with one, 111.7 and 201.3 with two.
+constexpr double kAdjRow[2] = {3.05, 4.9}, kAdjOver = 3.3;
 
 }  // namespace
 
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
   const int strips = (P.nx + kStepOwn - 1) / kStepOwn;
-  const int segs = row_segments(P.ny, strips, P.nb);
+  const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver);
   const long waves = (long)strips * segs * P.nb;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
   if (P.recon == 1)
     hipLaunchKernelGGL((k_step_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
   else
     hipLaunchKernelGGL((k_step_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+  return hipGetLastError();
+}
+
+hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s) {
+  if (a.fold.Z != nullptr || a.dtd.mu != nullptr) return hipErrorInvalidValue;
+  const int strips = (P.nx + kAdjOwn - 1) / kAdjOwn;
+  const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjOver);
+  const long waves = (long)strips * segs * P.nb;
+  const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
+  if (P.recon == 1)
+    hipLaunchKernelGGL((k_adj_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+  else
+    hipLaunchKernelGGL((k_adj_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
   return hipGetLastError();
 }
 

@@ -120,7 +120,7 @@ constexpr double kTieTol = 1e-10;
 // (m is negligible) come from the caller; a difference above the tolerance
 // is not zero, so a*b <= 0 is a comparison of signs.
 RT_DEV bool mc_zero(double a, double b, bool small) {
-  return small || (__double2hiint(a) ^ __double2hiint(b)) < 0;
+  return small | ((__double2hiint(a) ^ __double2hiint(b)) < 0);
 }
 RT_DEV double mc_value(double a, double b, double m, bool small) {
   const double s = fmin(2.0 * m, fabs(0.5 * (a + b)));
@@ -131,8 +131,10 @@ RT_DEV double mc_value(double a, double b, double m, bool small) {
 // Where two cases give the same value the central one, then 2a, is taken.
 RT_DEV int mc_code(double a, double b, double m, bool small) {
   const bool central = fabs(0.5 * (a + b)) <= 2.0 * m;
-  const bool left = fabs(a) <= fabs(b);
-  return mc_zero(a, b, small) ? 0 : (central ? 1 : (left ? 2 : 3));
+  const bool left = fabs(a) <= fabs(b), zero = mc_zero(a, b, small);
+  const int side = left ? 2 : 3;  // one select per statement: nested ones become branches
+  const int code = central ? 1 : side;
+  return zero ? 0 : code;
 }
 
 // Weights (d s/d a, d s/d b) of an MC case.
@@ -324,9 +326,8 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   }
   // F0 = m0 + sig (f - r); F1 = m0 n + p + sig (f SS - m0);
   // F2 = m0 t + sig (f t - r t); F3 = n (E + p) + sig (fH - E)
-  const double sigb =
-      h.act ? (Fb[0] * (h.f - h.r) + Fb[1] * (h.f * h.SS - h.m0) + Fb[2] * (h.f * h.t - h.r * h.t) + Fb[3] * (fH - h.E))
-            : 0.0;
+  const double dS = Fb[0] * (h.f - h.r) + Fb[1] * (h.f * h.SS - h.m0) + Fb[2] * (h.f * h.t - h.r * h.t) + Fb[3] * (fH - h.E);
+  const double sigb = h.act ? dS : 0.0;
   const double fb = sig * (Fb[0] + Fb[1] * h.SS + Fb[2] * h.t);
   const double fHb = sig * Fb[3];
   double SSb = sig * Fb[1] * h.f;
@@ -349,13 +350,10 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   // f = m k
   mb += fb * h.k;
   kb += fb * h.m;
-  // k = 1/(S - SS) when active
-  double Sb = 0.0;
-  if (h.act) {
-    const double kk = kb * h.k * h.k;
-    Sb -= kk;
-    SSb += kk;
-  }
+  // k = 1/(S - SS) when active (else k is 0)
+  const double kk = kb * h.k * h.k;
+  double Sb = -kk;
+  SSb += kk;
   // m0 = r n
   rb += m0b * h.n;
   nb += m0b * h.r;
@@ -366,14 +364,14 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   tb += Eb * h.r * h.t;
   // sigma = S when active
   Sb += sigb;
-  // scatter the side-K quantities to L or R
-  double rLb = 0, nLb = 0, tLb = 0, pLb = 0, rRb = 0, nRb = 0, tRb = 0, pRb = 0;
-  double SLb = 0, SRb = 0, mLb = 0, mRb = 0, dLb = 0, dRb = 0;
-  if (h.left) {
-    rLb += rb; nLb += nb; tLb += tb; pLb += pb; SLb += Sb; mLb += mb; dLb += db;
-  } else {
-    rRb += rb; nRb += nb; tRb += tb; pRb += pb; SRb += Sb; mRb += mb; dRb += db;
-  }
+  // scatter the side-K quantities to L or R (selects: lanes take both sides)
+  double rLb = h.left ? rb : 0.0, rRb = h.left ? 0.0 : rb;
+  double nLb = h.left ? nb : 0.0, nRb = h.left ? 0.0 : nb;
+  const double tLb = h.left ? tb : 0.0, tRb = h.left ? 0.0 : tb;
+  double pLb = h.left ? pb : 0.0, pRb = h.left ? 0.0 : pb;
+  double SLb = h.left ? Sb : 0.0, SRb = h.left ? 0.0 : Sb;
+  double mLb = h.left ? mb : 0.0, mRb = h.left ? 0.0 : mb;
+  double dLb = h.left ? db : 0.0, dRb = h.left ? 0.0 : db;
   // SS = num / dn, dn = mL - mR, num = pR - pL + mL nL - mR nR
   const double numb = SSb * h.rdn;
   const double dnb = -SSb * h.SS * h.rdn;
@@ -393,9 +391,13 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   SRb += dRb;
   nRb -= dRb;
   // Davis speeds
-  double cLb = 0.0, cRb = 0.0;
-  if (h.selL) { nLb += SLb; cLb -= SLb; } else { nRb += SLb; cRb -= SLb; }
-  if (h.selR) { nLb += SRb; cLb += SRb; } else { nRb += SRb; cRb += SRb; }
+  const double aLb = h.selL ? SLb : 0.0, bLb = h.selL ? 0.0 : SLb;
+  const double aRb = h.selR ? SRb : 0.0, bRb = h.selR ? 0.0 : SRb;
+  nLb += aLb;
+  nRb += bLb;
+  nLb += aRb;
+  nRb += bRb;
+  const double cLb = aRb - aLb, cRb = bRb - bLb;
   // c = sqrt(g p / r): dc/dp = g/(2 c r), dc/dr = -c/(2 r)
   pLb += cLb * 0.5 * g * h.rcL * h.riL;
   rLb -= cLb * 0.5 * h.cL * h.riL;

@@ -138,6 +138,9 @@ hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s);
 // then kernel B (limiter gather -> lambda^n), or kernel A alone
 // (gather = false) when the next kernel A folds the gather in.
 hipError_t launch_adjoint(const Params& P, int tile, const AdjArgs& a, hipStream_t s, bool gather = true);
+// The two in one launch by the column kernel (launch_adjoint with
+// TILE_COLUMNS): frozen steps, no folded gather, Z and codes unused.
+hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s);
 // Kernel B alone: lambda^n from Z, codes, U^n and lambda^{n+1} of step n.
 hipError_t launch_adj_gather(const Params& P, const AdjArgs& a, hipStream_t s);
 // Differentiated step size, after both adjoint kernels of step n (a.U = U^n,

@@ -1573,6 +1573,7 @@ static hipError_t launch_adj_a(const Params& P, int tile, const AdjArgs& a, hipS
 }
 
 hipError_t launch_adjoint(const Params& P, int tile, const AdjArgs& a, hipStream_t s, bool gather) {
+  if (tile == TILE_COLUMNS) return gather ? launch_adj_cols(P, a, s) : hipErrorInvalidValue;
   hipError_t e = launch_adj_a(P, tile, a, s);
   if (e != hipSuccess || !gather) return e;
   return launch_adj_gather(P, a, s);

@@ -45,7 +45,7 @@ KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_columns.hip", "csrc/rt_device.
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
 COUNTERS_JSON = os.path.join(ROOT, "profiles", "counters.json")
 COPY_BYTES = 2 * 1024**3
-CATEGORIES = ["step_given", "step_march", "adj_a_folded", "adj_a", "adj_b", "copy"]
+CATEGORIES = ["step_given", "step_march", "adj_a_folded", "adj_a", "adj_b", "adj_cols", "copy"]
 
 
 def kernel_source_hash() -> str:
@@ -114,6 +114,8 @@ def _classify(rows):
             cat[d] = "adj_a" if "k_adj_b" in nxt else "adj_a_folded"
         elif "k_adj_b" in n:
             cat[d] = "adj_b"
+        elif "k_adj_cols" in n:
+            cat[d] = "adj_cols"
         elif "copyBuffer" in n and d > last_lib:
             cat[d] = "copy"  # the calibration copies come after every library kernel
     return cat
@@ -182,7 +184,8 @@ def summarize(workload: str, trace: str, fetch: str, write: str, req: str | None
               f"{cp.get('FETCH_SIZE', float('nan')):.1f} KiB and WRITE_SIZE {cp.get('WRITE_SIZE', float('nan')):.1f} "
               f"KiB per dispatch: scale factors fetch {f_scale}, write {w_scale}.", ""]
     entry = {}
-    for name, parts in (("step", ["step_given"]), ("step_march", ["step_march"]), ("adjoint", ["adj_a", "adj_b"]),
+    for name, parts in (("step", ["step_given"]), ("step_march", ["step_march"]),
+                        ("adjoint", ["adj_cols"] if "adj_cols" in avg else ["adj_a", "adj_b"]),
                         ("adjoint_folded", ["adj_a_folded"])):
         if all(p in avg for p in parts):
             fb = sum(avg[p].get("FETCH_SIZE", 0.0) for p in parts) * 1024 * (f_scale or 1.0)
@@ -213,6 +216,11 @@ def key_for(workload: str, kernels: str) -> str:
     ("step/adjoint", Context.kernels): the tile kernels' under the workload's
     own name, the column kernels' beside them."""
     return workload + "_columns" if "columns" in kernels else workload
+
+
+def adjoint_parts(kernels: str) -> list:
+    """Kernel classes of one adjoint step for "step/adjoint" kernels."""
+    return ["adj_cols"] if kernels.endswith("/columns") else ["adj_a", "adj_b"]
 
 
 def traffic_for(workload: str, kernel: str, tiles: str | None = None) -> float | None:

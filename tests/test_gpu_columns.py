@@ -1,6 +1,6 @@
 """GPU: the column kernels against the tile kernels (the same bits: both
 evaluate the same expressions) and against the oracle, at the edges of their
-strips (60 columns), of their row segments and of the grid."""
+strips, of their row segments and of the grid."""
 import numpy as np
 import pytest
 import torch
@@ -11,12 +11,14 @@ from paper_2608_04085_amd.config import CKPT_UNIFORM, RECON_BALANCED, RTConfig, 
 
 pytestmark = pytest.mark.gpu
 
-# one strip with its halos wrapping onto itself, a full strip, one column
-# more, two strips and a bit; segments of one row (small batches), of several
-# rows (64 members), and whole columns (1100 members)
+# one strip with its halos wrapping onto itself, a full strip of the adjoint
+# (58 columns) and of the step (60), one column more, two strips and a bit;
+# segments of one row (small batches), of several rows (64 members), and whole
+# columns (1100 members)
 CASES = [
     RTConfig(nx=3, ny=2),
-    RTConfig(nx=59, ny=3, batch=2),
+    RTConfig(nx=58, ny=3, batch=2),
+    RTConfig(nx=59, ny=5),
     RTConfig(nx=60, ny=61),
     RTConfig(nx=61, ny=40, batch=3),
     RTConfig(nx=130, ny=37, batch=64),
@@ -33,9 +35,10 @@ def host(t):
 def contexts(cfg, max_steps=256):
     from paper_2608_04085_amd import rtcnop
     cols = rtcnop.Context(cfg, max_steps=max_steps)
-    cols.set_columns(rtcnop.COLUMNS_STEP)
+    cols.set_columns(rtcnop.COLUMNS_STEP | rtcnop.COLUMNS_ADJOINT)
     tiles = rtcnop.Context(cfg, max_steps=max_steps, tile="16x15")
-    assert tiles.columns == 0 and cols.columns == rtcnop.COLUMNS_STEP
+    cols.set_fold(False)
+    assert tiles.columns == 0 and cols.kernels == "columns/columns"
     return cols, tiles
 
 
@@ -66,7 +69,25 @@ def test_step_by_columns_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg):
         assert np.max(np.abs(host(Uc)[members][:, k] - want[:, k])) <= 1e-13 * np.max(np.abs(want[:, k]))
 
 
-@pytest.mark.parametrize("cfg", [CASES[1], CASES[4], CASES[6]], ids=[IDS[1], IDS[4], IDS[6]])
+@pytest.mark.parametrize("cfg", CASES, ids=IDS)
+def test_adjoint_by_columns_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg):
+    cols, tiles = contexts(cfg)
+    U = tiles.init_state(states(cfg))
+    for _ in range(2):
+        U = tiles.step(U)
+    dt = tiles.cfl_dt(U)
+    lam = torch.from_numpy(np.random.default_rng(7).standard_normal(U.shape)).cuda()
+    got = cols.step_adjoint(U, dt, lam)
+    np.testing.assert_array_equal(host(got), host(tiles.step_adjoint(U, dt, lam)))
+    cols.check_error()
+    members = sorted({0, cfg.batch - 1})
+    o = Oracle.from_config(cfg.with_(batch=len(members)))
+    want = o.step_vjp(*(np.ascontiguousarray(host(x)[members]) for x in (U, dt, lam)))
+    for k in range(4):
+        assert np.max(np.abs(host(got)[members][:, k] - want[:, k])) <= 1e-12 * np.max(np.abs(want[:, k]))
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[5], CASES[7]], ids=[IDS[1], IDS[5], IDS[7]])
 def test_march_and_gradient_by_columns_have_the_bits_of_the_tiles(cfg):
     # members of different step counts, the step log, and snapshots written
     # by the step kernel
@@ -88,15 +109,17 @@ def test_march_and_gradient_by_columns_have_the_bits_of_the_tiles(cfg):
     np.testing.assert_array_equal(host(ga), host(gb))
 
 
-def test_unphysical_state_is_reported_by_the_column_step():
+def test_unphysical_state_is_reported_by_the_column_kernels():
     from paper_2608_04085_amd import rtcnop
     cfg = RTConfig(nx=70, ny=20)
     cols, _ = contexts(cfg)
+    lam = torch.ones(1, 4, cfg.ny, cfg.nx, dtype=torch.float64)
     for var, value in ((3, -1.0), (0, -0.5), (0, float("nan")), (2, float("inf"))):
         U = cols.init_state(states(cfg))
         U[0, var, 13, 61] = value
-        cols.step(U, torch.tensor([1e-4]))
-        with pytest.raises(rtcnop.RTError) as e:
-            cols.check_error()
-        assert e.value.code == -4
-        cols.check_error()  # the flag is cleared
+        for call in (lambda: cols.step(U, torch.tensor([1e-4])), lambda: cols.step_adjoint(U, torch.tensor([1e-4]), lam)):
+            call()
+            with pytest.raises(rtcnop.RTError) as e:
+                cols.check_error()
+            assert e.value.code == -4
+            cols.check_error()  # the flag is cleared
