@@ -15,17 +15,19 @@
 // the march; 8 x 512x1024 153 -> 84 and 172 -> 94; 64 x 128x256 79 -> 58 and
 // 95 -> 63; 1024x2048 68 -> 47 and 77 -> 51.
 //
-// k_adj_cols is the whole adjoint of a step in one launch: about 1100 VALU
+// k_adj_cols is the whole adjoint of a step in one launch: about 990 VALU
 // instructions per row and wavefront, and no intermediates in memory (the
 // tile pair moves 1294 MiB per launch at 8 x 512x1024, most of it between its
 // two kernels).  It is bound by registers and latency: 220 registers per lane
 // leave two wavefronts per SIMD, so what a row hands to the next waits in LDS
-// (36 doubles per lane), is read again by each phase that needs it, and the
+// (40 doubles per lane), is read again by each phase that needs it, and the
 // limiter cases are formed at once (left to the end of the row they keep the
 // 8 slopes' differences in registers: 256 and spills, 227 us against 201 at
-// 8 x 512x1024; with all of it in registers 398).  Tiles against columns, us:
-// 8 x 1024x2048 1530 -> 750, 8 x 512x1024 398 -> 201, 64 x 128x256 198 -> 147,
-// 512x1024 46 -> 41.
+// 8 x 512x1024; with all of it in registers 398).  The cases travel as binary
+// exponents, so that a weight costs one ldexp, and the HLLC adjoint scatters
+// its upwind side by exact products (1100 -> 990 instructions, 201 -> 194).
+// Tiles against columns, us: 8 x 1024x2048 1530 -> 734, 8 x 512x1024 398 ->
+// 194, 64 x 128x256 198 -> 137, 512x1024 46 -> 40.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -309,21 +311,6 @@ __device__ __forceinline__ Lam load_lam(const Params& P, const double* Lm, size_
   return Lam{{ldg(p, col), ldg(p + N, col), ldg(p + 2 * N, col), ldg(p + 3 * N, col)}};
 }
 
-// Products of a slope cotangent with the weights of its MC case: pa of the
-// backward difference, pb of the forward one.  The weights are 0, 1/2 or 2,
-// so the products are exact and adding them is what a fused multiply-add of
-// weight and cotangent gives.
-__device__ __forceinline__ void slope_products(const W4& s, int code, double pa[4], double pb[4]) {
-  const double sb[4] = {s.r, s.u, s.v, s.p};
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    double wa, wb;
-    mc_weights((code >> (2 * v)) & 3, wa, wb);
-    pa[v] = wa * sb[v];
-    pb[v] = wb * sb[v];
-  }
-}
-
 // What a row hands on through LDS, each lane its own (registers bound the
 // wavefronts in flight).  Row k = m - 1: slopes, primitives, lambda^{n+1} and
 // the cotangent its lower face gives it.  Row g = m - 2: slope terms so far,
@@ -337,6 +324,7 @@ __device__ __forceinline__ void phase() { asm volatile("" ::: "memory"); }
 template <bool BAL>
 __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArgs a, int strips, int segs) {
   __shared__ double sRow[kColWaves][kAdjKept][64];
+  __shared__ int sCase[kColWaves][8][64];  // row k's limiter cases, x slopes then y slopes (mc_exponents)
   const int lane = threadIdx.x & 63;
   const int per = strips * segs;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -389,8 +377,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
   // row m: primitives and the differences across its lower face
   W4 wc = row_prims(P, qc, m0);
   D4 da = diff(wc, row_prims(P, qm, m0 - 1));
-  W4 qk{1, 0, 0, 1, 0};  // predicted state and limiter cases of row k
-  int codek = 0;
+  W4 qk{1, 0, 0, 1, 0};  // predicted state of row k
   bool unphys = false;
 
   // lambda^n of row g from its slope terms (the walls' ghosts last; row 0's
@@ -444,12 +431,12 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
     const D4 db = diff(wn, wc);
     const D4 xb = D4{from_right(wc.r) - wc.r, from_right(wc.u) - wc.u, from_right(wc.v) - wc.v, from_right(wc.p) - wc.p};
     const D4 xa = D4{from_left(xb.r), from_left(xb.u), from_left(xb.v), from_left(xb.p)};
-    int cx = 0, cy = 0;
-    const W4 sx = mc4_diff<true>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, cx);
-    W4 sy = mc4_diff<true>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, cy);
-    if constexpr (BAL) mc_p_balanced_diff<true>(P, wc, da.p, db.p, sy, cy);
-    int code = cx | (cy << 8);
-    asm volatile("" : "+v"(code));  // here, while the differences are at hand
+    int code, cases[8];
+    const W4 sx = mc4_diff<false>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, code, cases);
+    W4 sy = mc4_diff<false>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, code, cases + 4);
+    if constexpr (BAL) mc_p_balanced_diff<false>(P, wc, da.p, db.p, sy, code, cases + 4);
+#pragma unroll
+    for (int v = 0; v < 8; ++v) asm volatile("" : "+v"(cases[v]));  // here, while the differences are at hand
     const W4 q = predict(P, wc, sx, sy, hx, hy, hg);
     if (m >= ys && m < ye) {
       const double hr = 0.5 * fabs(sx.r), hp = 0.5 * fabs(sx.p), vr = 0.5 * fabs(sy.r), vp = 0.5 * fabs(sy.p);
@@ -500,8 +487,17 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
       W4 wb{0.0, 0.0, 0.0, 0.0, 0.0};
       predict_adj(P, wk, sxk, syk, hx, hy, qb, wb, sxb, syb);
       double pa[4], pb[4], ya[4], yf[4];
-      slope_products(sxb, codek & 0xff, pa, pb);
-      slope_products(syb, codek >> 8, ya, yf);
+      // (the weights are 0, 1/2 or 2: adding these exact products is what a
+      // fused multiply-add of weight and cotangent gives)
+      const double sxv[4] = {sxb.r, sxb.u, sxb.v, sxb.p}, syv[4] = {syb.r, syb.u, syb.v, syb.p};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int cx = sCase[wave][v][lane], cy = sCase[wave][4 + v][lane];
+        pa[v] = weighted_a(sxv[v], cx);
+        pb[v] = weighted_b(sxv[v], cx);
+        ya[v] = weighted_a(syv[v], cy);
+        yf[v] = weighted_b(syv[v], cy);
+      }
       double acc[4];
       if (k > ys) {
         // row g = k - 1 takes its last term, the backward part of row k
@@ -525,9 +521,8 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
         acc[v] = s;
       }
       if constexpr (BAL) {
-        double wa, wbb;
-        mc_weights((codek >> 14) & 3, wa, wbb);
-        acc[0] += P.g_y * P.dy * (1.0 - wa - wbb) * syb.p;
+        const int cp = sCase[wave][7][lane];
+        acc[0] += P.g_y * P.dy * (1.0 - weighted_a(1.0, cp) - weighted_b(1.0, cp)) * syb.p;
       }
       if (k > 0 && k > ys - 1) {
 #pragma unroll
@@ -558,7 +553,8 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
 #pragma unroll
     for (int v = 0; v < 4; ++v) kept(kLam + v) = lm.v[v];
     qk = q;
-    codek = code;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) sCase[wave][v][lane] = cases[v];
     wc = wn;
     da = db;
     un = u2;
@@ -598,7 +594,8 @@ int row_segments(int ny, int strips, int nb, const double (&c)[K], double over) 
 // wavefront per SIMD, 46.8 and 85.2 with two, 46.3 and 83.7 with three;
 // 512x1024 alone 17.7, 17.1, 16.9.
 constexpr double kStepRow[3] = {1.23, 2.10, 3.03}, kStepOver = 2.3;
-// 512x1024 x 4 and x 8: 122.5 and 234 us with one, 111.7 and 201.3 with two.
+// 512x1024 x 4 and x 8: 122.5 and 234 us with one, 111.7 and 201.3 with two
+// (at 1100 instructions per row; 106 and 194 with two now).
 constexpr double kAdjRow[2] = {3.05, 4.9}, kAdjOver = 3.3;
 
 }  // namespace

@@ -143,14 +143,29 @@ RT_DEV void mc_weights(int code, double& wa, double& wb) {
   wb = code == 1 ? 0.5 : (code == 3 ? 2.0 : 0.0);
 }
 
+// The case as the weights' binary exponents, those of d s/d a in the upper and
+// of d s/d b in the lower half: weight times x is ldexp(x, exponent), exact
+// (kNoWeight underflows any x to zero).
+constexpr int kNoWeight = -0x4000;
+constexpr int mc_pair(int ea, int eb) { return (int)(((unsigned)ea << 16) | ((unsigned)eb & 0xffffu)); }
+RT_DEV int mc_exponents(double a, double b, double m, bool small) {
+  const bool central = fabs(0.5 * (a + b)) <= 2.0 * m;
+  const bool left = fabs(a) <= fabs(b), zero = mc_zero(a, b, small);
+  const int side = left ? mc_pair(1, kNoWeight) : mc_pair(kNoWeight, 1);
+  const int pair = central ? mc_pair(-1, -1) : side;
+  return zero ? mc_pair(kNoWeight, kNoWeight) : pair;
+}
+RT_DEV double weighted_a(double x, int pair) { return ldexp(x, pair >> 16); }
+RT_DEV double weighted_b(double x, int pair) { return ldexp(x, (int)(int16_t)pair); }
+
 // Slopes of the four primitives (and, if CODES, their cases packed 2 bits
-// per variable), from the differences a to the cell below and b to the cell
-// above (mc4: from the three cells).  A difference is negligible below kTieTol times the centre
+// per variable; if pairs, as exponents), from the differences a to the cell
+// below and b to the cell above (mc4: from the three cells).  A difference is negligible below kTieTol times the centre
 // cell's density, pressure, or sound speed (velocities: d^2 <= kTieTol^2
 // gamma p / rho).
 template <bool CODES>
 RT_DEV W4 mc4_diff(const Params& P, const W4& c, double ar, double au, double av, double ap, double br, double bu,
-                   double bv, double bp, int& codes) {
+                   double bv, double bp, int& codes, int* pairs = nullptr) {
   const double tr = kTieTol * c.r, tp = kTieTol * c.p, tv2 = kTieTol * kTieTol * P.gamma * c.p * c.ri;
   W4 s;
   // the smaller difference is negligible if either is (squares round
@@ -166,6 +181,12 @@ RT_DEV W4 mc4_diff(const Params& P, const W4& c, double ar, double au, double av
   if (CODES)
     codes = mc_code(ar, br, mr, zr) | (mc_code(au, bu, mu, zu) << 2) | (mc_code(av, bv, mv, zv) << 4) |
             (mc_code(ap, bp, mp, zp) << 6);
+  if (pairs) {
+    pairs[0] = mc_exponents(ar, br, mr, zr);
+    pairs[1] = mc_exponents(au, bu, mu, zu);
+    pairs[2] = mc_exponents(av, bv, mv, zv);
+    pairs[3] = mc_exponents(ap, bp, mp, zp);
+  }
   return s;
 }
 template <bool CODES>
@@ -182,7 +203,8 @@ RT_DEV W4 mc4(const Params& P, const W4& m, const W4& c, const W4& p, int& codes
 // or differ in sign, so the two pressures at a face agree and the pressure
 // difference across the cell cancels the gravity source.
 template <bool CODES>
-RT_DEV void mc_p_balanced_diff(const Params& P, const W4& c, double pa, double pb, W4& s, int& codes) {
+RT_DEV void mc_p_balanced_diff(const Params& P, const W4& c, double pa, double pb, W4& s, int& codes,
+                               int* pairs = nullptr) {
   const double h = c.r * (P.g_y * P.dy);
   const double tp = kTieTol * c.p;
   const double a = pa - h, b = pb - h;
@@ -190,6 +212,7 @@ RT_DEV void mc_p_balanced_diff(const Params& P, const W4& c, double pa, double p
   const bool z = m <= tp;
   s.p = h + mc_value(a, b, m, z);
   if (CODES) codes = (codes & ~(3 << 6)) | (mc_code(a, b, m, z) << 6);
+  if (pairs) pairs[3] = mc_exponents(a, b, m, z);
 }
 template <bool CODES>
 RT_DEV void mc_p_balanced(const Params& P, const W4& m, const W4& c, const W4& p, W4& s, int& codes) {
@@ -219,15 +242,16 @@ RT_DEV W4 predict(const Params& P, const W4& w, const W4& sx, const W4& sy, doub
   return q;
 }
 
-// Adjoint of predict: q-bar -> (W-bar, sx-bar, sy-bar), accumulated.
+// Adjoint of predict: q-bar -> (W-bar, sx-bar, sy-bar), the slopes' added to
+// what they hold.
 RT_DEV void predict_adj(const Params& P, const W4& w, const W4& sx, const W4& sy, double hx, double hy,
                         const W4& qb, W4& wb, W4& sxb, W4& syb) {
   const double ri = w.ri;
   const double g = P.gamma;
-  wb.r += qb.r - hx * qb.r * sx.u - hy * qb.r * sy.v + (hx * qb.u * sx.p + hy * qb.v * sy.p) * ri * ri;
-  wb.u += qb.u - hx * (qb.r * sx.r + qb.u * sx.u + qb.v * sx.v + qb.p * sx.p);
-  wb.v += qb.v - hy * (qb.r * sy.r + qb.u * sy.u + qb.v * sy.v + qb.p * sy.p);
-  wb.p += qb.p - g * qb.p * (hx * sx.u + hy * sy.v);
+  wb.r = qb.r - hx * qb.r * sx.u - hy * qb.r * sy.v + (hx * qb.u * sx.p + hy * qb.v * sy.p) * ri * ri;
+  wb.u = qb.u - hx * (qb.r * sx.r + qb.u * sx.u + qb.v * sx.v + qb.p * sx.p);
+  wb.v = qb.v - hy * (qb.r * sy.r + qb.u * sy.u + qb.v * sy.v + qb.p * sy.p);
+  wb.p = qb.p - g * qb.p * (hx * sx.u + hy * sy.v);
   sxb.r += -hx * w.u * qb.r;
   sxb.u += -hx * (w.r * qb.r + w.u * qb.u + g * w.p * qb.p);
   sxb.v += -hx * w.u * qb.v;
@@ -309,7 +333,7 @@ RT_DEV void hllc(const Params& P, const FS& L, const FS& R, double F[4]) {
   F[3] = h.n * (h.E + h.p) + h.sig * (fH - h.E);
 }
 
-// Adjoint of hllc: given F-bar, accumulate L-bar and R-bar (reverse of the
+// Adjoint of hllc: given F-bar, L-bar and R-bar (reverse of the
 // computational graph of hllc_core + hllc).  F, if not null, also receives
 // the flux itself (as hllc gives it).
 RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[4], FS& Lb, FS& Rb,
@@ -364,14 +388,16 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   tb += Eb * h.r * h.t;
   // sigma = S when active
   Sb += sigb;
-  // scatter the side-K quantities to L or R (selects: lanes take both sides)
-  double rLb = h.left ? rb : 0.0, rRb = h.left ? 0.0 : rb;
-  double nLb = h.left ? nb : 0.0, nRb = h.left ? 0.0 : nb;
-  const double tLb = h.left ? tb : 0.0, tRb = h.left ? 0.0 : tb;
-  double pLb = h.left ? pb : 0.0, pRb = h.left ? 0.0 : pb;
-  double SLb = h.left ? Sb : 0.0, SRb = h.left ? 0.0 : Sb;
-  double mLb = h.left ? mb : 0.0, mRb = h.left ? 0.0 : mb;
-  double dLb = h.left ? db : 0.0, dRb = h.left ? 0.0 : db;
+  // scatter the side-K quantities to L or R, and the Davis speeds below, by
+  // products with 1 or 0 (exact, two instructions where two selects are four)
+  const double onL = h.left ? 1.0 : 0.0;
+  double rLb = rb * onL, rRb = rb - rLb;
+  double nLb = nb * onL, nRb = nb - nLb;
+  const double tLb = tb * onL, tRb = tb - tLb;
+  double pLb = pb * onL, pRb = pb - pLb;
+  double SLb = Sb * onL, SRb = Sb - SLb;
+  double mLb = mb * onL, mRb = mb - mLb;
+  double dLb = db * onL, dRb = db - dLb;
   // SS = num / dn, dn = mL - mR, num = pR - pL + mL nL - mR nR
   const double numb = SSb * h.rdn;
   const double dnb = -SSb * h.SS * h.rdn;
@@ -391,8 +417,8 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   SRb += dRb;
   nRb -= dRb;
   // Davis speeds
-  const double aLb = h.selL ? SLb : 0.0, bLb = h.selL ? 0.0 : SLb;
-  const double aRb = h.selR ? SRb : 0.0, bRb = h.selR ? 0.0 : SRb;
+  const double aLb = SLb * (h.selL ? 1.0 : 0.0), bLb = SLb - aLb;
+  const double aRb = SRb * (h.selR ? 1.0 : 0.0), bRb = SRb - aRb;
   nLb += aLb;
   nRb += bLb;
   nLb += aRb;
@@ -403,8 +429,8 @@ RT_DEV void hllc_adj(const Params& P, const FS& L, const FS& R, const double Fb[
   rLb -= cLb * 0.5 * h.cL * h.riL;
   pRb += cRb * 0.5 * g * h.rcR * h.riR;
   rRb -= cRb * 0.5 * h.cR * h.riR;
-  Lb.r += rLb; Lb.n += nLb; Lb.t += tLb; Lb.p += pLb;
-  Rb.r += rRb; Rb.n += nRb; Rb.t += tRb; Rb.p += pRb;
+  Lb = FS{rLb, nLb, tLb, pLb};
+  Rb = FS{rRb, nRb, tRb, pRb};
 }
 
 // Wall pressure: top wall (interior below the face, on the left of the
