@@ -163,7 +163,7 @@ def roofline(kind, kt_us, cells, traffic, counters):
         "traffic": None if traffic is None else round(traffic, 1),
         "algorithmic_flops_per_launch": flops,
         "kernel": ("fused forward step (k_step or k_step_cols with the CFL epilogue, march)" if kind == "step"
-                   else "adjoint step (k_adj_a + k_adj_b, or k_adj_cols)"),
+                   else "adjoint step (k_adj_a + k_adj_b, k_adj_cols or k_adj_fused)"),
         "launch_us": round(kt_us, 3),
         "hbm": {"achieved": round(gb, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gb / HBM_PEAK_GBS, 5),
                 "algorithmic_bytes_per_launch": nbytes},

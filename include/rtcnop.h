@@ -280,15 +280,19 @@ int rt_axpy(rt_ctx* ctx, const double* x, const double* alpha, const double* y, 
 int rt_set_tile(rt_ctx* ctx, int32_t tile);
 /* Select the step and adjoint variants separately. */
 int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
-/* Column kernels in place of the tile kernels, a mask of RT_COLUMNS_*: one
- * wavefront marches a strip of columns upward with its rows in registers,
- * without barriers; the adjoint takes one launch per step and leaves no
- * intermediates in memory.  Results are those of every tile variant to the
- * bit.  The adjoint of differentiated time steps and the folded sweep run
- * the tile kernels either way.  The default: both beyond three 32x8 blocks
- * per CU of cells in all; rt_set_tile and rt_set_tiles set the mask to 0, rt_autotune to what
- * it measures as faster. */
-enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2 };
+/* Kernels that run in place of the tile kernels, a mask: RT_COLUMNS_STEP and
+ * RT_COLUMNS_ADJOINT (one wavefront marches a strip of columns upward with
+ * its rows in registers, without barriers), RT_FUSED_ADJOINT (the two adjoint
+ * kernels in one, on tiles with a wider halo).  Both adjoints take one launch
+ * per step and leave no intermediates in memory; differentiated time steps
+ * run the fused one (or the tile kernels) also where RT_COLUMNS_ADJOINT is
+ * set.  Results are those of every tile variant to the bit (differentiated
+ * steps: to the rounding of mu's sum).  The default: RT_FUSED_ADJOINT, and
+ * beyond three 32x8 blocks per CU of cells in all RT_COLUMNS_STEP, and
+ * RT_COLUMNS_ADJOINT where it is expected to be faster.  rt_set_tile and
+ * rt_set_tiles set the mask to 0, rt_set_fold(ctx, 1) clears both adjoint
+ * bits, rt_autotune sets it to what it measures as fastest. */
+enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2, RT_FUSED_ADJOINT = 4 };
 int rt_set_columns(rt_ctx* ctx, int32_t mask);
 int rt_get_columns(const rt_ctx* ctx, int32_t* mask);
 /* The adaptive march replays captured HIP graphs of 48 steps (on = 1, the
@@ -312,10 +316,11 @@ int rt_autotune(rt_ctx* ctx, const double* U, int32_t reps, int32_t* step_tile, 
 /* The reverse sweep of RT_CKPT_STORE_ALL / RT_CKPT_UNIFORM runs one kernel
  * per adjoint step, which also completes the previous step's limiter gather
  * (on = 1), or the two kernels of rt_step_adjoint per step (on = 0); results
- * are identical.  rt_autotune folds when the folded step is more than 10%
- * faster than the two-kernel step on their own (the folded kernel shares
- * the CUs less well with the concurrent re-computation); before it, grids
- * of fewer than 2^16 cells in all fold (and use 8x8 single-pass tiles),
+ * are identical.  Folding needs the adjoint's tile kernels (see
+ * rt_set_columns).  rt_autotune folds when the folded step is more than 10%
+ * faster than any other on their own (the folded kernel shares the CUs less
+ * well with the concurrent re-computation); before it, grids of fewer than
+ * 2^16 cells in all are set to fold (and to 8x8 single-pass tiles),
  * larger ones run two adjoint kernels, with 32x16 step and 32x8 adjoint
  * tiles up to three 32x8 blocks per CU and 16x15 tiles for both beyond.  Binomial checkpointing,
  * differentiated time steps (rt_set_dt_mode) and the well-balanced variant

@@ -58,8 +58,13 @@ struct rt_ctx {
   int tile_adj;  // tile variant of the adjoint kernel
   int columns = 0;  // RT_COLUMNS_* kernels that run in place of the tile kernels (same results)
   int step_variant() const { return (columns & RT_COLUMNS_STEP) ? (int)rtk::TILE_COLUMNS : tile; }
-  // the adjoint step of frozen time steps outside the folded sweep
-  int adj_variant() const { return (columns & RT_COLUMNS_ADJOINT) ? (int)rtk::TILE_COLUMNS : tile_adj; }
+  // the adjoint step outside the folded sweep; dtd: with differentiated steps
+  int adj_variant(bool dtd) const {
+    if ((columns & RT_COLUMNS_ADJOINT) && !dtd) return rtk::TILE_COLUMNS;
+    return (columns & RT_FUSED_ADJOINT) ? (int)rtk::TILE_FUSED : tile_adj;
+  }
+  // the reverse sweep of uniform checkpoints folds the gather
+  bool folds() const { return fold && !(columns & (RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT)); }
   int red_blocks;
   // workspace
   char* ws = nullptr;
@@ -366,14 +371,17 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   // of 256 threads: every face loop is one pass of the block (255 and 256
   // faces of each direction; the step's single face list two), and four
   // small blocks per CU hide one another's barriers better than two large
-  // ones.  Beyond one round the column kernels run instead, which have no
-  // barriers, almost no halo work and, in the adjoint, no intermediates in
-  // memory: step at a given dt / march step / adjoint step in us, columns
-  // against tiles, 12 / 14 / 29 against 14 / 16.5 / 28.5 at 2 x 256x512,
-  // 18 / 20 / 41 against 22 / 25 / 46 at 512x1024, 87 / 95 / 201 against
-  // 155 / 172 / 398 at 8 x 512x1024; below it a launch lasts as long as one
-  // wavefront's chain of rows and the tiles win (7.7 / 9.1 / 18.6 against
-  // 8.4 / 10.2 / 28 at 256x512).
+  // ones.  Beyond one round the step runs the column kernel instead, which
+  // has no barriers and almost no halo work: given dt / march step in us,
+  // columns against tiles, 12 / 14 against 14 / 16.5 at 2 x 256x512, 18 / 20
+  // against 22 / 25 at 512x1024, 87 / 95 against 155 / 172 at 8 x 512x1024;
+  // below it a launch lasts as long as one wavefront's chain of rows and the
+  // tiles win (7.7 / 9.1 against 8.4 / 10.2 at 256x512).  The adjoint never
+  // runs the tile pair by default: in one launch it is faster at every size,
+  // fused on tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6 against
+  // 18.2, 512x512 22.0 against 28.0) or, where its expected time is less, by
+  // columns (512x768 32.0 against 32.7 fused, 512x1024 40 against 44, 8 x
+  // 512x1024 194 against 314 and the pair's 398).
   // rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
   const bool tiny = all_cells < ((size_t)1 << 16);
@@ -385,7 +393,8 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   c->tile = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x16 : rtk::TILE_16x15);
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
   c->fold = tiny;
-  c->columns = one_round ? 0 : RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT;
+  c->columns = RT_FUSED_ADJOINT | (one_round ? 0 : (int)RT_COLUMNS_STEP) |
+               (rtk::adj_cols_us(P) < rtk::adj_fused_us(P) ? (int)RT_COLUMNS_ADJOINT : 0);
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));
   *out = c;
@@ -414,7 +423,7 @@ int rt_set_tile(rt_ctx* c, int32_t tile) {
 
 int rt_set_columns(rt_ctx* c, int32_t mask) {
   if (!c) return fail(RT_EINVAL, "null context");
-  if (mask & ~(RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT)) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
+  if (mask & ~(RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT)) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
   c->columns = mask;
   return 0;
 }
@@ -456,6 +465,7 @@ int rt_set_overlap(rt_ctx* c, int32_t on) {
 int rt_set_fold(rt_ctx* c, int32_t on) {
   if (!c) return fail(RT_EINVAL, "null context");
   c->fold = on != 0;
+  if (on) c->columns &= ~(RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT);
   return 0;
 }
 
@@ -547,7 +557,7 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
     return e;
   };
   hipError_t e = rtk::launch_step(P, step_tile, a, s);
-  const int fold_tile = adj_tile == rtk::TILE_COLUMNS ? c->tile_adj : adj_tile;
+  const int fold_tile = adj_tile >= rtk::TILE_COUNT ? c->tile_adj : adj_tile;
   if (e == hipSuccess) e = rtk::launch_adjoint(P, fold_tile, j, s, false);  // fills Z, codes for the fold
   if (e == hipSuccess) e = timed([&](int) { return rtk::launch_step(P, step_tile, a, s); }, &out[0]);
   if (e == hipSuccess) e = rtk::launch_copy(U, c->S0, se, s);
@@ -604,7 +614,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   hipEvent_t e0, e1;
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
-  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f, cols_s = 1e30f, cols_a = 1e30f;
+  float best_s = 1e30f, best_f = 1e30f, best_u = 1e30f, cols_s = 1e30f, cols_a = 1e30f, fused_a = 1e30f;
   int bs = c->tile, bfold = c->tile_adj, bunf = c->tile_adj;
   int rc = 0;
   {
@@ -612,6 +622,8 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
     rc = time_kernels(c, U, rtk::TILE_COLUMNS, rtk::TILE_COLUMNS, reps, e0, e1, ms);
     cols_s = ms[0] + ms[1];
     cols_a = ms[3];
+    if (rc == 0) rc = time_kernels(c, U, c->tile, rtk::TILE_FUSED, reps, e0, e1, ms);
+    fused_a = ms[3];
   }
   for (int t = 0; t < rtk::TILE_COUNT && rc == 0; ++t) {
     float ms[4];
@@ -626,7 +638,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   // leaves less room on the CUs for the concurrent re-computation, which
   // costs it about 10% there relative to its time alone; so it is taken
   // only when it is more than 10% faster alone.
-  const bool fold = c->P.recon == RT_RECON_PRIMITIVE && best_f < 0.9f * std::min(best_u, cols_a);
+  const bool fold = c->P.recon == RT_RECON_PRIMITIVE && best_f < 0.9f * std::min({best_u, cols_a, fused_a});
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
@@ -635,7 +647,9 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   c->tile = bs;
   c->tile_adj = ba;
   c->fold = fold;
-  c->columns = (cols_s < best_s ? RT_COLUMNS_STEP : 0) | (cols_a < best_u ? RT_COLUMNS_ADJOINT : 0);
+  c->columns = cols_s < best_s ? RT_COLUMNS_STEP : 0;
+  if (!fold && fused_a < best_u) c->columns |= RT_FUSED_ADJOINT;
+  if (!fold && cols_a < std::min(best_u, fused_a)) c->columns |= RT_COLUMNS_ADJOINT;
   if (step_tile) *step_tile = bs;
   if (adj_tile) *adj_tile = ba;
   Flags f{};
@@ -655,12 +669,12 @@ int rt_kernel_times(rt_ctx* c, const double* U, int32_t reps, double* out) {
   RT_HIP(hipEventCreate(&e0));
   RT_HIP(hipEventCreate(&e1));
   float ms[4] = {0, 0, 0, 0};
-  const int rc = time_kernels(c, U, c->step_variant(), c->adj_variant(), reps, e0, e1, ms);
+  const int rc = time_kernels(c, U, c->step_variant(), c->adj_variant(false), reps, e0, e1, ms);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
   for (int k = 0; k < 4; ++k) out[k] = 1e3 * ms[k];
-  out[4] = (c->fold && c->dt_mode == RT_DT_FROZEN && c->P.recon == RT_RECON_PRIMITIVE) ? out[2] : out[3];
+  out[4] = (c->folds() && c->dt_mode == RT_DT_FROZEN && c->P.recon == RT_RECON_PRIMITIVE) ? out[2] : out[3];
   Flags f{};
   return read_flags(c, &f, true);
 }
@@ -859,7 +873,7 @@ int rt_step_adjoint(rt_ctx* c, const double* U, const double* dt, const double* 
   a.dt_stride = 1;
   a.dt_index = 0;
   a.flags = c->flags;
-  RT_HIP(rtk::launch_adjoint(c->P, c->adj_variant(), a, c->stream));
+  RT_HIP(rtk::launch_adjoint(c->P, c->adj_variant(false), a, c->stream));
   return 0;
 }
 
@@ -975,7 +989,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
   };
   const bool dtd = c->dt_mode == RT_DT_DIFFERENTIATED;
   // the folded sweep serves the frozen steps of the primitive variant
-  const bool use_fold = c->fold && !dtd && P.recon == RT_RECON_PRIMITIVE;
+  const bool use_fold = c->folds() && !dtd && P.recon == RT_RECON_PRIMITIVE;
   auto adjoint = [&](const double* Un, int n) -> int {
     rtk::AdjArgs a{};
     a.U = Un;
@@ -993,10 +1007,11 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dtd.smax = c->dtd_smax;
       a.dtd.imax = c->dtd_imax;
       a.dtd.stride = c->dtd_stride;
-      a.dtd.count = rtk::step_blocks(P, c->tile_adj);
+      a.dtd.count = c->adj_variant(true) == rtk::TILE_FUSED ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
+      a.dtd.batch = P.nb;
       a.dtd.mu_last = c->dtd_mu_last;
     }
-    RT_HIP(rtk::launch_adjoint(P, dtd ? c->tile_adj : c->adj_variant(), a, s));
+    RT_HIP(rtk::launch_adjoint(P, c->adj_variant(dtd), a, s));
     if (dtd) RT_HIP(rtk::launch_dt_correct(P, a, s));  // updates lambda^n (a.lam) in place
     std::swap(lam, lam_other);
     return 0;
@@ -1195,10 +1210,12 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
         a.dtd.smax = c->dtd_smax + G.b0 * (size_t)c->dtd_stride;
         a.dtd.imax = c->dtd_imax + G.b0 * (size_t)c->dtd_stride;
         a.dtd.stride = c->dtd_stride;
-        a.dtd.count = rtk::step_blocks(G.P, c->tile_adj);
+        a.dtd.count =
+            c->adj_variant(true) == rtk::TILE_FUSED ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
+        a.dtd.batch = P.nb;
         a.dtd.mu_last = c->dtd_mu_last + G.b0;
       }
-      RT_HIP(rtk::launch_adjoint(G.P, dtd ? c->tile_adj : c->adj_variant(), a, G.st));
+      RT_HIP(rtk::launch_adjoint(G.P, c->adj_variant(dtd), a, G.st));
       if (dtd) RT_HIP(rtk::launch_dt_correct(G.P, a, G.st));  // updates lambda^n (a.lam) in place
       std::swap(G.lam, G.lam_other);
       return 0;

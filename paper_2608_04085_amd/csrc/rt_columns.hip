@@ -577,7 +577,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
 // below and above it.
 constexpr int kSimds = 1024;
 template <int K>
-int row_segments(int ny, int strips, int nb, const double (&c)[K], double over) {
+int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, double* us = nullptr) {
   int best = 1;
   double cost = 1e300;
   for (int k = 1; k <= K; ++k) {
@@ -588,15 +588,16 @@ int row_segments(int ny, int strips, int nb, const double (&c)[K], double over) 
       best = segs;
     }
   }
+  if (us) *us = cost + 3.0;
   return best;
 }
 // 512x1024, x 4 and x 8 members, given dt: 51.2 and 95.9 us with one
 // wavefront per SIMD, 46.8 and 85.2 with two, 46.3 and 83.7 with three;
 // 512x1024 alone 17.7, 17.1, 16.9.
 constexpr double kStepRow[3] = {1.23, 2.10, 3.03}, kStepOver = 2.3;
-// 512x1024 x 4 and x 8: 122.5 and 234 us with one, 111.7 and 201.3 with two
-// (at 1100 instructions per row; 106 and 194 with two now).
-constexpr double kAdjRow[2] = {3.05, 4.9}, kAdjOver = 3.3;
+// 512x512, x768, x1024: 25.9, 32.0, 40.3 us with one; 512x1024 x 4 and x 8: 106
+// and 194 with two.
+constexpr double kAdjRow[2] = {2.9, 4.8}, kAdjOver = 3.0;
 
 }  // namespace
 
@@ -610,6 +611,12 @@ hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
   else
     hipLaunchKernelGGL((k_step_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
   return hipGetLastError();
+}
+
+double adj_cols_us(const Params& P) {
+  double us;
+  (void)row_segments(P.ny, (P.nx + kAdjOwn - 1) / kAdjOwn, P.nb, kAdjRow, kAdjOver, &us);
+  return us;
 }
 
 hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s) {

@@ -98,6 +98,7 @@ struct AdjArgs {
     int32_t* imax;    // [B][stride]
     int32_t stride;   // partials per member, >= the adjoint grid's tiles
     int32_t count;    // tiles of the adjoint grid per member
+    int32_t batch;    // members of the whole sweep: fixes the fused kernel's tile for launches over some of them
     double* mu_last;  // [B] mu of each member's last (clipped) step
   } dtd;
 };
@@ -122,7 +123,9 @@ enum TileId {
   TILE_16x15 = 10,
   TILE_15x16 = 11,
   TILE_COUNT = 12,
-  TILE_COLUMNS = 100  // not a tile: the column kernels (rt_columns.hip), same results
+  // not tile variants: other kernels with the same results
+  TILE_COLUMNS = 100,  // column kernels (rt_columns.hip)
+  TILE_FUSED = 101     // adjoint in one launch on tiles (rt_fused.hip)
 };
 void tile_dims(int tile, int* tx, int* ty, int* nt);
 int step_blocks(const Params& P, int tile);  // blocks per member
@@ -141,6 +144,15 @@ hipError_t launch_adjoint(const Params& P, int tile, const AdjArgs& a, hipStream
 // The two in one launch by the column kernel (launch_adjoint with
 // TILE_COLUMNS): frozen steps, no folded gather, Z and codes unused.
 hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s);
+// The two in one launch on tiles with a halo of three cells (launch_adjoint
+// with TILE_FUSED): no folded gather, Z and codes unused.
+hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s);
+// Blocks per member of its grid (AdjArgs::Dtd::count) in a sweep of nb members.
+int adj_fused_blocks(const Params& P, int nb);
+// Expected time of a launch in us, from measurements: what the choice between
+// the two is made by.
+double adj_fused_us(const Params& P);
+double adj_cols_us(const Params& P);
 // Kernel B alone: lambda^n from Z, codes, U^n and lambda^{n+1} of step n.
 hipError_t launch_adj_gather(const Params& P, const AdjArgs& a, hipStream_t s);
 // Differentiated step size, after both adjoint kernels of step n (a.U = U^n,

@@ -32,58 +32,6 @@ namespace rtk {
 
 namespace {
 
-template <int NT>
-__device__ double block_max(double v, double* red) {
-  v = wave_max(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) red[w] = v;
-  __syncthreads();
-  double m = red[0];
-#pragma unroll
-  for (int k = 1; k < NT / 64; ++k) m = fmax(m, red[k]);
-  return m;
-}
-
-template <int NT>
-__device__ double block_sum(double v, double* red) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) red[w] = v;
-  __syncthreads();
-  double s = red[0];
-#pragma unroll
-  for (int k = 1; k < NT / 64; ++k) s += red[k];
-  return s;
-}
-
-// Largest s over the block with the smallest i among equal s (a total
-// order, so the result does not depend on the order of combination).
-__device__ __forceinline__ void argmax_merge(double& s, int& i, double s2, int i2) {
-  if (s2 > s || (s2 == s && i2 < i)) {
-    s = s2;
-    i = i2;
-  }
-}
-
-template <int NT>
-__device__ void block_argmax(double& s, int& i, double* rs, int* ri) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) argmax_merge(s, i, __shfl_xor(s, o, 64), __shfl_xor(i, o, 64));
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) {
-    rs[w] = s;
-    ri[w] = i;
-  }
-  __syncthreads();
-  s = rs[0];
-  i = ri[0];
-#pragma unroll
-  for (int k = 1; k < NT / 64; ++k) argmax_merge(s, i, rs[k], ri[k]);
-}
-
 __device__ __forceinline__ double rho0_at(const Params& P, double y) {
   return 0.5 * (P.rho_h + P.rho_l) + 0.5 * (P.rho_h - P.rho_l) * tanh((y - P.y0) / P.h);
 }
@@ -93,14 +41,6 @@ __device__ __forceinline__ double p0_at(const Params& P, double y) {
   const double az = fabs(z);
   const double lc = az + log1p(exp(-2.0 * az)) - 0.69314718055994530942;
   return P.p_int + P.g_y * (0.5 * (P.rho_h + P.rho_l) * (y - P.y0) + 0.5 * (P.rho_h - P.rho_l) * P.h * lc);
-}
-
-// ----------------------------------------------------------------- tile of a workgroup
-__device__ __forceinline__ void tile_of_block(int& bx, int& by) {
-  const int nbx = (int)gridDim.x;
-  const int t = xcd_band((int)blockIdx.x + nbx * (int)blockIdx.y, nbx * (int)gridDim.y);
-  bx = t % nbx;
-  by = t / nbx;
 }
 
 // ----------------------------------------------------------------- LDS tile helpers
@@ -1573,6 +1513,7 @@ static hipError_t launch_adj_a(const Params& P, int tile, const AdjArgs& a, hipS
 }
 
 hipError_t launch_adjoint(const Params& P, int tile, const AdjArgs& a, hipStream_t s, bool gather) {
+  if (tile == TILE_FUSED) return gather ? launch_adj_fused(P, a, s) : hipErrorInvalidValue;
   if (tile == TILE_COLUMNS) return gather ? launch_adj_cols(P, a, s) : hipErrorInvalidValue;
   hipError_t e = launch_adj_a(P, tile, a, s);
   if (e != hipSuccess || !gather) return e;

@@ -83,6 +83,58 @@ __device__ __forceinline__ double wave_sum(double v) {
   return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
+template <int NT>
+__device__ double block_max(double v, double* red) {
+  v = wave_max(v);
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  __syncthreads();
+  if (l == 0) red[w] = v;
+  __syncthreads();
+  double m = red[0];
+#pragma unroll
+  for (int k = 1; k < NT / 64; ++k) m = fmax(m, red[k]);
+  return m;
+}
+
+template <int NT>
+__device__ double block_sum(double v, double* red) {
+  v = wave_sum(v);
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  __syncthreads();
+  if (l == 0) red[w] = v;
+  __syncthreads();
+  double s = red[0];
+#pragma unroll
+  for (int k = 1; k < NT / 64; ++k) s += red[k];
+  return s;
+}
+
+// Largest s over the block with the smallest i among equal s (a total
+// order, so the result does not depend on the order of combination).
+__device__ __forceinline__ void argmax_merge(double& s, int& i, double s2, int i2) {
+  if (s2 > s || (s2 == s && i2 < i)) {
+    s = s2;
+    i = i2;
+  }
+}
+
+template <int NT>
+__device__ void block_argmax(double& s, int& i, double* rs, int* ri) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) argmax_merge(s, i, __shfl_xor(s, o, 64), __shfl_xor(i, o, 64));
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  __syncthreads();
+  if (l == 0) {
+    rs[w] = s;
+    ri[w] = i;
+  }
+  __syncthreads();
+  s = rs[0];
+  i = ri[0];
+#pragma unroll
+  for (int k = 1; k < NT / 64; ++k) argmax_merge(s, i, rs[k], ri[k]);
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs of the chip (linear
 // id mod 8), and each XCD has its own L2.  With tiles in raster order,
 // horizontally adjacent tiles would sit on different XCDs and each L2 would
@@ -97,6 +149,13 @@ __device__ __forceinline__ int xcd_band(int L, int T) {
   const int tall = T - (per - 1) * kXcds;   // 1..8 XCDs with `per` items, the rest per - 1
   const int xcd = L % kXcds, local = L / kXcds;
   return xcd < tall ? xcd * per + local : tall * per + (xcd - tall) * (per - 1) + local;
+}
+
+__device__ __forceinline__ void tile_of_block(int& bx, int& by) {
+  const int nbx = (int)gridDim.x;
+  const int t = xcd_band((int)blockIdx.x + nbx * (int)blockIdx.y, nbx * (int)gridDim.y);
+  bx = t % nbx;
+  by = t / nbx;
 }
 
 }  // namespace rtk

@@ -40,12 +40,12 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_columns.hip", "csrc/rt_device.h", "csrc/rt_wave.h",
-                  "csrc/rt_kernels.h"]
+KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_columns.hip", "csrc/rt_fused.hip", "csrc/rt_device.h",
+                  "csrc/rt_wave.h", "csrc/rt_kernels.h"]
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
 COUNTERS_JSON = os.path.join(ROOT, "profiles", "counters.json")
 COPY_BYTES = 2 * 1024**3
-CATEGORIES = ["step_given", "step_march", "adj_a_folded", "adj_a", "adj_b", "adj_cols", "copy"]
+CATEGORIES = ["step_given", "step_march", "adj_a_folded", "adj_a", "adj_b", "adj_cols", "adj_fused", "copy"]
 
 
 def kernel_source_hash() -> str:
@@ -116,6 +116,8 @@ def _classify(rows):
             cat[d] = "adj_b"
         elif "k_adj_cols" in n:
             cat[d] = "adj_cols"
+        elif "k_adj_fused" in n:
+            cat[d] = "adj_fused"
         elif "copyBuffer" in n and d > last_lib:
             cat[d] = "copy"  # the calibration copies come after every library kernel
     return cat
@@ -185,7 +187,7 @@ def summarize(workload: str, trace: str, fetch: str, write: str, req: str | None
               f"KiB per dispatch: scale factors fetch {f_scale}, write {w_scale}.", ""]
     entry = {}
     for name, parts in (("step", ["step_given"]), ("step_march", ["step_march"]),
-                        ("adjoint", ["adj_cols"] if "adj_cols" in avg else ["adj_a", "adj_b"]),
+                        ("adjoint", next(([k] for k in ("adj_cols", "adj_fused") if k in avg), ["adj_a", "adj_b"])),
                         ("adjoint_folded", ["adj_a_folded"])):
         if all(p in avg for p in parts):
             fb = sum(avg[p].get("FETCH_SIZE", 0.0) for p in parts) * 1024 * (f_scale or 1.0)
@@ -214,13 +216,13 @@ def summarize(workload: str, trace: str, fetch: str, write: str, req: str | None
 def key_for(workload: str, kernels: str) -> str:
     """Where the counters of `workload` stand for the kernels that run
     ("step/adjoint", Context.kernels): the tile kernels' under the workload's
-    own name, the column kernels' beside them."""
-    return workload + "_columns" if "columns" in kernels else workload
+    own name, the others' beside them."""
+    return workload + next((f"_{k}" for k in ("columns", "fused") if k in kernels), "")
 
 
 def adjoint_parts(kernels: str) -> list:
     """Kernel classes of one adjoint step for "step/adjoint" kernels."""
-    return ["adj_cols"] if kernels.endswith("/columns") else ["adj_a", "adj_b"]
+    return {"columns": ["adj_cols"], "fused": ["adj_fused"]}.get(kernels.split("/")[1], ["adj_a", "adj_b"])
 
 
 def traffic_for(workload: str, kernel: str, tiles: str | None = None) -> float | None:

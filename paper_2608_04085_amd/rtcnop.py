@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "librtcnop.so")
 STATUS = {0: "RT_OK", -1: "RT_EINVAL", -2: "RT_EHIP", -3: "RT_ENOMEM", -4: "RT_EUNPHYS", -5: "RT_ESTATE"}
 TILES = {"16x16": 0, "32x8": 1, "64x4": 2, "16x16w": 3, "32x8w": 4, "16x8": 5, "8x8": 6, "16x8w": 7, "8x8w": 8, "32x16": 9,
          "16x15": 10, "15x16": 11}
-COLUMNS_STEP, COLUMNS_ADJOINT = 1, 2
+COLUMNS_STEP, COLUMNS_ADJOINT, FUSED_ADJOINT = 1, 2, 4
 DT_MODES = {"frozen": 0, "differentiated": 1}
 DT_MODES_BY_ID = {v: k for k, v in DT_MODES.items()}
 
@@ -256,7 +256,7 @@ class Context:
 
     @property
     def columns(self) -> int:
-        """Column kernels in use in place of the tile kernels (a mask of COLUMNS_*)."""
+        """Kernels in use in place of the tile kernels (a mask of COLUMNS_STEP, COLUMNS_ADJOINT, FUSED_ADJOINT)."""
         m = ctypes.c_int32()
         _check(load().rt_get_columns(self._h, ctypes.byref(m)), "rt_get_columns")
         return m.value
@@ -266,10 +266,10 @@ class Context:
 
     @property
     def kernels(self) -> str:
-        """What runs, "step/adjoint": a tile variant or "columns"."""
+        """What runs, "step/adjoint" (frozen steps): a tile variant, "columns" or "fused"."""
         step, adj = self.tile.split("/")
         m = self.columns
-        return f"{'columns' if m & COLUMNS_STEP else step}/{'columns' if m & COLUMNS_ADJOINT else adj}"
+        return f"{'columns' if m & COLUMNS_STEP else step}/{'columns' if m & COLUMNS_ADJOINT else 'fused' if m & FUSED_ADJOINT else adj}"
 
     def set_graphs(self, on: bool):
         _check(load().rt_set_graphs(self._h, 1 if on else 0), "rt_set_graphs")

@@ -1,6 +1,6 @@
-"""GPU: the column kernels against the tile kernels (the same bits: both
-evaluate the same expressions) and against the oracle, at the edges of their
-strips, of their row segments and of the grid."""
+"""GPU: the column kernels and the fused adjoint against the tile kernels (the
+same bits: all evaluate the same expressions) and against the oracle, at the
+edges of their strips, row segments and tiles and of the grid."""
 import numpy as np
 import pytest
 import torch
@@ -70,8 +70,13 @@ def test_step_by_columns_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg):
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=IDS)
-def test_adjoint_by_columns_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg):
+@pytest.mark.parametrize("kernel", ["columns", "fused"])
+def test_one_launch_adjoint_has_the_bits_of_the_tiles_and_matches_the_oracle(cfg, kernel):
+    from paper_2608_04085_amd import rtcnop
     cols, tiles = contexts(cfg)
+    if kernel == "fused":
+        cols.set_columns(rtcnop.FUSED_ADJOINT)
+    assert cols.kernels.endswith(kernel)
     U = tiles.init_state(states(cfg))
     for _ in range(2):
         U = tiles.step(U)
@@ -123,3 +128,60 @@ def test_unphysical_state_is_reported_by_the_column_kernels():
                 cols.check_error()
             assert e.value.code == -4
             cols.check_error()  # the flag is cleared
+
+
+# a grid, ragged in both directions, for each tile shape of the fused adjoint
+# beyond the smallest (which the cases above run on): 16x8, 16x16, 24x16 and
+# 32x16 tiles in one round of blocks, and 32x16 in two
+FUSED = [(126, 255, 1, 0), (250, 255, 1, 1), (310, 250, 1, 0), (255, 510, 1, 1), (255, 510, 2, 0)]
+
+
+@pytest.mark.parametrize("nx,ny,batch,recon", FUSED)
+def test_fused_adjoint_shapes_have_the_bits_of_the_tiles(nx, ny, batch, recon):
+    from paper_2608_04085_amd import rtcnop
+    cfg = RTConfig(nx=nx, ny=ny, batch=batch, recon=recon)
+    tiles = rtcnop.Context(cfg, max_steps=64, tile="16x15")
+    fused = rtcnop.Context(cfg, max_steps=64)
+    fused.set_columns(rtcnop.FUSED_ADJOINT)
+    U = tiles.step(tiles.init_state(states(cfg)))
+    dt = tiles.cfl_dt(U)
+    lam = torch.from_numpy(np.random.default_rng(8).standard_normal(U.shape)).cuda()
+    np.testing.assert_array_equal(host(fused.step_adjoint(U, dt, lam)), host(tiles.step_adjoint(U, dt, lam)))
+    fused.check_error()
+
+
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[4], CASES[7], RTConfig(nx=126, ny=255)],
+                         ids=[IDS[0], IDS[4], IDS[7], "126x255"])
+def test_differentiated_steps_by_the_fused_adjoint_match_the_tiles(cfg):
+    # the sum behind the step sizes' derivative is grouped by tile: equal to
+    # its rounding, about 1e-16 times the square root of its 1e2 to 1e5 terms,
+    # which 20 steps and the correction's cancellation leave far below 1e-11
+    from paper_2608_04085_amd import rtcnop
+    uv = states(cfg) * np.linspace(0.1, 1.0, cfg.batch)[:, None, None, None]
+    out = []
+    for mask in (0, rtcnop.FUSED_ADJOINT):
+        r = rtcnop.Context(cfg, max_steps=256, tile="16x15")
+        r.set_columns(mask)
+        r.set_dt_mode("differentiated")
+        T = 12.4 * float(host(r.cfl_dt(r.init_state(uv))).min())
+        out.append([host(x) for x in r.grad_u0(uv, T, rtcnop.Policy(CKPT_UNIFORM, 4))])
+    np.testing.assert_array_equal(out[1][0], out[0][0])
+    np.testing.assert_array_equal(out[1][2], out[0][2])
+    assert np.max(np.abs(out[1][1] - out[0][1])) <= 1e-11 * np.max(np.abs(out[0][1]))
+
+
+def test_default_kernels_by_grid_size():
+    from paper_2608_04085_amd import rtcnop
+    for cfg, want in ((RTConfig(nx=64, ny=128), "8x8w/fused"), (RTConfig(nx=256, ny=512), "32x16/fused"),
+                      (RTConfig(nx=512, ny=512), "columns/fused"),
+                      (RTConfig(nx=512, ny=1024, batch=8), "columns/columns")):
+        r = rtcnop.Context(cfg, max_steps=8)
+        assert r.kernels == want, (cfg, r.kernels)
+        r.set_tiles("16x16", "32x8")
+        assert r.kernels == "16x16/32x8" and r.columns == 0
+        r.set_columns(rtcnop.COLUMNS_ADJOINT | rtcnop.FUSED_ADJOINT)
+        assert r.kernels == "16x16/columns"
+        r.set_fold(True)
+        assert r.kernels == "16x16/32x8" and r.fold
+    with pytest.raises(rtcnop.RTError):
+        r.set_columns(8)
