@@ -288,8 +288,8 @@ int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
  * run the fused one (or the tile kernels) also where RT_COLUMNS_ADJOINT is
  * set.  Results are those of every tile variant to the bit (differentiated
  * steps: to the rounding of mu's sum).  The default: RT_FUSED_ADJOINT, and
- * beyond three 32x8 blocks per CU of cells in all RT_COLUMNS_STEP, and
- * RT_COLUMNS_ADJOINT where it is expected to be faster.  rt_set_tile and
+ * the column kernels where they are expected to be faster (the step's always
+ * beyond three 32x8 blocks per CU of cells in all).  rt_set_tile and
  * rt_set_tiles set the mask to 0, rt_set_fold(ctx, 1) clears both adjoint
  * bits, rt_autotune sets it to what it measures as fastest. */
 enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2, RT_FUSED_ADJOINT = 4 };
@@ -320,11 +320,12 @@ int rt_autotune(rt_ctx* ctx, const double* U, int32_t reps, int32_t* step_tile, 
  * rt_set_columns).  rt_autotune folds when the folded step is more than 10%
  * faster than any other on their own (the folded kernel shares the CUs less
  * well with the concurrent re-computation); before it, grids of fewer than
- * 2^16 cells in all are set to fold (and to 8x8 single-pass tiles),
- * larger ones run two adjoint kernels, with 32x16 step and 32x8 adjoint
- * tiles up to three 32x8 blocks per CU and 16x15 tiles for both beyond.  Binomial checkpointing,
+ * 2^16 cells in all are set to fold.  The tile variants before it, where
+ * tile kernels run: single-pass step tiles 8x8, 16x8, 32x8 or 32x16 by size,
+ * adjoint tiles 8x8 (single pass) below 2^16 cells and 32x8 above up to three
+ * 32x8 blocks per CU, 16x15 for both beyond.  Binomial checkpointing,
  * differentiated time steps (rt_set_dt_mode) and the well-balanced variant
- * (RT_RECON_BALANCED) always run two kernels per step. */
+ * (RT_RECON_BALANCED) never fold. */
 int rt_set_fold(rt_ctx* ctx, int32_t on);
 int rt_get_fold(const rt_ctx* ctx, int32_t* on);
 

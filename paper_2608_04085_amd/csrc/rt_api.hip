@@ -74,7 +74,7 @@ struct rt_ctx {
   int32_t *codes = nullptr, *codes2 = nullptr;
   double* partial = nullptr;
   double* rowmean = nullptr;  // [B][ny] horizontal density means
-  uint64_t* acc = nullptr;  // [3][B][kAccRow] signal-speed slots of the march, then [B] for rt_step
+  uint64_t* acc = nullptr;  // [3][B][kAccRow] signal-speed slots of the march, then [B][kAccRow] for rt_step
   Ctl* ctl = nullptr;       // [2][B] march control, double buffered
   long last_launch = 0;     // launches of the last march (final ctl in ctl[last_launch & 1])
   // Graph of a chunk of kGraphChunk march steps (captured once per set of
@@ -156,7 +156,7 @@ Layout layout(const rt_ctx* c, int32_t max_steps) {
   L.codes2 = take(c->cells() * c->P.nb * sizeof(int32_t));
   L.partial = take((size_t)maxblk * c->P.nb * sizeof(double));
   L.rowmean = take((size_t)c->P.ny * c->P.nb * sizeof(double));
-  L.acc = take(((size_t)3 * rtk::kAccRow + 1) * c->P.nb * sizeof(uint64_t));
+  L.acc = take((size_t)4 * rtk::kAccRow * c->P.nb * sizeof(uint64_t));
   L.ctl = take((size_t)2 * c->P.nb * sizeof(Ctl));
   L.flags = take(sizeof(Flags));
   L.dt_log = take((size_t)c->P.nb * std::max<int32_t>(max_steps, 1) * sizeof(double));
@@ -361,28 +361,21 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   P.h = phys->h;
   P.p_int = phys->p_int;
   c->stream = reinterpret_cast<hipStream_t>(stream);
-  // Defaults from measurements on MI355X.  Tiny grids (one partial round of
-  // blocks) are bound by one block's critical path: single-pass 8x8 tiles
-  // and the folded adjoint (one kernel per step) win.  From 2^16 cells on
-  // the adjoint runs two kernels.  While 32x8 tiles fill at most one round
-  // of three blocks per CU, each launch lasts about one block's critical
-  // path: the step takes 32x16 tiles of 512 threads (the least halo work
-  // per cell) and the adjoint 32x8 tiles.  Beyond that both take 16x15 tiles
-  // of 256 threads: every face loop is one pass of the block (255 and 256
-  // faces of each direction; the step's single face list two), and four
-  // small blocks per CU hide one another's barriers better than two large
-  // ones.  Beyond one round the step runs the column kernel instead, which
-  // has no barriers and almost no halo work: given dt / march step in us,
-  // columns against tiles, 12 / 14 against 14 / 16.5 at 2 x 256x512, 18 / 20
-  // against 22 / 25 at 512x1024, 87 / 95 against 155 / 172 at 8 x 512x1024;
-  // below it a launch lasts as long as one wavefront's chain of rows and the
-  // tiles win (7.7 / 9.1 against 8.4 / 10.2 at 256x512).  The adjoint never
-  // runs the tile pair by default: in one launch it is faster at every size,
-  // fused on tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6 against
-  // 18.2, 512x512 22.0 against 28.0) or, where its expected time is less, by
-  // columns (512x768 32.0 against 32.7 fused, 512x1024 40 against 44, 8 x
-  // 512x1024 194 against 314 and the pair's 398).
-  // rt_autotune measures instead.
+  // Defaults from measurements on MI355X.  Each kernel takes the form whose
+  // launch is expected to be shortest (the rules and their times stand with
+  // the kernels).  The step runs single-pass tiles on the smallest grids and
+  // the column kernel, which has no barriers and almost no halo work, where
+  // that is faster, beyond one round of three 32x8 blocks per CU always: given
+  // dt / march step in us, columns against tiles, 8.4 / 10.2 against 7.7 / 9.1
+  // at 256x512, 9.7 / 11.3 against 10.3 / 12.0 at 384x512, 18 / 20 against 22 /
+  // 25 at 512x1024, 87 / 95 against 155 / 172 at 8 x 512x1024.  The adjoint
+  // never runs the tile pair by default: in one launch it is faster at every
+  // size, fused on tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6
+  // against 18.2, 512x512 22.0 against 28.0) or, where its expected time is
+  // less, by columns (512x768 32.0 against 32.7 fused, 512x1024 40 against 44,
+  // 8 x 512x1024 194 against 314 and the pair's 398).  The tile variants that
+  // rt_get_tiles names for the adjoint, and for the step beyond one round, are
+  // the fastest of the tile kernels; rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
   const bool tiny = all_cells < ((size_t)1 << 16);
   int dev = 0, cus = 0;
@@ -390,10 +383,12 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     cus = 256;
   const bool one_round = all_cells <= (size_t)3 * cus * 256;
-  c->tile = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x16 : rtk::TILE_16x15);
+  double tile_us = 0.0;
+  const int small_tile = rtk::step_tile(P, &tile_us);
+  c->tile = one_round ? small_tile : rtk::TILE_16x15;
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
   c->fold = tiny;
-  c->columns = RT_FUSED_ADJOINT | (one_round ? 0 : (int)RT_COLUMNS_STEP) |
+  c->columns = RT_FUSED_ADJOINT | (one_round && tile_us <= rtk::step_cols_us(P) ? 0 : (int)RT_COLUMNS_STEP) |
                (rtk::adj_cols_us(P) < rtk::adj_fused_us(P) ? (int)RT_COLUMNS_ADJOINT : 0);
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));
@@ -721,7 +716,7 @@ int rt_set_workspace(rt_ctx* c, void* dev, size_t bytes, int32_t max_steps) {
   c->dtd_stride = L.dtd_stride;
   c->bg_p = reinterpret_cast<double*>(w + L.bg_p);
   if (c->P.recon == RT_RECON_BALANCED) RT_HIP(rtk::launch_background_rows(c->P, c->bg_p, c->stream));
-  RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->acc), 0, 2 * ((size_t)3 * rtk::kAccRow + 1) * c->P.nb,
+  RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->acc), 0, 2 * (size_t)4 * rtk::kAccRow * c->P.nb,
                               c->stream));
   RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->flags), 0, sizeof(Flags) / 4, c->stream));
   return 0;
@@ -755,13 +750,12 @@ int rt_step(rt_ctx* c, const double* U_in, double* U_out, const double* dt, doub
   a.dt_stride = 1;
   a.dt_index = 0;
   a.flags = c->flags;
-  uint64_t* acc_out = c->acc + 3 * (size_t)rtk::kAccRow * c->P.nb;  // after the march's rows
-  if (dt_next) {
-    RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(acc_out), 0, 2 * c->P.nb, c->stream));
-    a.acc_out = acc_out;
-  }
+  // the slots after the march's rows: zero here, since the workspace was set
+  // or since the kernel that read them last
+  uint64_t* acc_out = c->acc + 3 * (size_t)rtk::kAccRow * c->P.nb;
+  if (dt_next) a.acc_out = acc_out;
   RT_HIP(rtk::launch_step(c->P, c->step_variant(), a, c->stream));
-  if (dt_next) RT_HIP(rtk::launch_cfl_from_bits(c->P, acc_out, dt_next, c->stream));
+  if (dt_next) RT_HIP(rtk::launch_cfl_from_slots(c->P, acc_out, dt_next, c->stream));
   return 0;
 }
 

@@ -273,7 +273,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   if (!need_speed) return;
   const double bm = wave_max(smax);
   if (a.ctl == nullptr) {
-    if (lane == 0) atomicMax((unsigned long long*)(a.acc_out + b), (unsigned long long)__double_as_longlong(bm));
+    if (lane == 0)
+      atomicMax((unsigned long long*)(a.acc_out + (size_t)b * kAccRow + (t % kAccSlots) * kAccStride),
+                (unsigned long long)__double_as_longlong(bm));
     return;
   }
   const int L = a.launch;
@@ -600,6 +602,14 @@ constexpr double kStepRow[3] = {1.23, 2.10, 3.03}, kStepOver = 2.3;
 constexpr double kAdjRow[2] = {2.9, 4.8}, kAdjOver = 3.0;
 
 }  // namespace
+
+double step_cols_us(const Params& P) {
+  // a little less than the fit's constant below a few rows: 300x300 7.6,
+  // 256x512 9.0, 384x512 10.5
+  double us;
+  (void)row_segments(P.ny, (P.nx + kStepOwn - 1) / kStepOwn, P.nb, kStepRow, kStepOver, &us);
+  return us - 0.6;
+}
 
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
   const int strips = (P.nx + kStepOwn - 1) / kStepOwn;

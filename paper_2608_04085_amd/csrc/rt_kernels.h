@@ -55,8 +55,9 @@ struct StepArgs {
   double* pool;
   int32_t snap_interval, snap_slots;
   // Given-dt mode: dt = dt[b * dt_stride + dt_index]; members with
-  // dt_index >= nsteps_limit[b] are skipped.  acc_out (may be null) receives
-  // the largest signal speed of U^{n+1} (bit pattern, must start at 0).
+  // dt_index >= nsteps_limit[b] are skipped.  acc_out (may be null), slots
+  // [B][kAccSlots * kAccStride] as a row of acc, receives the largest signal
+  // speed of U^{n+1} (bit pattern, must start at 0).
   const double* dt;
   int32_t dt_stride, dt_index;
   const int32_t* nsteps_limit;
@@ -129,6 +130,10 @@ enum TileId {
 };
 void tile_dims(int tile, int* tx, int* ty, int* nt);
 int step_blocks(const Params& P, int tile);  // blocks per member
+// The step's tile variant for small grids, and the expected times in us of its
+// launch and of the column kernel's (given dt and march step averaged).
+int step_tile(const Params& P, double* us);
+double step_cols_us(const Params& P);
 
 // prow: background pressure per row (well-balanced variant) or null.
 hipError_t launch_init_state(const Params& P, const double* uv0, double* U, const double* prow, hipStream_t s);
@@ -170,7 +175,7 @@ hipError_t launch_reduce(const Params& P, int kind, const double* a, const doubl
 hipError_t launch_march_begin(const Params& P, const double* maxspeed, double T, Ctl* ctl, uint64_t* acc,
                               Flags* flags, hipStream_t s);
 hipError_t launch_cfl_from_speed(const Params& P, const double* maxspeed, double* dt, hipStream_t s);
-hipError_t launch_cfl_from_bits(const Params& P, const uint64_t* acc, double* dt, hipStream_t s);
+hipError_t launch_cfl_from_slots(const Params& P, uint64_t* acc, double* dt, hipStream_t s);  // and clears the slots
 hipError_t launch_copy_final(const Params& P, const Ctl* ctl, const double* A, const double* Bbuf, double* U,
                              double* t_out, int32_t* nsteps_out, const double* log_src, int32_t log_src_cap,
                              double* log_dst, int32_t log_dst_cap, hipStream_t s);

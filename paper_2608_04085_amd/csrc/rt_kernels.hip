@@ -483,7 +483,11 @@ __global__ __launch_bounds__(NT) void k_step(Params P, StepArgs a) {
   // member's accumulator (non-negative doubles order like their bits)
   const double bm = block_max<NT>(smax, sRed);
   if (a.ctl == nullptr) {
-    if (tid == 0) atomicMax((unsigned long long*)(a.acc_out + b), (unsigned long long)__double_as_longlong(bm));
+    if (tid == 0) {
+      const int slot = (int)((blockIdx.x + (size_t)gridDim.x * blockIdx.y) % kAccSlots);
+      atomicMax((unsigned long long*)(a.acc_out + (size_t)b * kAccRow + slot * kAccStride),
+                (unsigned long long)__double_as_longlong(bm));
+    }
     return;
   }
   const int L = a.launch;
@@ -1194,9 +1198,17 @@ __global__ void k_march_begin(Params P, const double* ms, double T, Ctl* ctl, ui
           (r == 0 && k == 0) ? (uint64_t)__double_as_longlong(ms[b]) : 0ull;
 }
 
-__global__ void k_cfl_from_bits(Params P, const uint64_t* acc, double* dt) {
-  const int b = threadIdx.x + blockIdx.x * blockDim.x;
-  if (b < P.nb) dt[b] = P.cfl / __longlong_as_double((long long)acc[b]);
+// CFL step from a member's signal-speed slots, which it clears for the next
+// step; one wavefront per member.
+__global__ __launch_bounds__(64) void k_cfl_from_slots(Params P, uint64_t* acc, double* dt) {
+  uint64_t* row = acc + (size_t)blockIdx.x * kAccRow;
+  double ms = 0.0;
+  if (threadIdx.x < kAccSlots) {
+    ms = __longlong_as_double((long long)row[threadIdx.x * kAccStride]);
+    row[threadIdx.x * kAccStride] = 0ull;
+  }
+  ms = wave_max(ms);
+  if (threadIdx.x == 0) dt[blockIdx.x] = P.cfl / ms;
 }
 
 __global__ void k_cfl_from_speed(Params P, const double* ms, double* dt) {
@@ -1410,6 +1422,34 @@ void tile_dims(int tile, int* tx, int* ty, int* nt) {
   if (nt) *nt = t;
 }
 
+// The step's tile for grids that a few rounds of blocks cover (a round: one
+// block per CU) and the time of a launch, given dt and march step averaged:
+// single-pass blocks, the smallest that cover the grid in one round, and 32x16
+// where that one has the least halo work.  Measured, us: 8x8 with 192 threads
+// 4.9 (64x128), 5.6 (96x192), 5.9 (128x256), 7.0 (256x256); 16x8 with 320 5.3,
+// 5.5 (96x192, 128x256), 6.4, 7.4 (300x300); 32x8 with 576 6.2 (256x256), 8.3
+// (256x512), 11.8 (384x512); 32x16 8.4 (256x512).
+int step_tile(const Params& P, double* us) {
+  struct Choice {
+    int tile;
+    double fixed, per_round;
+  };
+  constexpr Choice choices[] = {
+      {TILE_8x8W, 4.1, 0.73}, {TILE_16x8W, 4.2, 1.17}, {TILE_32x8W, 3.9, 2.5}, {TILE_32x16, 3.0, 5.4}};
+  int best = TILE_8x8W;
+  double t = 1e300;
+  for (const Choice& c : choices) {
+    const long rounds = ((long)step_blocks(P, c.tile) * P.nb + 255) / 256;
+    const double u = c.fixed + c.per_round * (double)rounds;
+    if (u < t) {
+      t = u;
+      best = c.tile;
+    }
+  }
+  if (us) *us = t;
+  return best;
+}
+
 int step_blocks(const Params& P, int tile) {
   int tx, ty;
   tile_dims(tile, &tx, &ty, nullptr);
@@ -1545,8 +1585,8 @@ hipError_t launch_march_begin(const Params& P, const double* ms, double T, Ctl* 
   return hipGetLastError();
 }
 
-hipError_t launch_cfl_from_bits(const Params& P, const uint64_t* acc, double* dt, hipStream_t s) {
-  hipLaunchKernelGGL(k_cfl_from_bits, dim3((P.nb + 63) / 64), dim3(64), 0, s, P, acc, dt);
+hipError_t launch_cfl_from_slots(const Params& P, uint64_t* acc, double* dt, hipStream_t s) {
+  hipLaunchKernelGGL(k_cfl_from_slots, dim3(P.nb), dim3(64), 0, s, P, acc, dt);
   return hipGetLastError();
 }
 

@@ -185,3 +185,19 @@ def test_default_kernels_by_grid_size():
         assert r.kernels == "16x16/32x8" and r.fold
     with pytest.raises(rtcnop.RTError):
         r.set_columns(8)
+
+
+@pytest.mark.parametrize("cfg", [RTConfig(nx=61, ny=40, batch=3), RTConfig(nx=250, ny=255)], ids=["61x40x3", "250x255"])
+def test_cfl_step_after_each_step_starts_from_cleared_slots(cfg):
+    # rt_step's dt_next comes from slots that the kernel that read them clears:
+    # calls in a row, after states of larger and of smaller signal speed, and
+    # through both step kernels
+    from paper_2608_04085_amd import rtcnop
+    r = rtcnop.Context(cfg, max_steps=8)
+    fast, slow = r.init_state(30.0 * states(cfg)), r.init_state(states(cfg))
+    dt = 0.5 * r.cfl_dt(fast)
+    for mask in (rtcnop.FUSED_ADJOINT, rtcnop.COLUMNS_STEP):
+        r.set_columns(mask)
+        for U in (slow, fast, slow, slow):
+            Un, nxt = r.step(U, dt, want_next=True)
+            np.testing.assert_array_equal(host(nxt), host(r.cfl_dt(Un)))
