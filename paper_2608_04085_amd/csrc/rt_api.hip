@@ -117,7 +117,12 @@ struct rt_ctx {
       if (group_stream[k]) (void)hipStreamDestroy(group_stream[k]);
     }
     if (aux_stream) (void)hipStreamDestroy(aux_stream);
+    if (report) (void)hipHostFree(report);
   }
+  // Pinned host memory that kernels report into (allocated with the first
+  // workspace), so that a march's host decisions cost one stream
+  // synchronisation and no copies.
+  rtk::Report* report = nullptr;
   Flags* flags = nullptr;
   double* dt_log = nullptr;
   int32_t* nsteps = nullptr;
@@ -269,38 +274,48 @@ int ensure_chunk_graph(rt_ctx* c, double* pool, int interval, int slots) {
   return 0;
 }
 
-// Adaptive march of all members from S0 to T, one launch per step for the
-// whole batch (captured in graphs of kGraphChunk steps).  Members that are
-// done skip their blocks; the host checks the number of active members once
-// per round of launches.  On return (stream synced) final_ctl(c) holds the
-// per-member step counts; the final state of member b is in S0 if its step
-// count is even, else in S1.  Snapshots of U^n go to `pool` every `interval`
-// steps when pool is not null.
-int march(rt_ctx* c, double T, double* pool, int interval, int slots) {
+// Sets up the march of all members from S0 to T and gives the number of
+// steps the largest initial signal speed suggests.  Synchronises.
+int march_start(rt_ctx* c, double T, long* nest) {
   Params& P = c->P;
   RT_HIP(rtk::launch_reduce(P, 0, c->S0, nullptr, c->partial, c->red_blocks, c->sc(0), c->stream));
-  RT_HIP(rtk::launch_march_begin(P, c->sc(0), T, c->ctl, c->acc, c->flags, c->stream));
-  std::vector<double> ms(P.nb);
-  RT_HIP(hipMemcpyAsync(ms.data(), c->sc(0), sizeof(double) * P.nb, hipMemcpyDeviceToHost, c->stream));
+  RT_HIP(rtk::launch_march_begin(P, c->sc(0), T, c->ctl, c->acc, c->flags, c->report, c->stream));
   RT_HIP(hipStreamSynchronize(c->stream));
   double msmax = 0.0;
-  for (double m : ms) msmax = std::max(msmax, m);
+  for (int b = 0; b < P.nb; ++b) msmax = std::max(msmax, c->report->member[b].speed);
   const double dtmin = P.cfl / msmax;
   if (!(dtmin > 0.0) || !std::isfinite(dtmin)) return fail(RT_EUNPHYS, "initial CFL step is %g", dtmin);
   const double est = std::ceil(T / dtmin);
-  const long nest = est > 1e9 ? 1000000000L : (long)est;
-  const bool graphs = c->use_graphs;
-  if (graphs) {
-    if (int rc = ensure_chunk_graph(c, pool, interval, slots)) return rc;
-  }
+  *nest = est > 1e9 ? 1000000000L : (long)est;
+  return 0;
+}
+
+// The march itself, one launch per step for the whole batch: graphs of
+// kGraphChunk steps, then single launches for the rest (a launch of finished
+// members only costs 1.7 us, and a graph of few launches costs more than they
+// do: 6.0 us a step at 64x128 in graphs of 6 against 5.5 launched singly and
+// 5.4 in graphs of 48).  Members that are done skip their blocks; the host
+// checks the number of active members once per round of launches.  Before
+// each check `finish` enqueues what the caller does with the final states,
+// so that a march that ended as estimated needs no further synchronisation.
+// On return (stream synced) final_ctl(c) holds the per-member step counts,
+// c->report the flags, step counts and KE(0) (sc(1)); the final state of member
+// b is in S0 if its step count is even, else in S1.  Snapshots of U^n go to
+// `pool` every `interval` steps when pool is not null.
+template <class Finish>
+int march_run(rt_ctx* c, long nest, double* pool, int interval, int slots, Finish&& finish) {
+  Params& P = c->P;
   long launched = 0;
   // the first round stops where the step log would overflow, so that a T
   // beyond max_steps is refused after at most one round past the limit
   long target = std::min<long>(nest, (long)c->max_steps + kGraphChunk + 2);
-  Flags f{};
+  const bool graphs = c->use_graphs && target >= kGraphChunk;
+  if (graphs) {
+    if (int rc = ensure_chunk_graph(c, pool, interval, slots)) return rc;
+  }
   for (;;) {
     while (launched < target) {
-      if (graphs) {
+      if (graphs && launched % kGraphChunk == 0 && target - launched >= kGraphChunk) {
         RT_HIP(hipGraphLaunch(c->chunk_exec, c->stream));
         launched += kGraphChunk;
         continue;
@@ -312,7 +327,10 @@ int march(rt_ctx* c, double T, double* pool, int interval, int slots) {
       ++launched;
     }
     c->last_launch = launched;
-    if (int rc = read_flags(c, &f, false)) return rc;
+    if (int rc = finish()) return rc;
+    RT_HIP(rtk::launch_report(P, final_ctl(c), c->flags, c->sc(1), c->report, c->stream));
+    RT_HIP(hipStreamSynchronize(c->stream));
+    const Flags& f = c->report->flags;
     if (f.n_active == 0 || f.err_unphys || f.err_overflow) break;
     if (launched > (long)c->max_steps + kGraphChunk + 2) {
       return fail(RT_ENOMEM, "march needs more than %d steps (workspace max_steps)", c->max_steps);
@@ -320,6 +338,16 @@ int march(rt_ctx* c, double T, double* pool, int interval, int slots) {
     target = launched + std::max<long>(8, nest / 32);
   }
   return 0;
+}
+
+// Status of the march just run, its flags cleared for the next call.
+int march_status(rt_ctx* c, bool* snaps_fit) {
+  const Flags f = c->report->flags;
+  if (f.err_unphys || f.err_overflow)
+    RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->flags), 0, 2, c->stream));
+  if (f.snap_overflow) RT_HIP(rtk::launch_fill_i32(&c->flags->snap_overflow, 0, 1, c->stream));
+  if (snaps_fit) *snaps_fit = !f.snap_overflow;
+  return flags_status(f);
 }
 
 }  // namespace
@@ -557,7 +585,7 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
   if (e == hipSuccess) e = timed([&](int) { return rtk::launch_step(P, step_tile, a, s); }, &out[0]);
   if (e == hipSuccess) e = rtk::launch_copy(U, c->S0, se, s);
   if (e == hipSuccess) e = rtk::launch_reduce(P, 0, c->S0, nullptr, c->partial, c->red_blocks, c->sc(0), s);
-  if (e == hipSuccess) e = rtk::launch_march_begin(P, c->sc(0), 1e300, c->ctl, c->acc, c->flags, s);
+  if (e == hipSuccess) e = rtk::launch_march_begin(P, c->sc(0), 1e300, c->ctl, c->acc, c->flags, c->report, s);
   if (e == hipSuccess)
     e = timed(
         [&](int k) {
@@ -685,6 +713,11 @@ int rt_set_workspace(rt_ctx* c, void* dev, size_t bytes, int32_t max_steps) {
   if (reinterpret_cast<uintptr_t>(dev) & 255) return fail(RT_EINVAL, "workspace must be 256-byte aligned");
   const Layout L = layout(c, max_steps);
   if (bytes < L.total) return fail(RT_ENOMEM, "workspace of %zu bytes < %zu needed", bytes, L.total);
+  if (!c->report) {
+    void* p = nullptr;
+    RT_HIP(hipHostMalloc(&p, sizeof(rtk::Report) + (size_t)c->P.nb * sizeof(rtk::Report::Member), hipHostMallocDefault));
+    c->report = static_cast<rtk::Report*>(p);
+  }
   char* w = static_cast<char*>(dev);
   if (c->chunk_exec) {
     RT_HIP(hipGraphExecDestroy(c->chunk_exec));
@@ -764,18 +797,19 @@ int rt_integrate(rt_ctx* c, double* U, double T, double* t_out, int32_t* nsteps,
   if (!U || !(T > 0) || !std::isfinite(T)) return fail(RT_EINVAL, "need U and 0 < T < inf");
   if (dt_log && cap < 1) return fail(RT_EINVAL, "dt_log needs cap >= 1");
   RT_HIP(rtk::launch_copy(U, c->S0, c->state_elems(), c->stream));
-  if (int rc = march(c, T, nullptr, 1, 0)) return rc;
-  RT_HIP(rtk::launch_copy_final(c->P, final_ctl(c), c->S0, c->S1, U, t_out, nsteps, c->dt_log, c->max_steps, dt_log,
-                                cap, c->stream));
-  Flags f{};
-  if (int rc = read_flags(c, &f, true)) return rc;
-  if (int rc = flags_status(f)) return rc;
+  long nest = 0;
+  if (int rc = march_start(c, T, &nest)) return rc;
+  auto copy_out = [&]() -> int {
+    RT_HIP(rtk::launch_copy_final(c->P, final_ctl(c), c->S0, c->S1, U, t_out, nsteps, c->dt_log, c->max_steps, dt_log,
+                                  cap, c->stream));
+    return 0;
+  };
+  if (int rc = march_run(c, nest, nullptr, 1, 0, copy_out)) return rc;
+  if (int rc = march_status(c, nullptr)) return rc;
   if (dt_log) {
-    std::vector<Ctl> h(c->P.nb);
-    RT_HIP(hipMemcpyAsync(h.data(), final_ctl(c), sizeof(Ctl) * c->P.nb, hipMemcpyDeviceToHost, c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));
-    for (const Ctl& x : h)
-      if (x.nsteps > cap) return fail(RT_ENOMEM, "dt_log capacity %d < %d steps", cap, x.nsteps);
+    for (int b = 0; b < c->P.nb; ++b)
+      if (c->report->member[b].nsteps > cap)
+        return fail(RT_ENOMEM, "dt_log capacity %d < %d steps", cap, c->report->member[b].nsteps);
   }
   return 0;
 }
@@ -911,52 +945,47 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
   int interval = 1;
   size_t snap_slots = 0;
   int rev_slots = 0;
+  long nest = 0;
   if (pol->kind == RT_CKPT_STORE_ALL || pol->kind == RT_CKPT_UNIFORM) {
     interval = pol->kind == RT_CKPT_STORE_ALL ? 1 : pol->interval;
     if (interval < 1) return fail(RT_EINVAL, "interval must be >= 1");
     if (slots_total < (size_t)interval) return fail(RT_ENOMEM, "pool holds %zu states, need > %d", slots_total, interval - 1);
-    snap_slots = slots_total - (interval - 1);
-    if (int rc = march(c, T, pool, interval, (int)std::min<size_t>(snap_slots, 1u << 30))) return rc;
+    snap_slots = std::min<size_t>(slots_total - (interval - 1), 1u << 30);
   } else if (pol->kind == RT_CKPT_REVOLVE) {
     if (slots_total < 2) return fail(RT_ENOMEM, "revolve needs a pool of at least 2 states");
-    // The objective's forward march also leaves level-1 snapshots, every
-    // `interval` steps, in slots 0 .. rev_slots - 2 (slot 0: U^0); the
-    // interval comes from the step count the initial CFL step suggests.
     rev_slots = (int)std::min<size_t>(slots_total, 1u << 20);
-    RT_HIP(rtk::launch_reduce(P, 0, c->S0, nullptr, c->partial, c->red_blocks, c->sc(0), s));
-    std::vector<double> ms(P.nb);
-    RT_HIP(hipMemcpyAsync(ms.data(), c->sc(0), sizeof(double) * P.nb, hipMemcpyDeviceToHost, s));
-    RT_HIP(hipStreamSynchronize(s));
-    const double msmax = *std::max_element(ms.begin(), ms.end());
-    const double est = std::ceil(T * msmax / P.cfl);
-    const int n_est = !(est < 1e8) ? 100000000 : std::max(1, (int)est);
-    interval = rtrev::level1_interval(n_est, rev_slots, kRevolveMargin);
-    if (int rc = march(c, T, pool, interval, std::max(1, rev_slots - 1))) return rc;
+    snap_slots = std::max(1, rev_slots - 1);
   } else {
     return fail(RT_EINVAL, "unknown checkpoint kind %d", pol->kind);
   }
-  Flags f{};
-  if (int rc = read_flags(c, &f, true)) return rc;
-  if (int rc = flags_status(f)) return rc;
+  if (int rc = march_start(c, T, &nest)) return rc;
+  if (pol->kind == RT_CKPT_REVOLVE) {
+    // The objective's forward march also leaves level-1 snapshots, every
+    // `interval` steps, in slots 0 .. rev_slots - 2 (slot 0: U^0); the
+    // interval comes from the step count the initial CFL step suggests.
+    interval = rtrev::level1_interval((int)std::min<long>(nest, 100000000L), rev_slots, kRevolveMargin);
+  }
+  // final states, step counts
+  auto copy_out = [&]() -> int {
+    RT_HIP(rtk::launch_copy_final(P, final_ctl(c), c->S0, c->S1, c->L1, nullptr, c->nsteps, nullptr, 0, nullptr, 0, s));
+    return 0;
+  };
+  if (int rc = march_run(c, nest, pool, interval, (int)snap_slots, copy_out)) return rc;
   // Level-1 snapshots beyond the pool: the uniform policies cannot go on;
   // revolve falls back to one binomial schedule over the whole march from
   // U^0 in slot 0 (the march it just ran then served to count the steps).
-  const bool snaps_fit = !f.snap_overflow;
+  bool snaps_fit = true;
+  if (int rc = march_status(c, &snaps_fit)) return rc;
   if (!snaps_fit && pol->kind != RT_CKPT_REVOLVE)
     return fail(RT_ENOMEM, "checkpoint pool of %zu states overflowed", slots_total);
-
-  // step counts and final state
-  RT_HIP(rtk::launch_copy_final(P, final_ctl(c), c->S0, c->S1, c->L1, nullptr, c->nsteps, nullptr, 0, nullptr, 0, s));
   if (nsteps_out) RT_HIP(hipMemcpyAsync(nsteps_out, c->nsteps, sizeof(int32_t) * P.nb, hipMemcpyDeviceToDevice, s));
-  std::vector<int32_t> hn(P.nb);
-  std::vector<double> hke0(P.nb);
-  RT_HIP(hipMemcpyAsync(hn.data(), c->nsteps, sizeof(int32_t) * P.nb, hipMemcpyDeviceToHost, s));
-  RT_HIP(hipMemcpyAsync(hke0.data(), c->sc(1), sizeof(double) * P.nb, hipMemcpyDeviceToHost, s));
-  RT_HIP(hipStreamSynchronize(s));
-  if (!ek_base)
-    for (double k : hke0)
-      if (!(k > 0.0) || !std::isfinite(k)) return fail(RT_EINVAL, "KE(0) = %g: the perturbation is zero or not finite", k);
-  const int nmax = *std::max_element(hn.begin(), hn.end());
+  int nmax = 0;
+  for (int b = 0; b < P.nb; ++b) {
+    const rtk::Report::Member& m = c->report->member[b];
+    nmax = std::max(nmax, m.nsteps);
+    if (!ek_base && (!(m.ke0 > 0.0) || !std::isfinite(m.ke0)))
+      return fail(RT_EINVAL, "KE(0) = %g: the perturbation is zero or not finite", m.ke0);
+  }
 
   // terminal adjoint lambda^N into L0 (from U^N in L1)
   if (ek_base) {
@@ -1281,6 +1310,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     RT_HIP(rtk::launch_initial_adjoint_plain(P, uv0, lam, grad, s));
   else
     RT_HIP(rtk::launch_initial_adjoint(P, uv0, lam, c->sc(1), c->sc(2), R, grad, s));
+  Flags f{};
   if (int rc = read_flags(c, &f, true)) return rc;
   return flags_status(f);
 }

@@ -29,6 +29,16 @@ struct Flags {
   int32_t snap_overflow; // a snapshot fell beyond the pool's slots (the march goes on)
 };
 
+// What kernels report to the host about a march (pinned host memory).
+struct Report {
+  Flags flags;
+  struct Member {
+    double speed;  // largest signal speed of the initial state
+    double ke0;    // KE(0)
+    int32_t nsteps, pad;
+  } member[1];  // nb of them
+};
+
 // Arguments of the fused step kernel.
 constexpr int kAccSlots = 32;   // atomic-max slots per member and row
 constexpr int kAccStride = 16;  // uint64 per slot: one 128-byte line each
@@ -172,8 +182,12 @@ hipError_t launch_dt_correct(const Params& P, const AdjArgs& a, hipStream_t s);
 // b = baseline e_k field [B][ny][nx]).
 hipError_t launch_reduce(const Params& P, int kind, const double* a, const double* b, double* partial,
                          int nblk, double* out, hipStream_t s);
+// report: also every member's speed, to the host.
 hipError_t launch_march_begin(const Params& P, const double* maxspeed, double T, Ctl* ctl, uint64_t* acc,
-                              Flags* flags, hipStream_t s);
+                              Flags* flags, Report* report, hipStream_t s);
+// Flags, step counts and KE(0) to the host.
+hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report,
+                         hipStream_t s);
 hipError_t launch_cfl_from_speed(const Params& P, const double* maxspeed, double* dt, hipStream_t s);
 hipError_t launch_cfl_from_slots(const Params& P, uint64_t* acc, double* dt, hipStream_t s);  // and clears the slots
 hipError_t launch_copy_final(const Params& P, const Ctl* ctl, const double* A, const double* Bbuf, double* U,

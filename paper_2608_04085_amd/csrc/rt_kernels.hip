@@ -1181,10 +1181,12 @@ __global__ __launch_bounds__(256) void k_reduce_final(Params P, int kind, const 
   }
 }
 
-__global__ void k_march_begin(Params P, const double* ms, double T, Ctl* ctl, uint64_t* acc, Flags* flags) {
+__global__ void k_march_begin(Params P, const double* ms, double T, Ctl* ctl, uint64_t* acc, Flags* flags,
+                              Report* report) {
   const int b = threadIdx.x + blockIdx.x * blockDim.x;
   if (b == 0) flags->n_active = P.nb;
   if (b >= P.nb) return;
+  report->member[b].speed = ms[b];
   Ctl c;
   c.t = 0.0;
   c.T = T;
@@ -1214,6 +1216,14 @@ __global__ __launch_bounds__(64) void k_cfl_from_slots(Params P, uint64_t* acc, 
 __global__ void k_cfl_from_speed(Params P, const double* ms, double* dt) {
   const int b = threadIdx.x + blockIdx.x * blockDim.x;
   if (b < P.nb) dt[b] = P.cfl / ms[b];
+}
+
+__global__ void k_report(Params P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report) {
+  const int b = threadIdx.x + blockIdx.x * blockDim.x;
+  if (b == 0) report->flags = *flags;
+  if (b >= P.nb) return;
+  report->member[b].ke0 = ke0[b];
+  report->member[b].nsteps = ctl[b].nsteps;
 }
 
 __global__ void k_copy_final(Params P, const Ctl* ctl, const double* A, const double* Bb, double* U) {
@@ -1580,8 +1590,14 @@ hipError_t launch_reduce(const Params& P, int kind, const double* a, const doubl
 }
 
 hipError_t launch_march_begin(const Params& P, const double* ms, double T, Ctl* ctl, uint64_t* acc, Flags* flags,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(k_march_begin, dim3((P.nb + 63) / 64), dim3(64), 0, s, P, ms, T, ctl, acc, flags);
+                              Report* report, hipStream_t s) {
+  hipLaunchKernelGGL(k_march_begin, dim3((P.nb + 63) / 64), dim3(64), 0, s, P, ms, T, ctl, acc, flags, report);
+  return hipGetLastError();
+}
+
+hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_report, dim3((P.nb + 63) / 64), dim3(64), 0, s, P, ctl, flags, ke0, report);
   return hipGetLastError();
 }
 
