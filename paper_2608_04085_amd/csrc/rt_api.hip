@@ -998,7 +998,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
   double* lam = c->L0;
   double* lam_other = c->L1;
 
-  auto step_given = [&](const double* src, double* dst, int n, hipStream_t ss) -> int {
+  auto given_args = [&](const double* src, double* dst, int n) {
     rtk::StepArgs a{};
     a.U = src;
     a.Un = dst;
@@ -1007,13 +1007,17 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     a.dt_index = n;
     a.nsteps_limit = c->nsteps;
     a.flags = c->flags;
-    RT_HIP(rtk::launch_step(P, c->step_variant(), a, ss));
+    return a;
+  };
+  auto step_given = [&](const double* src, double* dst, int n, hipStream_t ss) -> int {
+    RT_HIP(rtk::launch_step(P, c->step_variant(), given_args(src, dst, n), ss));
     return 0;
   };
   const bool dtd = c->dt_mode == RT_DT_DIFFERENTIATED;
   // the folded sweep serves the frozen steps of the primitive variant
   const bool use_fold = c->folds() && !dtd && P.recon == RT_RECON_PRIMITIVE;
-  auto adjoint = [&](const double* Un, int n) -> int {
+  // beside: a step of the re-computation in the same launch, or null
+  auto adjoint = [&](const double* Un, int n, const rtk::StepArgs* beside) -> int {
     rtk::AdjArgs a{};
     a.U = Un;
     a.lam_next = lam;
@@ -1034,7 +1038,8 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dtd.batch = P.nb;
       a.dtd.mu_last = c->dtd_mu_last;
     }
-    RT_HIP(rtk::launch_adjoint(P, c->adj_variant(dtd), a, s));
+    if (beside) RT_HIP(rtk::launch_adj_fused_and_step(P, a, *beside, s));
+    else RT_HIP(rtk::launch_adjoint(P, c->adj_variant(dtd), a, s));
     if (dtd) RT_HIP(rtk::launch_dt_correct(P, a, s));  // updates lambda^n (a.lam) in place
     std::swap(lam, lam_other);
     return 0;
@@ -1109,7 +1114,13 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     // leaves room for one: K <= slots_total - (interval - 1)).
     const bool two = c->overlap && interval > 1 && K > 1 && slots_total >= (size_t)K + 2 * (size_t)(interval - 1);
     double* segs[2] = {state_slot((size_t)K), state_slot((size_t)K + (two ? interval - 1 : 0))};
-    if (two) {
+    // On small grids the two go in one launch, step beside adjoint step, on
+    // the caller's stream: no events and half the launches (64x128, segments
+    // of 8: 2.50 -> 2.13 ms per gradient).
+    const bool pair = two && !use_fold && c->adj_variant(dtd) == rtk::TILE_FUSED &&
+                      !(c->columns & RT_COLUMNS_STEP) && rtk::adj_fused_pairs(P);
+    const bool streams = two && !pair;
+    if (streams) {
       if (int rc = ensure_aux(c)) return rc;
       RT_HIP(hipEventRecord(c->seg_free[0], s));
       RT_HIP(hipEventRecord(c->seg_free[1], s));
@@ -1124,29 +1135,42 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
         if (int rc = step_given(st(k, n), st(k, n + 1), n, rs)) return rc;
       return 0;
     };
-    if (two) {
+    if (streams) {
       RT_HIP(hipStreamWaitEvent(c->aux_stream, c->seg_free[(K - 1) & 1], 0));
       if (int rc = recompute(K - 1, c->aux_stream)) return rc;
       RT_HIP(hipEventRecord(c->seg_ready[(K - 1) & 1], c->aux_stream));
+    } else if (pair) {
+      if (int rc = recompute(K - 1, s)) return rc;
     }
     for (int k = K - 1; k >= 0; --k) {
       const int base = k * interval, hi = std::min(base + interval, nmax);
-      if (two) {
+      if (streams) {
         if (k > 0) {
           RT_HIP(hipStreamWaitEvent(c->aux_stream, c->seg_free[(k - 1) & 1], 0));
           if (int rc = recompute(k - 1, c->aux_stream)) return rc;
           RT_HIP(hipEventRecord(c->seg_ready[(k - 1) & 1], c->aux_stream));
         }
         RT_HIP(hipStreamWaitEvent(s, c->seg_ready[k & 1], 0));
-      } else if (int rc = recompute(k, s)) {
-        return rc;
+      } else if (!pair) {
+        if (int rc = recompute(k, s)) return rc;
       }
-      for (int n = hi - 1; n >= base; --n)
-        if (int rc = use_fold ? adjoint_folded(st(k, n), n) : adjoint(st(k, n), n)) return rc;
-      if (two) RT_HIP(hipEventRecord(c->seg_free[k & 1], s));
+      // pair: the re-computation of segment k - 1, from its snapshot on
+      int m = pair && k > 0 ? base - interval : base;
+      for (int n = hi - 1; n >= base; --n) {
+        const bool beside = m < base - 1;
+        rtk::StepArgs st_args{};
+        if (beside) {
+          st_args = given_args(st(k - 1, m), st(k - 1, m + 1), m);
+          ++m;
+        }
+        if (int rc = use_fold ? adjoint_folded(st(k, n), n) : adjoint(st(k, n), n, beside ? &st_args : nullptr)) return rc;
+      }
+      for (; m < base - 1; ++m)
+        if (int rc = step_given(st(k - 1, m), st(k - 1, m + 1), m, s)) return rc;
+      if (streams) RT_HIP(hipEventRecord(c->seg_free[k & 1], s));
     }
     if (int rc = finish_folded()) return rc;
-    if (two) {
+    if (streams) {
       RT_HIP(hipEventRecord(c->aux_done, c->aux_stream));
       RT_HIP(hipStreamWaitEvent(s, c->aux_done, 0));
     }

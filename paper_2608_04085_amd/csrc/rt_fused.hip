@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include "rt_kernels.h"
+#include "rt_step.h"
 #include "rt_wave.h"
 
 namespace rtk {
@@ -37,17 +38,14 @@ struct FusedLDS {
   int32_t C[QY][QX];  // limiter cases, x slopes then y slopes
 };
 
+// One tile (tbx, tby) of member b.
 template <int TX, int TY, int NT, bool DTD, bool BAL>
-__global__ __launch_bounds__(NT) void k_adj_fused(Params P, AdjArgs a) {
+__device__ __forceinline__ void adj_tile_body(const Params& P, const AdjArgs& a, FusedLDS<TX, TY>& S, int b, int tbx,
+                                              int tby) {
   using LDS = FusedLDS<TX, TY>;
   constexpr int PX = LDS::PX, PY = LDS::PY, QX = LDS::QX, QY = LDS::QY, ZX = LDS::ZX, ZY = LDS::ZY;
   constexpr int EX = ZX > ZY ? ZX : ZY;  // threads beside the cells': first faces of rows and columns
   static_assert(NT >= ZX * ZY + EX && NT >= PX * PY && NT % 64 == 0, "one pass per phase");
-  __shared__ LDS S;
-
-  const int b = blockIdx.z;
-  int tbx, tby;
-  tile_of_block(tbx, tby);
   const int x0 = tbx * TX, y0 = tby * TY;
   const int tid = threadIdx.x;
   const int nx = P.nx, ny = P.ny;
@@ -371,6 +369,46 @@ __global__ __launch_bounds__(NT) void k_adj_fused(Params P, AdjArgs a) {
   }
 }
 
+template <int TX, int TY, int NT, bool DTD, bool BAL>
+__global__ __launch_bounds__(NT) void k_adj_fused(Params P, AdjArgs a) {
+  __shared__ FusedLDS<TX, TY> S;
+  int tbx, tby;
+  tile_of_block(tbx, tby);
+  adj_tile_body<TX, TY, NT, DTD, BAL>(P, a, S, blockIdx.z, tbx, tby);
+}
+
+// The adjoint of one step and, in the second half of the grid, a step at a
+// given dt of other states (the reverse sweep's re-computation of the segment
+// before): both are a chain of phases that leaves most of the chip idle on
+// small grids, so side by side they take little more than the longer one, and
+// the sweep needs no second stream and no events.
+template <int TX, int TY, int NT, bool DTD, bool BAL>
+__global__ __launch_bounds__(NT) void k_adj_fused_and_step(Params P, AdjArgs a, StepArgs st) {
+  __shared__ union {
+    FusedLDS<TX, TY> adj;
+    StepLDS<TX, TY, false> step;
+  } S;
+  int tbx, tby;
+  tile_of_block(tbx, tby);
+  const int b = blockIdx.z;
+  if (b < P.nb) adj_tile_body<TX, TY, NT, DTD, BAL>(P, a, S.adj, b, tbx, tby);
+  else step_tile_body<TX, TY, NT, BAL, false>(P, st, S.step, nullptr, b - P.nb, tbx, tby);
+}
+
+template <int TX, int TY, int NT, bool DTD, bool BAL>
+hipError_t launch_pair(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
+  const dim3 grid((P.nx + TX - 1) / TX, (P.ny + TY - 1) / TY, 2 * P.nb);
+  if (DTD && (a.dtd.count != (int)(grid.x * grid.y) || a.dtd.stride < a.dtd.count)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_adj_fused_and_step<TX, TY, NT, DTD, BAL>), grid, dim3(NT), 0, s, P, a, st);
+  return hipGetLastError();
+}
+template <int TX, int TY, int NT>
+hipError_t launch_pair_t(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
+  if (a.dtd.mu != nullptr)
+    return P.recon == 1 ? launch_pair<TX, TY, NT, true, true>(P, a, st, s) : launch_pair<TX, TY, NT, true, false>(P, a, st, s);
+  return P.recon == 1 ? launch_pair<TX, TY, NT, false, true>(P, a, st, s) : launch_pair<TX, TY, NT, false, false>(P, a, st, s);
+}
+
 template <int TX, int TY, int NT>
 hipError_t launch_t(const Params& P, const AdjArgs& a, hipStream_t s) {
   const dim3 grid((P.nx + TX - 1) / TX, (P.ny + TY - 1) / TY, P.nb);
@@ -445,6 +483,18 @@ hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s) {
     case 2: return launch_t<16, 16, 512>(P, a, s);
     case 3: return launch_t<24, 16, 704>(P, a, s);
     default: return launch_t<32, 16, 1024>(P, a, s);
+  }
+}
+
+bool adj_fused_pairs(const Params& P) { return pick_shape(P, P.nb, nullptr) <= 2; }
+
+hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
+  if (a.fold.Z != nullptr || st.ctl != nullptr || st.acc_out != nullptr) return hipErrorInvalidValue;
+  switch (pick_shape(P, P.nb, nullptr)) {
+    case 0: return launch_pair_t<8, 8, 256>(P, a, st, s);
+    case 1: return launch_pair_t<16, 8, 320>(P, a, st, s);
+    case 2: return launch_pair_t<16, 16, 512>(P, a, st, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -162,6 +162,10 @@ hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s);
 // The two in one launch on tiles with a halo of three cells (launch_adjoint
 // with TILE_FUSED): no folded gather, Z and codes unused.
 hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s);
+// The same and a step at a given dt (st: no ctl, no acc_out) in one launch, for
+// grids small enough that both fit beside each other (adj_fused_pairs).
+bool adj_fused_pairs(const Params& P);
+hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s);
 // Blocks per member of its grid (AdjArgs::Dtd::count) in a sweep of nb members.
 int adj_fused_blocks(const Params& P, int nb);
 // Expected time of a launch in us, from measurements: what the choice between
