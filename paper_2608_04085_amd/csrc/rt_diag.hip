@@ -11,11 +11,141 @@ namespace {
 
 constexpr int kSpecThreads = 256;
 
-// One block per (mode n, member b): each thread takes whole rows of the
-// selection, forms the row's Fourier coefficient at n with the twiddles
-// exp(-2 pi i k / nx) held in LDS (index n x mod nx, advanced by n per
-// column), and accumulates its squared modulus; a fixed-order tree sums
-// the threads.
+// DFTs of n <= kSplitMax points in two stages, n = n1 n2 with n1 the largest
+// divisor up to sqrt(n):
+//   Y[b][j] = sum_a f[a n2 + b] w^{a j n2},  j < n1, b < n2
+//   F[k]    = sum_b Y[b][k mod n1] w^{b k}
+// with w = e^{-2 pi i / n}: n1 + n2 products per coefficient instead of n.
+// Twiddles and Y in LDS; every twiddle is sincospi of its own angle.  The
+// direct kernels below, n products per coefficient, take prime n (n1 = 1) and
+// longer lines, whose tables and Y exceed the default LDS limit of 64 KB.
+// 256x256: rows 13.5 -> 5.0 us, columns 39.7 -> 5.6, one row's spectrum 11.3 ->
+// 3.4; bound by the LDS reads of the twiddles (two per product).
+constexpr int kSplitMax = 2048;
+
+int split_of(int n) {
+  int n1 = 1;
+  for (int d = 2; d * d <= n; ++d)
+    if (n % d == 0) n1 = d;
+  return n1;
+}
+
+bool splits(int n) { return n <= kSplitMax && split_of(n) > 1; }
+
+__device__ __forceinline__ void twiddles(int n, double* tw) {  // [0, n): cos(2 pi k / n), [n, 2 n): sin
+  for (int k = threadIdx.x; k < n; k += kSpecThreads) {
+    double sn, cs;
+    sincospi(2.0 * k / n, &sn, &cs);
+    tw[k] = cs;
+    tw[n + k] = sn;
+  }
+}
+
+// Stage 2 for coefficient k of a line's Y ([n2][n1] (re, im) pairs).
+__device__ __forceinline__ void stage2(int n, int n1, int n2, const double* tw, const double* Y, int k, double& re,
+                                       double& im) {
+  re = 0.0;
+  im = 0.0;
+  int idx = 0;
+  const double* y = Y + 2 * (k % n1);
+  for (int b = 0; b < n2; ++b) {
+    const double cr = y[2 * b * n1], ci = y[2 * b * n1 + 1], c = tw[idx], s = tw[n + idx];
+    re += cr * c + ci * s;  // (cr + i ci)(c - i s)
+    im += ci * c - cr * s;
+    idx += k;
+    if (idx >= n) idx -= n;
+  }
+}
+
+// Stage 1 of a row of real values into Y.
+__device__ __forceinline__ void stage1_real(int n, int n1, int n2, const double* tw, const double* f, double* Y) {
+  for (int o = threadIdx.x; o < n; o += kSpecThreads) {
+    const int b = o / n1, step = (o - b * n1) * n2;
+    double re = 0.0, im = 0.0;
+    int idx = 0;
+    for (int a = 0; a < n1; ++a) {
+      const double v = f[a * n2 + b];
+      re += v * tw[idx];
+      im -= v * tw[n + idx];
+      idx += step;
+      if (idx >= n) idx -= n;
+    }
+    Y[2 * o] = re;
+    Y[2 * o + 1] = im;
+  }
+}
+
+// C[b][y][k], k = 0 .. nx/2, of every row; one block per row and member.
+__global__ __launch_bounds__(kSpecThreads) void k_dft_rows_split(int nx, int ny, int n1, const double* f,
+                                                                 long long mstride, int nk, double* C) {
+  extern __shared__ double lds[];  // twiddles 2 nx, Y 2 nx
+  const int y = blockIdx.x, b = blockIdx.y;
+  twiddles(nx, lds);
+  __syncthreads();
+  stage1_real(nx, n1, nx / n1, lds, f + (long long)b * mstride + (size_t)y * nx, lds + 2 * nx);
+  __syncthreads();
+  double* c = C + ((size_t)b * ny + y) * nk * 2;
+  for (int k = threadIdx.x; k < nk; k += kSpecThreads) {
+    double re, im;
+    stage2(nx, n1, nx / n1, lds, lds + 2 * nx, k, re, im);
+    c[2 * k] = re;
+    c[2 * k + 1] = im;
+  }
+}
+
+// E[b][q][k] = |sum_y C[b][y][k] e^{-2 pi i q y / ny}|^2; one block per column
+// and member.
+__global__ __launch_bounds__(kSpecThreads) void k_dft_cols_split(int ny, int n1, int nk, const double* C, double* E) {
+  extern __shared__ double lds[];  // twiddles 2 ny, Y 2 ny
+  const int k = blockIdx.x, b = blockIdx.y, n2 = ny / n1;
+  double* Y = lds + 2 * ny;
+  twiddles(ny, lds);
+  __syncthreads();
+  const double* cb = C + ((size_t)b * ny * nk + k) * 2;
+  for (int o = threadIdx.x; o < ny; o += kSpecThreads) {
+    const int r = o / n1, step = (o - r * n1) * n2;
+    double re = 0.0, im = 0.0;
+    int idx = 0;
+    for (int a = 0; a < n1; ++a) {
+      const double* v = cb + (size_t)(a * n2 + r) * nk * 2;
+      const double cr = v[0], ci = v[1], c = lds[idx], s = lds[ny + idx];
+      re += cr * c + ci * s;
+      im += ci * c - cr * s;
+      idx += step;
+      if (idx >= ny) idx -= ny;
+    }
+    Y[2 * o] = re;
+    Y[2 * o + 1] = im;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < ny; q += kSpecThreads) {
+    double re, im;
+    stage2(ny, n1, n2, lds, Y, q, re, im);
+    E[((size_t)b * ny + q) * nk + k] = re * re + im * im;
+  }
+}
+
+// E[b][k] = |F[k]|^2 of one row; one block per member.
+__global__ __launch_bounds__(kSpecThreads) void k_one_row_spectrum(int nx, int n1, const double* f, long long mstride,
+                                                                   int nbins, double* E) {
+  extern __shared__ double lds[];
+  const int b = blockIdx.x;
+  twiddles(nx, lds);
+  __syncthreads();
+  stage1_real(nx, n1, nx / n1, lds, f + (long long)b * mstride, lds + 2 * nx);
+  __syncthreads();
+  for (int k = threadIdx.x; k < nbins; k += kSpecThreads) {
+    double re, im;
+    stage2(nx, n1, nx / n1, lds, lds + 2 * nx, k, re, im);
+    E[(size_t)b * nbins + k] = re * re + im * im;
+  }
+}
+
+// All rows, or one that is not split.  One block per (mode n, member b): each
+// thread takes whole rows of the selection, forms the row's Fourier
+// coefficient at n with the twiddles exp(-2 pi i k / nx) held in LDS (index
+// n x mod nx, advanced by n per column), and accumulates its squared modulus;
+// a fixed-order tree sums the threads.
 __global__ __launch_bounds__(kSpecThreads) void k_row_spectrum(int nx, int ny, const double* f, long long mstride,
                                                                int row, int nbins, double* E) {
   extern __shared__ double tw[];  // [0, nx): cos(2 pi k / nx), [nx, 2 nx): sin
@@ -53,8 +183,8 @@ __global__ __launch_bounds__(kSpecThreads) void k_row_spectrum(int nx, int ny, c
   if (tid == 0) E[(size_t)b * nbins + n] = red[0];
 }
 
-// 2-D DFT, pass 1: C[b][y][k] = sum_x f_b(y, x) e^{-2 pi i k x / nx} for
-// k = 0 .. nx/2, as (re, im) pairs.  One thread per coefficient, threads of
+// 2-D DFT of lines that are not split, pass 1: C[b][y][k] = sum_x f_b(y, x)
+// e^{-2 pi i k x / nx} for k = 0 .. nx/2, as (re, im) pairs.  One thread per coefficient, threads of
 // a block along k for one row (the row's values are read by every thread:
 // broadcast), twiddles in LDS.
 __global__ __launch_bounds__(kSpecThreads) void k_dft_rows(int nx, int ny, const double* f, long long mstride,
@@ -121,12 +251,20 @@ hipError_t launch_power_spectrum_2d(int nx, int ny, int nb, const double* f, lon
                                     double* E, hipStream_t s) {
   if (nx < 1 || nx > kSpecMaxNx || ny < 1 || ny > kSpecMaxNx || nb < 1) return hipErrorInvalidValue;
   const int nk = nx / 2 + 1;
-  hipLaunchKernelGGL(k_dft_rows, dim3((nk + kSpecThreads - 1) / kSpecThreads, ny, nb), dim3(kSpecThreads),
-                     2 * (size_t)nx * sizeof(double), s, nx, ny, f, member_stride, nk, C);
+  if (splits(nx))
+    hipLaunchKernelGGL(k_dft_rows_split, dim3(ny, nb), dim3(kSpecThreads), 4 * (size_t)nx * sizeof(double), s, nx, ny,
+                       split_of(nx), f, member_stride, nk, C);
+  else
+    hipLaunchKernelGGL(k_dft_rows, dim3((nk + kSpecThreads - 1) / kSpecThreads, ny, nb), dim3(kSpecThreads),
+                       2 * (size_t)nx * sizeof(double), s, nx, ny, f, member_stride, nk, C);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_dft_cols_power, dim3((ny + kSpecThreads - 1) / kSpecThreads, nk, nb), dim3(kSpecThreads),
-                     2 * (size_t)ny * sizeof(double), s, ny, nk, C, E);
+  if (splits(ny))
+    hipLaunchKernelGGL(k_dft_cols_split, dim3(nk, nb), dim3(kSpecThreads), 4 * (size_t)ny * sizeof(double), s, ny,
+                       split_of(ny), nk, C, E);
+  else
+    hipLaunchKernelGGL(k_dft_cols_power, dim3((ny + kSpecThreads - 1) / kSpecThreads, nk, nb), dim3(kSpecThreads),
+                       2 * (size_t)ny * sizeof(double), s, ny, nk, C, E);
   return hipGetLastError();
 }
 
@@ -134,6 +272,15 @@ hipError_t launch_row_spectrum(int nx, int ny, int nb, const double* f, long lon
                                hipStream_t s) {
   if (nx < 1 || nx > kSpecMaxNx || ny < 1 || nb < 1 || row < -1 || row >= ny) return hipErrorInvalidValue;
   const int nbins = nx / 2 + 1;
+  // One block per member does both stages in turn, where the direct kernel
+  // has a block per mode: split only while the block's chain is the shorter.
+  auto chunks = [](int n) { return (n + kSpecThreads - 1) / kSpecThreads; };
+  const int n1 = split_of(nx);
+  if (row >= 0 && splits(nx) && chunks(nx) * n1 + chunks(nbins) * (nx / n1) < nx) {
+    hipLaunchKernelGGL(k_one_row_spectrum, dim3(nb), dim3(kSpecThreads), 4 * (size_t)nx * sizeof(double), s, nx,
+                       n1, f + (size_t)row * nx, member_stride, nbins, E);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_row_spectrum, dim3(nbins, nb), dim3(kSpecThreads), 2 * (size_t)nx * sizeof(double), s, nx,
                      ny, f, member_stride, row, nbins, E);
   return hipGetLastError();
