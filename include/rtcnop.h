@@ -253,6 +253,9 @@ int rt_pool_bytes(const rt_ctx* ctx, int32_t kind, int32_t interval, int32_t nst
  * before scaling. */
 int rt_project_to_constraint(rt_ctx* ctx, double* uv, double delta, int32_t norm, int32_t set,
                              double* norm_out);
+/* The same into another array out (same layout; uv is kept). */
+int rt_project_into(rt_ctx* ctx, const double* uv, double delta, int32_t norm, int32_t set, double* out,
+                    double* norm_out);
 
 /* Per-member inner products of velocity fields: out[B] = sum_cells a . b
  * (device).  Used by the spectral projected-gradient step. */
@@ -303,7 +306,8 @@ int rt_set_graphs(rt_ctx* ctx, int32_t on);
  * re-computes segment k-1 on it while the adjoint of segment k runs on the
  * context's stream, if the pool holds two segment buffers beside the
  * snapshots (the size rt_pool_bytes returns); with room for one, the sweep
- * runs on one stream.  RT_CKPT_REVOLVE with two or more members runs the
+ * runs on one stream; on small grids the steps ride in the adjoint's
+ * launches instead, all on the context's stream.  RT_CKPT_REVOLVE with two or more members runs the
  * binomial plan for members [0, B/2) on the context's stream and for
  * [B/2, B) on the second one, one action later, each on its own slice of
  * every buffer.  Results are identical either way; on = 0 runs everything

@@ -1116,7 +1116,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     double* segs[2] = {state_slot((size_t)K), state_slot((size_t)K + (two ? interval - 1 : 0))};
     // On small grids the two go in one launch, step beside adjoint step, on
     // the caller's stream: no events and half the launches (64x128, segments
-    // of 8: 2.50 -> 2.13 ms per gradient).
+    // of 8: 2.50 -> 2.10 ms per gradient).
     const bool pair = two && !use_fold && c->adj_variant(dtd) == rtk::TILE_FUSED &&
                       !(c->columns & RT_COLUMNS_STEP) && rtk::adj_fused_pairs(P);
     const bool streams = two && !pair;
@@ -1394,13 +1394,17 @@ int rt_ek_anomaly(rt_ctx* c, const double* U, const double* ek_base, double* J) 
   return 0;
 }
 
-int rt_project_to_constraint(rt_ctx* c, double* uv, double delta, int32_t norm, int32_t set, double* norm_out) {
+int rt_project_into(rt_ctx* c, const double* uv, double delta, int32_t norm, int32_t set, double* out, double* norm_out) {
   if (int rc = need_ws(c)) return rc;
-  if (!uv || !(delta > 0) || norm < 0 || norm > 2 || set < 0 || set > 1) return fail(RT_EINVAL, "bad argument");
+  if (!uv || !out || !(delta > 0) || norm < 0 || norm > 2 || set < 0 || set > 1) return fail(RT_EINVAL, "bad argument");
   double* m = norm_out ? norm_out : c->sc(4);
   RT_HIP(rtk::launch_reduce(c->P, 2 + norm, uv, nullptr, c->partial, c->red_blocks, m, c->stream));
-  RT_HIP(rtk::launch_scale_project(c->P, uv, m, delta, norm, set, c->stream));
+  RT_HIP(rtk::launch_scale_project(c->P, uv, m, delta, norm, set, out, c->stream));
   return 0;
+}
+
+int rt_project_to_constraint(rt_ctx* c, double* uv, double delta, int32_t norm, int32_t set, double* norm_out) {
+  return rt_project_into(c, uv, delta, norm, set, uv, norm_out);
 }
 
 int rt_dot(rt_ctx* c, const double* a, const double* b, double* out) {

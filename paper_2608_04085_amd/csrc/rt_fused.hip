@@ -486,7 +486,9 @@ hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s) {
   }
 }
 
-bool adj_fused_pairs(const Params& P) { return pick_shape(P, P.nb, nullptr) <= 2; }
+// Whether the small shapes, those with a paired kernel, are the ones that run,
+// and the pair's grid holds both halves of the batch.
+bool adj_fused_pairs(const Params& P) { return P.nb <= 32767 && pick_shape(P, P.nb, nullptr) <= 2; }
 
 hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
   if (a.fold.Z != nullptr || st.ctl != nullptr || st.acc_out != nullptr) return hipErrorInvalidValue;

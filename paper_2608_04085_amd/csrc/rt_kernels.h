@@ -210,8 +210,8 @@ hipError_t launch_initial_adjoint_plain(const Params& P, const double* uv0, cons
 hipError_t launch_ek_field(const Params& P, const double* U, double* ek, hipStream_t s);
 // Mixing width of Eqs. 13-14 (rowmean: scratch [B][ny]).
 hipError_t launch_mix_width(const Params& P, const double* U, double* rowmean, double* h, hipStream_t s);
-hipError_t launch_scale_project(const Params& P, double* uv, const double* m, double delta, int norm,
-                                int set, hipStream_t s);
+hipError_t launch_scale_project(const Params& P, const double* uv, const double* m, double delta, int norm, int set,
+                                double* out, hipStream_t s);
 hipError_t launch_axpy(const Params& P, const double* x, const double* alpha, const double* y, double* out,
                        hipStream_t s);
 hipError_t launch_ratio(int nb, const double* num, const double* den, double* out, hipStream_t s);

@@ -41,7 +41,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 KERNEL_SOURCES = ["csrc/rt_kernels.hip", "csrc/rt_columns.hip", "csrc/rt_fused.hip", "csrc/rt_device.h",
-                  "csrc/rt_wave.h", "csrc/rt_kernels.h"]
+                  "csrc/rt_step.h", "csrc/rt_wave.h", "csrc/rt_kernels.h"]
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
 COUNTERS_JSON = os.path.join(ROOT, "profiles", "counters.json")
 COPY_BYTES = 2 * 1024**3

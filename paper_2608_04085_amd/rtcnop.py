@@ -84,6 +84,7 @@ def load():
         "rt_grad_u0": [_vp, _vp, ctypes.c_double, ctypes.POINTER(RtCkptPolicy), _vp, _vp, _vp],
         "rt_pool_bytes": [_vp, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_size_t)],
         "rt_project_to_constraint": [_vp, _vp, ctypes.c_double, _i32, _i32, _vp],
+        "rt_project_into": [_vp, _vp, ctypes.c_double, _i32, _i32, _vp, _vp],
         "rt_dot": [_vp, _vp, _vp, _vp],
         "rt_max_abs": [_vp, _vp, _vp],
         "rt_set_graphs": [_vp, _i32],
@@ -126,7 +127,7 @@ EXPORTED = ["rt_create", "rt_destroy", "rt_set_stream", "rt_workspace_bytes", "r
             "rt_set_tiles", "rt_ek_field", "rt_ek_anomaly", "rt_grad_ek_anomaly",
             "rt_mix_width", "rt_set_dt_mode", "rt_get_dt_mode", "rt_get_tile", "rt_revolve_stats",
             "rt_row_spectrum", "rt_ke_ratio", "rt_revolve_plan_stats", "rt_ke_ratio_noalloc",
-            "rt_power_spectrum_2d", "rt_set_columns", "rt_get_columns"]
+            "rt_power_spectrum_2d", "rt_set_columns", "rt_get_columns", "rt_project_into"]
 
 
 def _check(rc: int, call: str):
@@ -308,7 +309,7 @@ class Context:
 
     def set_overlap(self, on: bool):
         """Second stream in the reverse sweep (default on): the UNIFORM policy re-computes the next segment on
-        it, REVOLVE runs half of the members on it; results are identical."""
+        it (on small grids in the adjoint's launches), REVOLVE runs half of the members on it; results are identical."""
         _check(load().rt_set_overlap(self._h, 1 if on else 0), "rt_set_overlap")
 
     def autotune(self, U, reps: int = 20) -> str:
@@ -558,13 +559,14 @@ class Context:
         return J, g, n
 
     def project_to_constraint(self, uv, delta: float, norm: int = NORM_L2, kind: int = SET_SPHERE):
-        """In-place on a copy: returns (projected uv, norm before scaling)."""
+        """Returns (projected uv, norm before scaling); uv is kept."""
         self._sync_stream()
-        uv = self.as_dev(uv).reshape(self.shape_uv).clone()
+        uv = self.as_dev(uv).reshape(self.shape_uv)
+        out = torch.empty_like(uv)
         m = self._f64((self.cfg.batch,))
-        _check(load().rt_project_to_constraint(self._h, _ptr(uv), float(delta), int(norm), int(kind), _ptr(m)),
-               "rt_project_to_constraint")
-        return uv, m
+        _check(load().rt_project_into(self._h, _ptr(uv), float(delta), int(norm), int(kind), _ptr(out), _ptr(m)),
+               "rt_project_into")
+        return out, m
 
     def dot(self, a, b) -> torch.Tensor:
         self._sync_stream()
@@ -585,7 +587,10 @@ class Context:
         self._sync_stream()
         x = self.as_dev(x)
         y = self.as_dev(y)
-        al = self.as_dev(torch.as_tensor(alpha, dtype=torch.float64).expand(self.cfg.batch).clone())
+        if isinstance(alpha, (int, float)):  # filled on the device: a copy from host memory would wait for the stream
+            al = torch.full((self.cfg.batch,), float(alpha), dtype=torch.float64, device=self.device)
+        else:
+            al = self.as_dev(torch.as_tensor(alpha, dtype=torch.float64).expand(self.cfg.batch))
         out = torch.empty_like(x)
         _check(load().rt_axpy(self._h, _ptr(x), _ptr(al), _ptr(y), _ptr(out)), "rt_axpy")
         return out
