@@ -307,11 +307,11 @@ int rt_set_graphs(rt_ctx* ctx, int32_t on);
  * context's stream, if the pool holds two segment buffers beside the
  * snapshots (the size rt_pool_bytes returns); with room for one, the sweep
  * runs on one stream; on small grids the steps ride in the adjoint's
- * launches instead, all on the context's stream.  RT_CKPT_REVOLVE with two or more members runs the
- * binomial plan for members [0, B/2) on the context's stream and for
- * [B/2, B) on the second one, one action later, each on its own slice of
- * every buffer.  Results are identical either way; on = 0 runs everything
- * on the context's stream. */
+ * launches instead, all on the context's stream.  RT_CKPT_REVOLVE with two
+ * or more members (column kernels: other than three) runs the binomial plan
+ * for members [0, B/2) on the context's stream and for [B/2, B) on the second
+ * one, one action later, each on its own slice of every buffer.  Results are
+ * identical either way; on = 0 runs everything on the context's stream. */
 int rt_set_overlap(rt_ctx* ctx, int32_t on);
 int rt_get_tiles(const rt_ctx* ctx, int32_t* step_tile, int32_t* adj_tile);
 /* The step kernel's variant (as rt_get_tiles' step_tile). */

@@ -401,7 +401,7 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   // size, fused on tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6
   // against 18.2, 512x512 22.0 against 28.0) or, where its expected time is
   // less, by columns (512x768 32.0 against 32.7 fused, 512x1024 40 against 44,
-  // 8 x 512x1024 194 against 314 and the pair's 398).  The tile variants that
+  // 8 x 512x1024 181 against 314 and the pair's 398).  The tile variants that
   // rt_get_tiles names for the adjoint, and for the step beyond one round, are
   // the fastest of the tile kernels; rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
@@ -1198,8 +1198,16 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     // has launched its first kernels, so that one group's gather (bound by
     // HBM) and steps overlap another's kernel A (bound by VALU issue)
     // instead of running in lockstep with it.
-    const bool split = c->overlap && P.nb >= 2;
+    // Column kernels of the two groups go side by side, one wavefront per SIMD
+    // each: sized to fill the chip alone, each would wait for the other's
+    // wavefronts to end (2 x 512x1024 11.3 ms per gradient, side by side 10.1,
+    // one stream 10.3; 8 x 512x1024 108, 104, 105).  Three members leave one
+    // group with half the other's work and are faster in one (3 x 500x700 15.8
+    // against 16.6, 3 x 512x1024 14.1 and 14.8; five and seven split as well).
+    const bool columns = c->adj_variant(dtd) == rtk::TILE_COLUMNS;
+    const bool split = c->overlap && P.nb >= 2 && !(columns && P.nb == 3);
     const int ng = split ? std::min(P.nb, kSplitGroups) : 1;
+    const bool beside = columns && split;
     const size_t N = (size_t)P.nx * P.ny, sm = 4 * N;
     struct Group {
       Params P;
@@ -1237,6 +1245,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dt_index = n;
       a.nsteps_limit = c->nsteps + G.b0;
       a.flags = c->flags;
+      a.beside = beside;
       RT_HIP(rtk::launch_step(G.P, c->step_variant(), a, G.st));
       return 0;
     };
@@ -1252,6 +1261,7 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.dt_index = n;
       a.nsteps_limit = c->nsteps + G.b0;
       a.flags = c->flags;
+      a.beside = beside;
       if (dtd) {
         a.dtd.mu = c->dtd_mu + G.b0 * (size_t)c->dtd_stride;
         a.dtd.smax = c->dtd_smax + G.b0 * (size_t)c->dtd_stride;

@@ -10,12 +10,13 @@
 // k_step_cols is bound by VALU issue: about 490 instructions per row and
 // wavefront at a given dt (530 in the march) where the 16x15 tiles take 845
 // per 64 cells plus their barriers.  Two rows per loop turn save 3-6 % (what
-// a row hands to the next changes registers by name, not by moves).  Tiles
-// against columns, us: 8 x 1024x2048 550 -> 320 given dt and 590 -> 348 in
-// the march; 8 x 512x1024 153 -> 84 and 172 -> 94; 64 x 128x256 79 -> 58 and
-// 95 -> 63; 1024x2048 68 -> 47 and 77 -> 51.
+// a row hands to the next changes registers by name, not by moves), and 4 %
+// more come from wavefronts that keep pace (below).  Tiles against columns,
+// us: 8 x 1024x2048 550 -> 315 given dt and 590 -> 338 in the march; 8 x
+// 512x1024 153 -> 79 and 172 -> 89; 64 x 128x256 79 -> 55 and 95 -> 60;
+// 1024x2048 68 -> 47 and 77 -> 51.
 //
-// k_adj_cols is the whole adjoint of a step in one launch: about 990 VALU
+// k_adj_cols is the whole adjoint of a step in one launch: about 970 VALU
 // instructions per row and wavefront, and no intermediates in memory (the
 // tile pair moves 1294 MiB per launch at 8 x 512x1024, most of it between its
 // two kernels).  It is bound by registers and latency: 220 registers per lane
@@ -26,8 +27,10 @@
 // 8 x 512x1024; with all of it in registers 398).  The cases travel as binary
 // exponents, so that a weight costs one ldexp, and the HLLC adjoint scatters
 // its upwind side by exact products (1100 -> 990 instructions, 201 -> 194).
-// Tiles against columns, us: 8 x 1024x2048 1530 -> 734, 8 x 512x1024 398 ->
-// 194, 64 x 128x256 198 -> 137, 512x1024 46 -> 40.
+// Two rows per loop turn and even pace: 194 -> 181.  (Reading a phase's LDS
+// values a phase ahead is worth nothing.)  Tiles against columns, us: 8 x
+// 1024x2048 1510 -> 685, 8 x 512x1024 398 -> 181, 64 x 128x256 198 -> 127,
+// 512x1024 46 -> 36.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -80,13 +83,28 @@ __device__ __forceinline__ W4 row_prims(const Params& P, const Raw& q, int gy) {
   return w;
 }
 
+// A SIMD issues its oldest wavefront first, so wavefronts with the same work
+// end one after the other and the last runs alone, at its own latency (3 per
+// SIMD were resident for 66 % of the launch on average, 2 for 78 %).  Priority
+// falls with the rows still to come: whoever is ahead fills the others' gaps,
+// and they end together.  8 x 512x1024, us: step 102 -> 97, adjoint 200 -> 192.
+// Not with one wavefront per SIMD, whose priority would only hold up another
+// stream's blocks (32 x 64x128 gradient 9.2 ms, with it 9.4).  One call per two
+// rows.
+__device__ __forceinline__ void pace(int left, int rows) {
+  if (16 * left <= rows) __builtin_amdgcn_s_setprio(0);
+  else if (4 * left <= rows) __builtin_amdgcn_s_setprio(1);
+  else if (2 * left <= rows) __builtin_amdgcn_s_setprio(2);
+  else __builtin_amdgcn_s_setprio(3);
+}
+
 struct D4 {
   double r, u, v, p;
 };
 __device__ __forceinline__ D4 diff(const W4& a, const W4& b) { return D4{a.r - b.r, a.u - b.u, a.v - b.v, a.p - b.p}; }
 
 template <bool BAL>
-__global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs a, int strips, int segs) {
+__global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs a, int strips, int segs, int paced) {
   const int lane = threadIdx.x & 63;
   const int per = strips * segs;
   const int w = __builtin_amdgcn_readfirstlane(xcd_band((int)blockIdx.x, (int)gridDim.x) * kColWaves + (int)(threadIdx.x >> 6));
@@ -257,7 +275,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   };
   // two rows per turn, so that what a row hands to the next changes
   // registers by name instead of by moves
-  for (int j = ys > 0 ? ys - 1 : 0;;) {
+  const int j0 = ys > 0 ? ys - 1 : 0;
+  for (int j = j0;;) {
+    if (paced) pace(jend + 1 - j, jend + 1 - j0);
     row(j);
     if (++j > jend) break;
     row(j);
@@ -324,7 +344,7 @@ enum { kSx = 0, kSy = 4, kPrim = 8, kLam = 13, kYb = 17, kAcc = 21, kDir = 25, k
 __device__ __forceinline__ void phase() { asm volatile("" ::: "memory"); }
 
 template <bool BAL>
-__global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArgs a, int strips, int segs) {
+__global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArgs a, int strips, int segs, int paced) {
   __shared__ double sRow[kColWaves][kAdjKept][64];
   __shared__ int sCase[kColWaves][8][64];  // row k's limiter cases, x slopes then y slopes (mc_exponents)
   const int lane = threadIdx.x & 63;
@@ -562,7 +582,13 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
     un = u2;
     lm = ln;
   };
-  for (int m = m0; m <= m1; ++m) row(m);
+  for (int m = m0;;) {
+    if (paced) pace(m1 + 1 - m, m1 + 1 - m0);
+    row(m);
+    if (++m > m1) break;
+    row(m);
+    if (++m > m1) break;
+  }
   if (ye == ny) {
     double acc[4];
 #pragma unroll
@@ -576,13 +602,14 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
 // at the kernel's registers, the k with the least of c_k (rows per segment +
 // over).  That is the measured time of a launch in us less a constant 3: a
 // row costs c_k with k wavefronts on a SIMD, and a segment `over` rows' worth
-// below and above it.
+// below and above it.  A launch beside another one (beside) takes one
+// wavefront per SIMD and leaves the other its own.
 constexpr int kSimds = 1024;
 template <int K>
-int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, double* us = nullptr) {
+int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, bool beside, double* us = nullptr) {
   int best = 1;
   double cost = 1e300;
-  for (int k = 1; k <= K; ++k) {
+  for (int k = 1; k <= (beside ? 1 : K); ++k) {
     const int segs = std::min(ny, std::max(1, (int)((long)k * kSimds / ((long)strips * nb))));
     const double t = c[k - 1] * ((ny + segs - 1) / segs + over);
     if (t < cost) {
@@ -593,13 +620,13 @@ int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, 
   if (us) *us = cost + 3.0;
   return best;
 }
-// 512x1024, x 4 and x 8 members, given dt: 51.2 and 95.9 us with one
-// wavefront per SIMD, 46.8 and 85.2 with two, 46.3 and 83.7 with three;
-// 512x1024 alone 17.7, 17.1, 16.9.
-constexpr double kStepRow[3] = {1.23, 2.10, 3.03}, kStepOver = 2.3;
-// 512x512, x768, x1024: 25.9, 32.0, 40.3 us with one; 512x1024 x 4 and x 8: 106
-// and 194 with two.
-constexpr double kAdjRow[2] = {2.9, 4.8}, kAdjOver = 3.0;
+// Step, noisy states, launch included, with one, two and three wavefronts per
+// SIMD: 512x1024 19.9, 18.7, 18.6; x 4 members 58.8, 51.6, 52.4; x 8 106, 93.0,
+// 91.3; 64 x 128x256 76.2, 67.8, 62.9; 8 x 1024x2048 382, 348, 345.
+constexpr double kStepRow[3] = {1.23, 2.12, 3.03}, kStepOver = 2.3;
+// Adjoint, the same with one and two: 512x512 25.9, 29.1; 512x1024 39.6, 38.4;
+// x 4 118, 99.8; x 8 224, 189; 64 x 128x256 163, 135.
+constexpr double kAdjRow[2] = {2.9, 4.6}, kAdjOver = 2.7;
 
 }  // namespace
 
@@ -607,38 +634,40 @@ double step_cols_us(const Params& P) {
   // a little less than the fit's constant below a few rows: 300x300 7.6,
   // 256x512 9.0, 384x512 10.5
   double us;
-  (void)row_segments(P.ny, (P.nx + kStepOwn - 1) / kStepOwn, P.nb, kStepRow, kStepOver, &us);
+  (void)row_segments(P.ny, (P.nx + kStepOwn - 1) / kStepOwn, P.nb, kStepRow, kStepOver, false, &us);
   return us - 0.6;
 }
 
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
   const int strips = (P.nx + kStepOwn - 1) / kStepOwn;
-  const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver);
+  const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
+  const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
   if (P.recon == 1)
-    hipLaunchKernelGGL((k_step_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+    hipLaunchKernelGGL((k_step_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
   else
-    hipLaunchKernelGGL((k_step_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+    hipLaunchKernelGGL((k_step_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
   return hipGetLastError();
 }
 
 double adj_cols_us(const Params& P) {
   double us;
-  (void)row_segments(P.ny, (P.nx + kAdjOwn - 1) / kAdjOwn, P.nb, kAdjRow, kAdjOver, &us);
+  (void)row_segments(P.ny, (P.nx + kAdjOwn - 1) / kAdjOwn, P.nb, kAdjRow, kAdjOver, false, &us);
   return us;
 }
 
 hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s) {
   if (a.fold.Z != nullptr || a.dtd.mu != nullptr) return hipErrorInvalidValue;
   const int strips = (P.nx + kAdjOwn - 1) / kAdjOwn;
-  const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjOver);
+  const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
+  const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
   if (P.recon == 1)
-    hipLaunchKernelGGL((k_adj_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+    hipLaunchKernelGGL((k_adj_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
   else
-    hipLaunchKernelGGL((k_adj_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs);
+    hipLaunchKernelGGL((k_adj_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
   return hipGetLastError();
 }
 

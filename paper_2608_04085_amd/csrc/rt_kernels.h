@@ -73,6 +73,7 @@ struct StepArgs {
   const int32_t* nsteps_limit;
   uint64_t* acc_out;
   Flags* flags;
+  bool beside;  // another launch of the kind runs at the same time (column kernels leave it its wavefront slots)
 };
 
 struct AdjArgs {
@@ -85,6 +86,7 @@ struct AdjArgs {
   int32_t dt_stride, dt_index;
   const int32_t* nsteps_limit;  // members with dt_index >= limit[b] pass lambda through
   Flags* flags;
+  bool beside;  // as in StepArgs
   // Folded gather (fold.Z != nullptr): lambda^{n+1} is not read from
   // lam_next but formed on the tile + halo 1 from the previous adjoint
   // kernel's outputs for step n+1 (its Z, codes, state U^{n+1} and

@@ -7,7 +7,7 @@ import torch
 
 from oracle.rto import Oracle
 from paper_2608_04085_amd import inputs
-from paper_2608_04085_amd.config import CKPT_UNIFORM, RECON_BALANCED, RTConfig, paper_preset
+from paper_2608_04085_amd.config import CKPT_REVOLVE, CKPT_UNIFORM, RECON_BALANCED, RTConfig, paper_preset
 
 pytestmark = pytest.mark.gpu
 
@@ -201,3 +201,22 @@ def test_cfl_step_after_each_step_starts_from_cleared_slots(cfg):
         for U in (slow, fast, slow, slow):
             Un, nxt = r.step(U, dt, want_next=True)
             np.testing.assert_array_equal(host(nxt), host(r.cfl_dt(Un)))
+
+
+@pytest.mark.parametrize("nx,ny,nb", [(61, 40, 2), (130, 37, 3), (70, 21, 5), (300, 100, 70)])
+def test_groups_of_columns_side_by_side_have_the_bits_of_one_stream(nx, ny, nb):
+    # the binomial sweep in column kernels: two even groups, three members in
+    # one stream, uneven groups, launches of more than one wavefront per SIMD
+    from paper_2608_04085_amd import rtcnop
+    cfg = RTConfig(nx=nx, ny=ny, batch=nb)
+    uv = states(cfg) * np.linspace(0.1, 1.0, nb)[:, None, None, None]
+    r = rtcnop.Context(cfg, max_steps=64)
+    r.set_columns(rtcnop.COLUMNS_STEP | rtcnop.COLUMNS_ADJOINT)
+    T = 12.4 * float(host(r.cfl_dt(r.init_state(uv))).min())
+    want = [host(x) for x in r.grad_u0(uv, T, rtcnop.Policy(CKPT_UNIFORM, 1))]
+    for on in (False, True, True):
+        r.set_overlap(on)
+        got = [host(x) for x in r.grad_u0(uv, T, rtcnop.Policy(CKPT_REVOLVE, pool_bytes=5 * 32 * nx * ny * nb))]
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, b)
+    r.check_error()
