@@ -47,19 +47,28 @@ constexpr int kStepHalo = 2;                 // columns to each side a step need
 constexpr int kStepOwn = 64 - 2 * kStepHalo; // columns a wavefront of the step writes
 
 // The value of the lane to the right / to the left (whole wavefront active;
-// lane 63 / lane 0 get zero).
-__device__ __forceinline__ double from_right(double v) {
+// lane 63 / lane 0 get zero, or with ROT those of lane 0 / lane 63).
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x130, 0xf, 0xf, true);  // wave_shl:1
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x130, 0xf, 0xf, true);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-__device__ __forceinline__ double from_left(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x138, 0xf, 0xf, true);  // wave_shr:1
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x138, 0xf, 0xf, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+template <bool ROT>
+__device__ __forceinline__ double lane_right(double v) {
+  return lane_move<ROT ? 0x134 : 0x130>(v);  // wave_rol:1, wave_shl:1
 }
+template <bool ROT>
+__device__ __forceinline__ double lane_left(double v) {
+  return lane_move<ROT ? 0x13c : 0x138>(v);  // wave_ror:1, wave_shr:1
+}
+
+// A row of exactly 64 cells fills a wavefront and is periodic by rotation: no
+// columns beside the strip, and one strip where 60 (58) columns each take two.
+// 256 x 64x128, us: step 77 -> 43, in the march 89 -> 50, adjoint 160 -> 92; 16
+// x 64x128 step 10.0 -> 7.3 (tiles 8.2).
+inline bool row_is_wavefront(const Params& P) { return P.nx == 64; }
 
 // A value that is the same in every lane, in scalar registers.
 __device__ __forceinline__ double uniform(double v) { return read_lane(v, 0); }
@@ -103,8 +112,11 @@ struct D4 {
 };
 __device__ __forceinline__ D4 diff(const W4& a, const W4& b) { return D4{a.r - b.r, a.u - b.u, a.v - b.v, a.p - b.p}; }
 
-template <bool BAL>
+template <bool BAL, bool ROT>
 __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs a, int strips, int segs, int paced) {
+  constexpr int halo = ROT ? 0 : kStepHalo;
+  auto from_right = [](double v) __attribute__((always_inline)) { return lane_right<ROT>(v); };
+  auto from_left = [](double v) __attribute__((always_inline)) { return lane_left<ROT>(v); };
   const int lane = threadIdx.x & 63;
   const int per = strips * segs;
   const int w = __builtin_amdgcn_readfirstlane(xcd_band((int)blockIdx.x, (int)gridDim.x) * kColWaves + (int)(threadIdx.x >> 6));
@@ -114,9 +126,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   const int nx = P.nx, ny = P.ny;
   const size_t N = (size_t)nx * ny;
   const int ys = (int)((long)ny * seg / segs), ye = (int)((long)ny * (seg + 1) / segs);
-  const int x0 = strip * kStepOwn;
-  const uint32_t col = (uint32_t)wrapx(x0 - kStepHalo + lane, nx);
-  const bool own = lane >= kStepHalo && lane < 64 - kStepHalo && x0 - kStepHalo + lane < nx;
+  const int x0 = strip * (64 - 2 * halo);
+  const uint32_t col = (uint32_t)wrapx(x0 - halo + lane, nx);
+  const bool own = lane >= halo && lane < 64 - halo && x0 - halo + lane < nx;
   const bool first = t == 0;
   const double* U = a.U + (size_t)b * 4 * N;
   double* Un = a.Un + (size_t)b * 4 * N;
@@ -343,10 +355,13 @@ enum { kSx = 0, kSy = 4, kPrim = 8, kLam = 13, kYb = 17, kAcc = 21, kDir = 25, k
 // again there instead of staying in registers.
 __device__ __forceinline__ void phase() { asm volatile("" ::: "memory"); }
 
-template <bool BAL>
+template <bool BAL, bool ROT>
 __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArgs a, int strips, int segs, int paced) {
   __shared__ double sRow[kColWaves][kAdjKept][64];
   __shared__ int sCase[kColWaves][8][64];  // row k's limiter cases, x slopes then y slopes (mc_exponents)
+  constexpr int halo = ROT ? 0 : kAdjHalo;
+  auto from_right = [](double v) __attribute__((always_inline)) { return lane_right<ROT>(v); };
+  auto from_left = [](double v) __attribute__((always_inline)) { return lane_left<ROT>(v); };
   const int lane = threadIdx.x & 63;
   const int per = strips * segs;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -357,9 +372,9 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
   const int nx = P.nx, ny = P.ny;
   const size_t N = (size_t)nx * ny;
   const int ys = (int)((long)ny * seg / segs), ye = (int)((long)ny * (seg + 1) / segs);
-  const int x0 = strip * kAdjOwn;
-  const uint32_t col = (uint32_t)wrapx(x0 - kAdjHalo + lane, nx);
-  const bool own = lane >= kAdjHalo && lane < 64 - kAdjHalo && x0 - kAdjHalo + lane < nx;
+  const int x0 = strip * (64 - 2 * halo);
+  const uint32_t col = (uint32_t)wrapx(x0 - halo + lane, nx);
+  const bool own = lane >= halo && lane < 64 - halo && x0 - halo + lane < nx;
   const double* U = a.U + (size_t)b * 4 * N;
   const double* Lm = a.lam_next + (size_t)b * 4 * N;
   double* Lo = a.lam + (size_t)b * 4 * N;
@@ -628,46 +643,53 @@ constexpr double kStepRow[3] = {1.23, 2.12, 3.03}, kStepOver = 2.3;
 // x 4 118, 99.8; x 8 224, 189; 64 x 128x256 163, 135.
 constexpr double kAdjRow[2] = {2.9, 4.6}, kAdjOver = 2.7;
 
+int step_strips(const Params& P) { return row_is_wavefront(P) ? 1 : (P.nx + kStepOwn - 1) / kStepOwn; }
+int adj_strips(const Params& P) { return row_is_wavefront(P) ? 1 : (P.nx + kAdjOwn - 1) / kAdjOwn; }
+
 }  // namespace
 
 double step_cols_us(const Params& P) {
   // a little less than the fit's constant below a few rows: 300x300 7.6,
   // 256x512 9.0, 384x512 10.5
   double us;
-  (void)row_segments(P.ny, (P.nx + kStepOwn - 1) / kStepOwn, P.nb, kStepRow, kStepOver, false, &us);
+  (void)row_segments(P.ny, step_strips(P), P.nb, kStepRow, kStepOver, false, &us);
   return us - 0.6;
 }
 
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
-  const int strips = (P.nx + kStepOwn - 1) / kStepOwn;
+  const int strips = step_strips(P);
   const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
   const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
-  if (P.recon == 1)
-    hipLaunchKernelGGL((k_step_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
-  else
-    hipLaunchKernelGGL((k_step_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
+  const dim3 block(64 * kColWaves);
+  const bool rot = row_is_wavefront(P);
+  if (P.recon == 1 && rot) hipLaunchKernelGGL((k_step_cols<true, true>), grid, block, 0, s, P, a, strips, segs, paced);
+  else if (P.recon == 1) hipLaunchKernelGGL((k_step_cols<true, false>), grid, block, 0, s, P, a, strips, segs, paced);
+  else if (rot) hipLaunchKernelGGL((k_step_cols<false, true>), grid, block, 0, s, P, a, strips, segs, paced);
+  else hipLaunchKernelGGL((k_step_cols<false, false>), grid, block, 0, s, P, a, strips, segs, paced);
   return hipGetLastError();
 }
 
 double adj_cols_us(const Params& P) {
   double us;
-  (void)row_segments(P.ny, (P.nx + kAdjOwn - 1) / kAdjOwn, P.nb, kAdjRow, kAdjOver, false, &us);
+  (void)row_segments(P.ny, adj_strips(P), P.nb, kAdjRow, kAdjOver, false, &us);
   return us;
 }
 
 hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s) {
   if (a.fold.Z != nullptr || a.dtd.mu != nullptr) return hipErrorInvalidValue;
-  const int strips = (P.nx + kAdjOwn - 1) / kAdjOwn;
+  const int strips = adj_strips(P);
   const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
   const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
-  if (P.recon == 1)
-    hipLaunchKernelGGL((k_adj_cols<true>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
-  else
-    hipLaunchKernelGGL((k_adj_cols<false>), grid, dim3(64 * kColWaves), 0, s, P, a, strips, segs, paced);
+  const dim3 block(64 * kColWaves);
+  const bool rot = row_is_wavefront(P);
+  if (P.recon == 1 && rot) hipLaunchKernelGGL((k_adj_cols<true, true>), grid, block, 0, s, P, a, strips, segs, paced);
+  else if (P.recon == 1) hipLaunchKernelGGL((k_adj_cols<true, false>), grid, block, 0, s, P, a, strips, segs, paced);
+  else if (rot) hipLaunchKernelGGL((k_adj_cols<false, true>), grid, block, 0, s, P, a, strips, segs, paced);
+  else hipLaunchKernelGGL((k_adj_cols<false, false>), grid, block, 0, s, P, a, strips, segs, paced);
   return hipGetLastError();
 }
 

@@ -24,6 +24,10 @@ CASES = [
     RTConfig(nx=130, ny=37, batch=64),
     RTConfig(nx=5, ny=9, batch=1100),
     paper_preset(62, batch=40).with_(recon=RECON_BALANCED),
+    # a row that is one wavefront
+    RTConfig(nx=64, ny=2),
+    RTConfig(nx=64, ny=37, batch=70),
+    paper_preset(64, batch=3).with_(recon=RECON_BALANCED),
 ]
 IDS = [f"{c.nx}x{c.ny}x{c.batch}-{c.recon}" for c in CASES]
 
