@@ -140,7 +140,7 @@ def _ptr(t: torch.Tensor | None):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous CUDA/HIP tensors"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()  # the argument types of load() make it a pointer
 
 
 def revolve_stats(nsteps: int, slots: int):
@@ -192,8 +192,8 @@ class Context:
                       cfg.recon)
         h = ctypes.c_void_p()
         with torch.cuda.device(self.device):  # rt_set_workspace launches its set-up on the current device
-            _check(L.rt_create(ctypes.byref(grid), ctypes.byref(phys), self._stream(), ctypes.byref(h)),
-                   "rt_create")
+            stream = torch.cuda.current_stream().cuda_stream
+            _check(L.rt_create(ctypes.byref(grid), ctypes.byref(phys), stream, ctypes.byref(h)), "rt_create")
             self._h = h
             if tile is not None:
                 _check(L.rt_set_tile(h, TILES[tile]), "rt_set_tile")
@@ -212,17 +212,13 @@ class Context:
         except Exception:
             pass
 
-    def _stream(self):
-        if not torch.cuda.is_available():
-            return None
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-
     def _sync_stream(self):
         # the library launches on the current device: refuse to run on another
         if torch.cuda.current_device() != self.device.index:
             raise RuntimeError(f"the context lives on {self.device}; make it the current device "
                                f"(torch.cuda.set_device) before calling it")
-        _check(load().rt_set_stream(self._h, self._stream()), "rt_set_stream")
+        # (the stream's handle alone: a torch.cuda.Stream object per call took 4 of a call's 12 us)
+        _check(load().rt_set_stream(self._h, torch._C._cuda_getCurrentRawStream(self.device.index)), "rt_set_stream")
 
     # ---------------------------------------------------------------- shapes
     @property
@@ -238,6 +234,8 @@ class Context:
 
     def as_dev(self, a) -> torch.Tensor:
         if isinstance(a, torch.Tensor):
+            if a.dtype is torch.float64 and a.device == self.device and a.is_contiguous():
+                return a
             return a.to(device=self.device, dtype=torch.float64).contiguous()
         return torch.as_tensor(a, dtype=torch.float64, device=self.device).contiguous()
 
