@@ -7,8 +7,8 @@
 // (4 of 64) and two rows around a segment.  The expressions are those of the
 // tile kernels, so the results are the same to the bit.
 //
-// k_step_cols is bound by VALU issue: about 490 instructions per row and
-// wavefront at a given dt (530 in the march) where the 16x15 tiles take 845
+// k_step_cols is bound by VALU issue: about 460 instructions per row and
+// wavefront at a given dt (500 in the march) where the 16x15 tiles take 845
 // per 64 cells plus their barriers.  Two rows per loop turn save 3-6 % (what
 // a row hands to the next changes registers by name, not by moves), and 4 %
 // more come from wavefronts that keep pace (below).  Tiles against columns,
@@ -16,7 +16,7 @@
 // 512x1024 153 -> 79 and 172 -> 89; 64 x 128x256 79 -> 55 and 95 -> 60;
 // 1024x2048 68 -> 47 and 77 -> 51.
 //
-// k_adj_cols is the whole adjoint of a step in one launch: about 970 VALU
+// k_adj_cols is the whole adjoint of a step in one launch: about 940 VALU
 // instructions per row and wavefront, and no intermediates in memory (the
 // tile pair moves 1294 MiB per launch at 8 x 512x1024, most of it between its
 // two kernels).  It is bound by registers and latency: 220 registers per lane
@@ -232,9 +232,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
     D4 xb = D4{from_right(wc.r) - wc.r, from_right(wc.u) - wc.u, from_right(wc.v) - wc.v, from_right(wc.p) - wc.p};
     D4 xa = D4{from_left(xb.r), from_left(xb.u), from_left(xb.v), from_left(xb.p)};
     int code;
-    const W4 sx = mc4_diff<false>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, code);
-    W4 sy = mc4_diff<false>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, code);
-    if constexpr (BAL) mc_p_balanced_diff<false>(P, wc, da.p, db.p, sy, code);
+    const W4 sx = mc4_diff<false, true>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, code);
+    W4 sy = mc4_diff<false, true>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, code);
+    if constexpr (BAL) mc_p_balanced_diff<false, true>(P, wc, da.p, db.p, sy, code);
     const W4 q = predict(P, wc, sx, sy, hx, hy, hg);
     if (j >= ys) {
       const FS bot{q.r - 0.5 * sy.r, q.v - 0.5 * sy.v, q.u - 0.5 * sy.u, q.p - 0.5 * sy.p};
@@ -469,9 +469,9 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
     const D4 xb = D4{from_right(wc.r) - wc.r, from_right(wc.u) - wc.u, from_right(wc.v) - wc.v, from_right(wc.p) - wc.p};
     const D4 xa = D4{from_left(xb.r), from_left(xb.u), from_left(xb.v), from_left(xb.p)};
     int code, cases[8];
-    const W4 sx = mc4_diff<false>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, code, cases);
-    W4 sy = mc4_diff<false>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, code, cases + 4);
-    if constexpr (BAL) mc_p_balanced_diff<false>(P, wc, da.p, db.p, sy, code, cases + 4);
+    const W4 sx = mc4_diff<false, true>(P, wc, xa.r, xa.u, xa.v, xa.p, xb.r, xb.u, xb.v, xb.p, code, cases);
+    W4 sy = mc4_diff<false, true>(P, wc, da.r, da.u, da.v, da.p, db.r, db.u, db.v, db.p, code, cases + 4);
+    if constexpr (BAL) mc_p_balanced_diff<false, true>(P, wc, da.p, db.p, sy, code, cases + 4);
 #pragma unroll
     for (int v = 0; v < 8; ++v) asm volatile("" : "+v"(cases[v]));  // here, while the differences are at hand
     const W4 q = predict(P, wc, sx, sy, hx, hy, hg);
