@@ -50,6 +50,11 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr int kMaxGroups = 4;
 // Groups the sweep uses (fewer if the batch has fewer members).
 constexpr int kSplitGroups = 2;
+// Differentiated steps: most tiles of a member whose next launch corrects
+// lambda.  Gradients with a launch of its own / so, ms: 64x128 (128 tiles) 2.41
+// / 2.18, 256x512 (256) 4.48 / 4.10, 512x512 (512) 14.1 / 13.5, 512x1024 (1024)
+// 14.1 / 15.0, 1024x1024 (2048) 32.0 / 38.8.
+constexpr int kDeferTiles = 512;
 
 struct rt_ctx {
   Params P;
@@ -100,7 +105,7 @@ struct rt_ctx {
   // Step sizes in the gradient: held at the forward run's values
   // (RT_DT_FROZEN) or differentiated (RT_DT_DIFFERENTIATED).
   int dt_mode = RT_DT_FROZEN;
-  double *dtd_mu = nullptr, *dtd_smax = nullptr, *dtd_mu_last = nullptr;
+  double *dtd_mu = nullptr, *dtd_smax = nullptr, *dtd_u = nullptr, *dtd_mu_last = nullptr;
   int32_t* dtd_imax = nullptr;
   int32_t dtd_stride = 0;
   double* bg_p = nullptr;  // [ny] background pressure rows of the well-balanced variant
@@ -136,7 +141,7 @@ namespace {
 
 struct Layout {
   size_t S0, S1, L0, L1, Z, Z2, codes, codes2, partial, rowmean, acc, ctl, flags, dt_log, nsteps, scal;
-  size_t dtd_mu, dtd_smax, dtd_imax, dtd_mu_last, bg_p, total;
+  size_t dtd_mu, dtd_smax, dtd_imax, dtd_u, dtd_mu_last, bg_p, total;
   int32_t dtd_stride;
 };
 
@@ -171,9 +176,11 @@ Layout layout(const rt_ctx* c, int32_t max_steps) {
   int adjblk = 1;
   for (int t = 0; t < rtk::TILE_COUNT; ++t) adjblk = std::max(adjblk, rtk::step_blocks(c->P, t));
   L.dtd_stride = adjblk;
-  L.dtd_mu = take((size_t)adjblk * c->P.nb * sizeof(double));
-  L.dtd_smax = take((size_t)adjblk * c->P.nb * sizeof(double));
-  L.dtd_imax = take((size_t)adjblk * c->P.nb * sizeof(int32_t));
+  // two of each: a launch may read what the one before it left
+  L.dtd_mu = take(2 * (size_t)adjblk * c->P.nb * sizeof(double));
+  L.dtd_smax = take(2 * (size_t)adjblk * c->P.nb * sizeof(double));
+  L.dtd_imax = take(2 * (size_t)adjblk * c->P.nb * sizeof(int32_t));
+  L.dtd_u = take(2 * (size_t)adjblk * c->P.nb * 4 * sizeof(double));
   L.dtd_mu_last = take((size_t)c->P.nb * sizeof(double));
   L.bg_p = take((size_t)c->P.ny * sizeof(double));
   L.total = off;
@@ -745,6 +752,7 @@ int rt_set_workspace(rt_ctx* c, void* dev, size_t bytes, int32_t max_steps) {
   c->dtd_mu = reinterpret_cast<double*>(w + L.dtd_mu);
   c->dtd_smax = reinterpret_cast<double*>(w + L.dtd_smax);
   c->dtd_imax = reinterpret_cast<int32_t*>(w + L.dtd_imax);
+  c->dtd_u = reinterpret_cast<double*>(w + L.dtd_u);
   c->dtd_mu_last = reinterpret_cast<double*>(w + L.dtd_mu_last);
   c->dtd_stride = L.dtd_stride;
   c->bg_p = reinterpret_cast<double*>(w + L.bg_p);
@@ -1014,6 +1022,27 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     return 0;
   };
   const bool dtd = c->dt_mode == RT_DT_DIFFERENTIATED;
+  // Differentiated steps in the fused kernel: the correction of lambda^{n+1},
+  // otherwise a launch of its own (4.7 us), is left to the launch that reads
+  // it, while a member's partials are few enough for every block to read all.
+  const bool dtd_fused = c->adj_variant(true) == rtk::TILE_FUSED;
+  const int dtd_count = dtd_fused ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
+  const bool dtd_deferred = dtd_fused && dtd_count <= kDeferTiles;
+  auto dtd_args = [&](size_t b0, int n) {  // of members from b0 on
+    const size_t half = (size_t)c->dtd_stride * P.nb, o = b0 * (size_t)c->dtd_stride;
+    const size_t w = o + (n & 1 ? half : 0), r = o + (n & 1 ? 0 : half);
+    rtk::AdjArgs::Dtd d{};
+    d.mu = c->dtd_mu + w;
+    d.smax = c->dtd_smax + w;
+    d.imax = c->dtd_imax + w;
+    d.u = c->dtd_u + 4 * w;
+    d.stride = c->dtd_stride;
+    d.count = dtd_count;
+    d.batch = P.nb;
+    d.mu_last = c->dtd_mu_last + b0;
+    if (dtd_deferred && n + 1 < nmax) d.before = {c->dtd_mu + r, c->dtd_smax + r, c->dtd_imax + r, c->dtd_u + 4 * r};
+    return d;
+  };
   // the folded sweep serves the frozen steps of the primitive variant
   const bool use_fold = c->folds() && !dtd && P.recon == RT_RECON_PRIMITIVE;
   // beside: a step of the re-computation in the same launch, or null
@@ -1029,18 +1058,10 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     a.dt_index = n;
     a.nsteps_limit = c->nsteps;
     a.flags = c->flags;
-    if (dtd) {
-      a.dtd.mu = c->dtd_mu;
-      a.dtd.smax = c->dtd_smax;
-      a.dtd.imax = c->dtd_imax;
-      a.dtd.stride = c->dtd_stride;
-      a.dtd.count = c->adj_variant(true) == rtk::TILE_FUSED ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
-      a.dtd.batch = P.nb;
-      a.dtd.mu_last = c->dtd_mu_last;
-    }
+    if (dtd) a.dtd = dtd_args(0, n);
     if (beside) RT_HIP(rtk::launch_adj_fused_and_step(P, a, *beside, s));
     else RT_HIP(rtk::launch_adjoint(P, c->adj_variant(dtd), a, s));
-    if (dtd) RT_HIP(rtk::launch_dt_correct(P, a, s));  // updates lambda^n (a.lam) in place
+    if (dtd && !(dtd_deferred && n > 0)) RT_HIP(rtk::launch_dt_correct(P, a, s));  // updates lambda^n (a.lam) in place
     std::swap(lam, lam_other);
     return 0;
   };
@@ -1262,18 +1283,9 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
       a.nsteps_limit = c->nsteps + G.b0;
       a.flags = c->flags;
       a.beside = beside;
-      if (dtd) {
-        a.dtd.mu = c->dtd_mu + G.b0 * (size_t)c->dtd_stride;
-        a.dtd.smax = c->dtd_smax + G.b0 * (size_t)c->dtd_stride;
-        a.dtd.imax = c->dtd_imax + G.b0 * (size_t)c->dtd_stride;
-        a.dtd.stride = c->dtd_stride;
-        a.dtd.count =
-            c->adj_variant(true) == rtk::TILE_FUSED ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
-        a.dtd.batch = P.nb;
-        a.dtd.mu_last = c->dtd_mu_last + G.b0;
-      }
+      if (dtd) a.dtd = dtd_args(G.b0, n);
       RT_HIP(rtk::launch_adjoint(G.P, c->adj_variant(dtd), a, G.st));
-      if (dtd) RT_HIP(rtk::launch_dt_correct(G.P, a, G.st));  // updates lambda^n (a.lam) in place
+      if (dtd && !(dtd_deferred && n > 0)) RT_HIP(rtk::launch_dt_correct(G.P, a, G.st));
       std::swap(G.lam, G.lam_other);
       return 0;
     };

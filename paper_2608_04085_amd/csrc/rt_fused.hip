@@ -73,6 +73,40 @@ __device__ __forceinline__ void adj_tile_body(const Params& P, const AdjArgs& a,
   const double dt = a.dt[(size_t)b * a.dt_stride + a.dt_index];
   const double hdtg = 0.5 * dt * P.g_y;
   int bad = 0;
+  // DTD: step n + 1's sum of mu and its cell of largest speed, as
+  // launch_dt_correct forms them (its 256 threads are this block's first), in
+  // the shadow of the loads below: 3 x 127x130 gradient 2.61 -> 2.28 ms
+  __shared__ double cm[4], cs[4];
+  __shared__ int ci[4], ct[4];
+  bool corrects = false;
+  if constexpr (DTD) {
+    corrects = a.dtd.before.mu != nullptr && a.dt_index + 1 < a.nsteps_limit[b];
+    if (corrects && tid < 256) {
+      const size_t o = (size_t)b * a.dtd.stride;
+      double m = 0.0, sp = -1.0;
+      int ix = 0x7fffffff, tile = 0;
+      auto merge = [&](double s2, int i2, int t2) {
+        if (s2 > sp || (s2 == sp && i2 < ix)) {
+          sp = s2;
+          ix = i2;
+          tile = t2;
+        }
+      };
+      for (int k = tid; k < a.dtd.count; k += 256) {
+        m += a.dtd.before.mu[o + k];
+        merge(a.dtd.before.smax[o + k], a.dtd.before.imax[o + k], k);
+      }
+      m = wave_sum(m);
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) merge(__shfl_xor(sp, d, 64), __shfl_xor(ix, d, 64), __shfl_xor(tile, d, 64));
+      if ((tid & 63) == 0) {
+        cm[tid >> 6] = m;
+        cs[tid >> 6] = sp;
+        ci[tid >> 6] = ix;
+        ct[tid >> 6] = tile;
+      }
+    }
+  }
 
   // primitives of the tile + 3 and lambda^{n+1} of the tile + 2
   {
@@ -125,6 +159,30 @@ __device__ __forceinline__ void adj_tile_body(const Params& P, const AdjArgs& a,
     }
   }
   __syncthreads();
+  if constexpr (DTD) {
+    if (corrects) {
+      // wherever this tile holds the cell (its lambda is read after the next
+      // barrier)
+      int w = 0;
+#pragma unroll
+      for (int k = 1; k < 4; ++k)
+        if (cs[k] > cs[w] || (cs[k] == cs[w] && ci[k] < ci[w])) w = k;
+      const int ix = ci[w];
+      const double m = ((cm[0] + cm[1]) + cm[2]) + cm[3];
+      const bool last = a.dt_index + 2 == a.nsteps_limit[b];  // step n + 1 was the member's last: its mu is kept
+      if (last && tid == 0 && tbx == 0 && tby == 0) a.dtd.mu_last[b] = m;
+      for (int k = tid; k < QX * QY; k += NT) {
+        const int j = y0 - 2 + k / QX, sy = j < 0 ? 0 : (j >= ny ? ny - 1 : j);
+        if (last || sy * nx + wrapx(x0 - 2 + k % QX, nx) != ix) continue;
+        const double* u = a.dtd.before.u + ((size_t)b * a.dtd.stride + ct[w]) * 4;
+        double d[4];
+        const double Sm = signal_speed_grad(P, u[0], u[1], u[2], u[3], d);
+        const double coef = (m - a.dtd.mu_last[b]) * (-P.cfl / (Sm * Sm));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) S.L[v][k / QX][k % QX] += coef * d[v];
+      }
+    }
+  }
 
   // slopes, their cases and the predicted states of the tile + 2 (but for the
   // three cells of each corner that no face needs)
@@ -360,8 +418,15 @@ __device__ __forceinline__ void adj_tile_body(const Params& P, const AdjArgs& a,
     }
     const double m = block_sum<NT>(mu, rmu);
     block_argmax<NT>(sp, ix, rsp, rix);
+    const size_t o = (size_t)b * a.dtd.stride + (size_t)tby * gridDim.x + tbx;
+    if (own && (int)c == ix) {
+      double* u = a.dtd.u + o * 4;
+      u[0] = u0;
+      u[1] = u1;
+      u[2] = u2;
+      u[3] = u3;
+    }
     if (tid == 0) {
-      const size_t o = (size_t)b * a.dtd.stride + (size_t)tby * gridDim.x + tbx;
       a.dtd.mu[o] = m;
       a.dtd.smax[o] = sp;
       a.dtd.imax[o] = ix;
@@ -369,8 +434,9 @@ __device__ __forceinline__ void adj_tile_body(const Params& P, const AdjArgs& a,
   }
 }
 
+// (DTD: 128 registers, where 130 would leave three blocks of 256 threads per CU)
 template <int TX, int TY, int NT, bool DTD, bool BAL>
-__global__ __launch_bounds__(NT) void k_adj_fused(Params P, AdjArgs a) {
+__global__ __launch_bounds__(NT, DTD && NT <= 512 ? 4 : 1) void k_adj_fused(Params P, AdjArgs a) {
   __shared__ FusedLDS<TX, TY> S;
   int tbx, tby;
   tile_of_block(tbx, tby);
@@ -383,7 +449,7 @@ __global__ __launch_bounds__(NT) void k_adj_fused(Params P, AdjArgs a) {
 // small grids, so side by side they take little more than the longer one, and
 // the sweep needs no second stream and no events.
 template <int TX, int TY, int NT, bool DTD, bool BAL>
-__global__ __launch_bounds__(NT) void k_adj_fused_and_step(Params P, AdjArgs a, StepArgs st) {
+__global__ __launch_bounds__(NT, DTD ? 4 : 1) void k_adj_fused_and_step(Params P, AdjArgs a, StepArgs st) {
   __shared__ union {
     FusedLDS<TX, TY> adj;
     StepLDS<TX, TY, false> step;
@@ -398,7 +464,8 @@ __global__ __launch_bounds__(NT) void k_adj_fused_and_step(Params P, AdjArgs a, 
 template <int TX, int TY, int NT, bool DTD, bool BAL>
 hipError_t launch_pair(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
   const dim3 grid((P.nx + TX - 1) / TX, (P.ny + TY - 1) / TY, 2 * P.nb);
-  if (DTD && (a.dtd.count != (int)(grid.x * grid.y) || a.dtd.stride < a.dtd.count)) return hipErrorInvalidValue;
+  if (DTD && (a.dtd.count != (int)(grid.x * grid.y) || a.dtd.stride < a.dtd.count || !a.dtd.u || !a.nsteps_limit))
+    return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_adj_fused_and_step<TX, TY, NT, DTD, BAL>), grid, dim3(NT), 0, s, P, a, st);
   return hipGetLastError();
 }
@@ -414,7 +481,8 @@ hipError_t launch_t(const Params& P, const AdjArgs& a, hipStream_t s) {
   const dim3 grid((P.nx + TX - 1) / TX, (P.ny + TY - 1) / TY, P.nb);
   const bool bal = P.recon == 1;
   if (a.dtd.mu != nullptr) {
-    if (a.dtd.count != (int)(grid.x * grid.y) || a.dtd.stride < a.dtd.count) return hipErrorInvalidValue;
+    if (a.dtd.count != (int)(grid.x * grid.y) || a.dtd.stride < a.dtd.count || !a.dtd.u || !a.nsteps_limit)
+      return hipErrorInvalidValue;
     if (bal)
       hipLaunchKernelGGL((k_adj_fused<TX, TY, NT, true, true>), grid, dim3(NT), 0, s, P, a);
     else

@@ -99,12 +99,12 @@ struct AdjArgs {
     double* lam_out;         // lambda^{n+1}
     int32_t dt_index;        // n + 1
   } fold;
-  // Differentiated step size (dtd.mu != nullptr, two-kernel form only):
-  // kernel A also writes, per block (tile index ty * tiles_x + tx), its
+  // Differentiated step size (dtd.mu != nullptr; tile pair and fused kernel):
+  // the kernel also writes, per block (tile index ty * tiles_x + tx), its
   // share of mu = <lambda^{n+1}, dU^{n+1}/d dt> (every face once, every own
   // cell once) and the largest signal speed of U^n over its own cells with
-  // the smallest index of a cell that holds it; launch_dt_correct then
-  // combines them.
+  // the smallest index of a cell that holds it; launch_dt_correct, or the
+  // fused launch of the step before, then combines them.
   struct Dtd {
     double* mu;       // [B][stride]
     double* smax;     // [B][stride]
@@ -113,6 +113,16 @@ struct AdjArgs {
     int32_t count;    // tiles of the adjoint grid per member
     int32_t batch;    // members of the whole sweep: fixes the fused kernel's tile for launches over some of them
     double* mu_last;  // [B] mu of each member's last (clipped) step
+    // Fused kernel only: the state of that cell, and the same of step n + 1
+    // (mu == nullptr: none), from which this launch corrects the lambda^{n+1}
+    // that it reads; launch_dt_correct then follows the last launch alone.
+    double* u;  // [B][stride][4]
+    struct Before {
+      const double* mu;
+      const double* smax;
+      const int32_t* imax;
+      const double* u;
+    } before;
   } dtd;
 };
 

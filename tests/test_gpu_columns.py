@@ -224,3 +224,32 @@ def test_groups_of_columns_side_by_side_have_the_bits_of_one_stream(nx, ny, nb):
         for a, b in zip(got, want):
             np.testing.assert_array_equal(a, b)
     r.check_error()
+
+
+@pytest.mark.parametrize("cfg", [RTConfig(nx=3, ny=2, batch=2), RTConfig(nx=9, ny=7), RTConfig(nx=61, ny=40, batch=3),
+                                 RTConfig(nx=250, ny=254), paper_preset(62, batch=3).with_(recon=RECON_BALANCED),
+                                 RTConfig(nx=520, ny=1100)],
+                         ids=["3x2x2", "9x7", "61x40x3", "250x254", "62x62x3-balanced", "520x1100"])
+def test_step_size_correction_by_the_next_launch_matches_the_tiles(cfg):
+    # Members end at different steps; the cell of largest speed lies anywhere,
+    # also in the halo of tiles that wrap onto themselves; 520x1100 has more
+    # tiles than a launch corrects from.  The sum behind mu is grouped by tile:
+    # 1e-11 as above; the policies agree to the bit.
+    from paper_2608_04085_amd import rtcnop
+    uv = states(cfg) * np.linspace(0.1, 1.0, cfg.batch)[:, None, None, None]
+    out = []
+    for mask in (0, rtcnop.FUSED_ADJOINT):
+        r = rtcnop.Context(cfg, max_steps=64, tile="16x15")
+        r.set_columns(mask)
+        r.set_dt_mode("differentiated")
+        T = (12.4 if cfg.cells < 100000 else 3.4) * float(host(r.cfl_dt(r.init_state(uv))).min())
+        for pol in (rtcnop.Policy(CKPT_UNIFORM, 1), rtcnop.Policy(CKPT_UNIFORM, 3),
+                    rtcnop.Policy(CKPT_REVOLVE, pool_bytes=3 * 32 * cfg.cells * cfg.batch)):
+            out.append([host(x) for x in r.grad_u0(uv, T, pol)])
+        r.check_error()
+    for o in out[1:3]:
+        np.testing.assert_array_equal(o[1], out[0][1])
+    for o in out[4:]:
+        np.testing.assert_array_equal(o[1], out[3][1])
+    np.testing.assert_array_equal(out[3][2], out[0][2])
+    assert np.max(np.abs(out[3][1] - out[0][1])) <= 1e-11 * np.max(np.abs(out[0][1]))
