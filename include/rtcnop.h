@@ -271,7 +271,7 @@ int rt_axpy(rt_ctx* ctx, const double* x, const double* alpha, const double* y, 
 /* Kernel variants.  The fused step and adjoint kernels come in tile shapes
  * 16x16, 32x8, 64x4 (256 threads), 16x16, 32x8 (576 threads, one pass per
  * phase), 16x8 (128), 8x8 (64), 16x8 (320, one pass), 8x8 (192, one
- * pass), 32x16 (512), 16x15 and 15x16 (256, every face loop in one pass);
+ * pass), 32x16 (768, adjoint 512), 16x15 and 15x16 (256, every face loop in one pass);
  * ids 0..11 in that order.  Every variant gives bitwise-identical
  * results.  rt_set_tile selects one variant for both kernels;
  * rt_autotune times every variant (and the column kernels) on the state U (device) with `reps`

@@ -128,7 +128,8 @@ struct AdjArgs {
 
 // Tile shapes of the fused step / adjoint kernels: TX x TY cells with 256
 // threads, with 576 threads ("W" variants: one pass per phase), 32 x 16
-// cells with 512 threads (less halo work per cell), or 16 x 15 and 15 x 16
+// cells with 768 threads in the step and 512 in the adjoint (less halo work
+// per cell), or 16 x 15 and 15 x 16
 // cells with 256 threads (every face loop of the adjoint in one pass of the
 // block: 255 and 256 faces of each direction).  All variants produce
 // bitwise-identical results.

@@ -991,7 +991,7 @@ void tile_dims(int tile, int* tx, int* ty, int* nt) {
     case TILE_8x8: a = 8; b = 8; t = 64; break;
     case TILE_16x8W: b = 8; t = 320; break;
     case TILE_8x8W: a = 8; b = 8; t = 192; break;
-    case TILE_32x16: a = 32; b = 16; t = 512; break;
+    case TILE_32x16: a = 32; b = 16; t = 768; break;
     case TILE_16x15: b = 15; break;
     case TILE_15x16: a = 15; break;
     default: break;
@@ -1007,7 +1007,10 @@ void tile_dims(int tile, int* tx, int* ty, int* nt) {
 // where that one has the least halo work.  Measured, us: 8x8 with 192 threads
 // 4.9 (64x128), 5.6 (96x192), 5.9 (128x256), 7.0 (256x256); 16x8 with 320 5.3,
 // 5.5 (96x192, 128x256), 6.4, 7.4 (300x300); 32x8 with 576 6.2 (256x256), 8.3
-// (256x512), 11.8 (384x512); 32x16 8.4 (256x512).
+// (256x512), 11.8 (384x512); 32x16 8.1 (256x512), with 768 threads, which take
+// its 720 primitives and 612 predicted states in one pass each and its 1072
+// faces in two (512 threads: two, two and three, 8.4; 256x512 gradient 8.56 ->
+// 8.33 ms).
 int step_tile(const Params& P, double* us) {
   struct Choice {
     int tile;
@@ -1070,7 +1073,7 @@ hipError_t launch_step(const Params& P, int tile, const StepArgs& a, hipStream_t
     case TILE_8x8: return launch_step_t<8, 8, 64>(P, a, s);
     case TILE_16x8W: return launch_step_t<16, 8, 320>(P, a, s);
     case TILE_8x8W: return launch_step_t<8, 8, 192>(P, a, s);
-    case TILE_32x16: return launch_step_t<32, 16, 512>(P, a, s);
+    case TILE_32x16: return launch_step_t<32, 16, 768>(P, a, s);
     case TILE_16x15: return launch_step_t<16, 15, 256>(P, a, s);
     case TILE_15x16: return launch_step_t<15, 16, 256>(P, a, s);
     default: return launch_step_t<16, 16, 256>(P, a, s);
