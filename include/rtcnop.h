@@ -176,8 +176,9 @@ int rt_ke_ratio(rt_ctx* ctx, const double* U0, const double* UT, double* R);
 int rt_ke_ratio_noalloc(rt_ctx* ctx, const double* U0, const double* UT, double* R);
 
 /* Adjoint of one step: lam = (d Phi_dt / dU)(U)^T lam_next with dt[B]
- * (device) held fixed.  Arrays are states [B][4][ny][nx]; lam must not
- * overlap lam_next. */
+ * (device) held fixed.  Arrays are states [B][4][ny][nx]; lam must not be
+ * lam_next.  It may be U or share memory with U otherwise (the result is then
+ * formed in the workspace first, where the kernel needs that). */
 int rt_step_adjoint(rt_ctx* ctx, const double* U, const double* dt, const double* lam_next, double* lam);
 
 /* R[B] = KE(U(T))/KE(U(0)) for the initial perturbation uv0, and its

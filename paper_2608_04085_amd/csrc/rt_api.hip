@@ -896,20 +896,40 @@ int rt_ke_ratio_noalloc(rt_ctx* c, const double* U0, const double* UT, double* R
   return 0;
 }
 
+namespace {
+// Whether n doubles from a and m doubles from b share memory.
+bool overlap(const double* a, size_t n, const double* b, size_t m) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + m * sizeof(double) && y < x + n * sizeof(double);
+}
+}  // namespace
+
 int rt_step_adjoint(rt_ctx* c, const double* U, const double* dt, const double* lam_next, double* lam) {
   if (int rc = need_ws(c)) return rc;
   if (!U || !dt || !lam_next || !lam || lam == lam_next) return fail(RT_EINVAL, "bad argument");
+  const size_t se = c->state_elems();
+  const int variant = c->adj_variant(false);
+  // The kernels that take one launch write lambda^n while other blocks still
+  // read their halos of U and lambda^{n+1}.  The pair writes it after all of
+  // lambda^{n+1} is read and reads U once more at the cell it writes, so only
+  // a lam shifted against U is in its way.  Where lam shares memory with what
+  // is still to be read, lambda^n is formed in the workspace and copied.
+  const bool one_launch = variant >= rtk::TILE_COUNT;
+  const bool over_U = overlap(lam, se, U, se);
+  const bool staged = one_launch ? over_U || overlap(lam, se, lam_next, se) || overlap(lam, se, dt, (size_t)c->P.nb)
+                                 : over_U && lam != U;
   rtk::AdjArgs a{};
   a.U = U;
   a.lam_next = lam_next;
-  a.lam = lam;
+  a.lam = staged ? c->Z2 : lam;  // the folded sweep's, free here
   a.Z = c->Z;
   a.codes = c->codes;
   a.dt = dt;
   a.dt_stride = 1;
   a.dt_index = 0;
   a.flags = c->flags;
-  RT_HIP(rtk::launch_adjoint(c->P, c->adj_variant(false), a, c->stream));
+  RT_HIP(rtk::launch_adjoint(c->P, variant, a, c->stream));
+  if (staged) RT_HIP(rtk::launch_copy(c->Z2, lam, se, c->stream));
   return 0;
 }
 

@@ -394,6 +394,7 @@ class Context:
         return self.ke_ratio(U0, UT)
 
     def step_adjoint(self, U, dt, lam_next, out: torch.Tensor | None = None) -> torch.Tensor:
+        """lambda^n of one step; out may be U (which it then replaces), not lam_next."""
         self._sync_stream()
         U = self.as_dev(U)
         lam_next = self.as_dev(lam_next)
