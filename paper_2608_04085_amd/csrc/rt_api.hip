@@ -79,7 +79,7 @@ struct rt_ctx {
   int32_t *codes = nullptr, *codes2 = nullptr;
   double* partial = nullptr;
   double* rowmean = nullptr;  // [B][ny] horizontal density means
-  uint64_t* acc = nullptr;  // [3][B][kAccRow] signal-speed slots of the march, then [B][kAccRow] for rt_step
+  uint64_t* acc = nullptr;  // [3][B][kAccRow] signal-speed slots of the march
   Ctl* ctl = nullptr;       // [2][B] march control, double buffered
   long last_launch = 0;     // launches of the last march (final ctl in ctl[last_launch & 1])
   // Graph of a chunk of kGraphChunk march steps (captured once per set of
@@ -154,7 +154,7 @@ Layout layout(const rt_ctx* c, int32_t max_steps) {
     return o;
   };
   const size_t se = c->state_elems() * sizeof(double);
-  int maxblk = c->red_blocks;
+  int maxblk = std::max(c->red_blocks, rtk::step_parts(c->P, rtk::TILE_COLUMNS));
   for (int t = 0; t < rtk::TILE_COUNT; ++t) maxblk = std::max(maxblk, rtk::step_blocks(c->P, t));
   L.S0 = take(se);
   L.S1 = take(se);
@@ -166,7 +166,7 @@ Layout layout(const rt_ctx* c, int32_t max_steps) {
   L.codes2 = take(c->cells() * c->P.nb * sizeof(int32_t));
   L.partial = take((size_t)maxblk * c->P.nb * sizeof(double));
   L.rowmean = take((size_t)c->P.ny * c->P.nb * sizeof(double));
-  L.acc = take((size_t)4 * rtk::kAccRow * c->P.nb * sizeof(uint64_t));
+  L.acc = take((size_t)3 * rtk::kAccRow * c->P.nb * sizeof(uint64_t));
   L.ctl = take((size_t)2 * c->P.nb * sizeof(Ctl));
   L.flags = take(sizeof(Flags));
   L.dt_log = take((size_t)c->P.nb * std::max<int32_t>(max_steps, 1) * sizeof(double));
@@ -757,7 +757,7 @@ int rt_set_workspace(rt_ctx* c, void* dev, size_t bytes, int32_t max_steps) {
   c->dtd_stride = L.dtd_stride;
   c->bg_p = reinterpret_cast<double*>(w + L.bg_p);
   if (c->P.recon == RT_RECON_BALANCED) RT_HIP(rtk::launch_background_rows(c->P, c->bg_p, c->stream));
-  RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->acc), 0, 2 * (size_t)4 * rtk::kAccRow * c->P.nb,
+  RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->acc), 0, 2 * (size_t)3 * rtk::kAccRow * c->P.nb,
                               c->stream));
   RT_HIP(rtk::launch_fill_i32(reinterpret_cast<int32_t*>(c->flags), 0, sizeof(Flags) / 4, c->stream));
   return 0;
@@ -791,12 +791,15 @@ int rt_step(rt_ctx* c, const double* U_in, double* U_out, const double* dt, doub
   a.dt_stride = 1;
   a.dt_index = 0;
   a.flags = c->flags;
-  // the slots after the march's rows: zero here, since the workspace was set
-  // or since the kernel that read them last
-  uint64_t* acc_out = c->acc + 3 * (size_t)rtk::kAccRow * c->P.nb;
-  if (dt_next) a.acc_out = acc_out;
-  RT_HIP(rtk::launch_step(c->P, c->step_variant(), a, c->stream));
-  if (dt_next) RT_HIP(rtk::launch_cfl_from_slots(c->P, acc_out, dt_next, c->stream));
+  // every speed that forms dt_next is written by this call's launch: nothing
+  // in the workspace has to be as an earlier call left it
+  const int variant = c->step_variant(), parts = rtk::step_parts(c->P, variant);
+  if (dt_next) {
+    a.speeds = c->partial;
+    a.speeds_stride = parts;
+  }
+  RT_HIP(rtk::launch_step(c->P, variant, a, c->stream));
+  if (dt_next) RT_HIP(rtk::launch_cfl_from_parts(c->P, c->partial, parts, dt_next, c->stream));
   return 0;
 }
 

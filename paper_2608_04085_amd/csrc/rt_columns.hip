@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
 
   const double hx = 0.5 * dt * P.inv_dx, hy = 0.5 * dt * P.inv_dy, hg = 0.5 * dt * P.g_y;
   const double ax = dt * P.inv_dx, ay = dt * P.inv_dy, dtg = dt * P.g_y;
-  const bool need_speed = a.ctl != nullptr || a.acc_out != nullptr;
+  const bool need_speed = a.ctl != nullptr || a.speeds != nullptr;
   double smax = 0.0;
 
   // Carried from row j - 1 to row j: its upper face state (r, n = v, t = u,
@@ -305,9 +305,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   if (!need_speed) return;
   const double bm = wave_max(smax);
   if (a.ctl == nullptr) {
-    if (lane == 0)
-      atomicMax((unsigned long long*)(a.acc_out + (size_t)b * kAccRow + (t % kAccSlots) * kAccStride),
-                (unsigned long long)__double_as_longlong(bm));
+    if (lane == 0) a.speeds[(size_t)b * a.speeds_stride + t] = bm;
     return;
   }
   const int L = a.launch;
@@ -656,7 +654,13 @@ double step_cols_us(const Params& P) {
   return us - 0.6;
 }
 
+int step_cols_parts(const Params& P) {
+  const int strips = step_strips(P);
+  return strips * row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, false);
+}
+
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
+  if (a.speeds && a.beside) return hipErrorInvalidValue;  // (other segments than step_cols_parts counts)
   const int strips = step_strips(P);
   const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, a.beside);
   const long waves = (long)strips * segs * P.nb;

@@ -559,7 +559,7 @@ hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s) {
 bool adj_fused_pairs(const Params& P) { return P.nb <= 32767 && pick_shape(P, P.nb, nullptr) <= 2; }
 
 hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s) {
-  if (a.fold.Z != nullptr || st.ctl != nullptr || st.acc_out != nullptr) return hipErrorInvalidValue;
+  if (a.fold.Z != nullptr || st.ctl != nullptr || st.speeds != nullptr) return hipErrorInvalidValue;
   switch (pick_shape(P, P.nb, nullptr)) {
     case 0: return launch_pair_t<8, 8, 256>(P, a, st, s);
     case 1: return launch_pair_t<16, 8, 320>(P, a, st, s);

@@ -65,13 +65,15 @@ struct StepArgs {
   double* pool;
   int32_t snap_interval, snap_slots;
   // Given-dt mode: dt = dt[b * dt_stride + dt_index]; members with
-  // dt_index >= nsteps_limit[b] are skipped.  acc_out (may be null), slots
-  // [B][kAccSlots * kAccStride] as a row of acc, receives the largest signal
-  // speed of U^{n+1} (bit pattern, must start at 0).
+  // dt_index >= nsteps_limit[b] are skipped.  speeds (may be null)
+  // [B][speeds_stride] receives the largest signal speed of U^{n+1} over each
+  // of the step_parts(P, tile) parts of a member (tiles, or strips' segments),
+  // all of them written by the launch.
   const double* dt;
   int32_t dt_stride, dt_index;
   const int32_t* nsteps_limit;
-  uint64_t* acc_out;
+  double* speeds;
+  int32_t speeds_stride;
   Flags* flags;
   bool beside;  // another launch of the kind runs at the same time (column kernels leave it its wavefront slots)
 };
@@ -153,6 +155,8 @@ enum TileId {
 };
 void tile_dims(int tile, int* tx, int* ty, int* nt);
 int step_blocks(const Params& P, int tile);  // blocks per member
+int step_parts(const Params& P, int tile);   // StepArgs::speeds per member, for TILE_COLUMNS too
+int step_cols_parts(const Params& P);
 // The step's tile variant for small grids, and the expected times in us of its
 // launch and of the column kernel's (given dt and march step averaged).
 int step_tile(const Params& P, double* us);
@@ -175,7 +179,7 @@ hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s);
 // The two in one launch on tiles with a halo of three cells (launch_adjoint
 // with TILE_FUSED): no folded gather, Z and codes unused.
 hipError_t launch_adj_fused(const Params& P, const AdjArgs& a, hipStream_t s);
-// The same and a step at a given dt (st: no ctl, no acc_out) in one launch, for
+// The same and a step at a given dt (st: no ctl, no speeds) in one launch, for
 // grids small enough that both fit beside each other (adj_fused_pairs).
 bool adj_fused_pairs(const Params& P);
 hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s);
@@ -206,7 +210,8 @@ hipError_t launch_march_begin(const Params& P, const double* maxspeed, double T,
 hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report,
                          hipStream_t s);
 hipError_t launch_cfl_from_speed(const Params& P, const double* maxspeed, double* dt, hipStream_t s);
-hipError_t launch_cfl_from_slots(const Params& P, uint64_t* acc, double* dt, hipStream_t s);  // and clears the slots
+// From StepArgs::speeds with speeds_stride = count.
+hipError_t launch_cfl_from_parts(const Params& P, const double* speeds, int count, double* dt, hipStream_t s);
 hipError_t launch_copy_final(const Params& P, const Ctl* ctl, const double* A, const double* Bbuf, double* U,
                              double* t_out, int32_t* nsteps_out, const double* log_src, int32_t log_src_cap,
                              double* log_dst, int32_t log_dst_cap, hipStream_t s);

@@ -747,16 +747,13 @@ __global__ void k_march_begin(Params P, const double* ms, double T, Ctl* ctl, ui
           (r == 0 && k == 0) ? (uint64_t)__double_as_longlong(ms[b]) : 0ull;
 }
 
-// CFL step from a member's signal-speed slots, which it clears for the next
-// step; one wavefront per member.
-__global__ __launch_bounds__(64) void k_cfl_from_slots(Params P, uint64_t* acc, double* dt) {
-  uint64_t* row = acc + (size_t)blockIdx.x * kAccRow;
+// CFL step from the speeds of a member's parts; one block per member.
+__global__ __launch_bounds__(256) void k_cfl_from_parts(Params P, const double* speeds, int count, double* dt) {
+  __shared__ double red[4];
+  const double* v = speeds + (size_t)blockIdx.x * count;
   double ms = 0.0;
-  if (threadIdx.x < kAccSlots) {
-    ms = __longlong_as_double((long long)row[threadIdx.x * kAccStride]);
-    row[threadIdx.x * kAccStride] = 0ull;
-  }
-  ms = wave_max(ms);
+  for (int k = threadIdx.x; k < count; k += 256) ms = fmax(ms, v[k]);
+  ms = block_max<256>(ms, red);
   if (threadIdx.x == 0) dt[blockIdx.x] = P.cfl / ms;
 }
 
@@ -1038,6 +1035,8 @@ int step_blocks(const Params& P, int tile) {
   return ((P.nx + tx - 1) / tx) * ((P.ny + ty - 1) / ty);
 }
 
+int step_parts(const Params& P, int tile) { return tile == TILE_COLUMNS ? step_cols_parts(P) : step_blocks(P, tile); }
+
 #ifndef RT_ALIAS_MODE
 #define RT_ALIAS_MODE 2
 #endif
@@ -1191,8 +1190,8 @@ hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, co
   return hipGetLastError();
 }
 
-hipError_t launch_cfl_from_slots(const Params& P, uint64_t* acc, double* dt, hipStream_t s) {
-  hipLaunchKernelGGL(k_cfl_from_slots, dim3(P.nb), dim3(64), 0, s, P, acc, dt);
+hipError_t launch_cfl_from_parts(const Params& P, const double* speeds, int count, double* dt, hipStream_t s) {
+  hipLaunchKernelGGL(k_cfl_from_parts, dim3(P.nb), dim3(256), 0, s, P, speeds, count, dt);
   return hipGetLastError();
 }
 

@@ -399,7 +399,7 @@ __device__ __forceinline__ void step_tile_body(const Params& P, const StepArgs& 
   __syncthreads();
 
   // phase D: update with the gravity source
-  const bool need_speed = a.ctl != nullptr || a.acc_out != nullptr;
+  const bool need_speed = a.ctl != nullptr || a.speeds != nullptr;
   double smax = 0.0;
   if (own) {
     const double ax = dt * P.inv_dx, ay = dt * P.inv_dy;
@@ -439,15 +439,12 @@ __device__ __forceinline__ void step_tile_body(const Params& P, const StepArgs& 
   if (bad & 1) atomicOr(&a.flags->err_unphys, 1);
   if (!need_speed) return;
 
-  // epilogue: fold the block's largest signal speed of U^{n+1} into the
-  // member's accumulator (non-negative doubles order like their bits)
+  // epilogue: the block's largest signal speed of U^{n+1}; in the march
+  // folded into the member's accumulator (non-negative doubles order like
+  // their bits)
   const double bm = block_max<NT>(smax, sRed);
   if (a.ctl == nullptr) {
-    if (tid == 0) {
-      const int slot = (int)((blockIdx.x + (size_t)gridDim.x * blockIdx.y) % kAccSlots);
-      atomicMax((unsigned long long*)(a.acc_out + (size_t)b * kAccRow + slot * kAccStride),
-                (unsigned long long)__double_as_longlong(bm));
-    }
+    if (tid == 0) a.speeds[(size_t)b * a.speeds_stride + blockIdx.x + (size_t)gridDim.x * blockIdx.y] = bm;
     return;
   }
   const int L = a.launch;
