@@ -11,6 +11,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/rtcnop.h"
@@ -43,6 +44,53 @@ int fail(int code, const char* fmt, ...) {
   } while (0)
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Pinned host memory for the contexts' reports.  hipHostFree waits for every
+// stream of the device (a context destroyed beside 0.3 s of other work took
+// 0.3 s), so a destroyed context leaves its block to the next one: at most
+// kMost bytes of whole pages by powers of two; what exceeds that is freed.  No
+// launch that writes a block is pending when its context is destroyed (each
+// call that launches one waits for it).
+class ReportBlocks {
+ public:
+  hipError_t take(size_t bytes, void** p, size_t* size) {
+    size_t n = 4096;
+    while (n < bytes) n *= 2;
+    *size = n;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      for (auto it = free_.begin(); it != free_.end(); ++it) {
+        if (it->second != n) continue;
+        *p = it->first;
+        held_ -= n;
+        free_.erase(it);
+        return hipSuccess;
+      }
+    }
+    return hipHostMalloc(p, n, hipHostMallocDefault);  // mapped on every device
+  }
+  void give(void* p, size_t size) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (held_ + size <= kMost) {
+        free_.emplace_back(p, size);
+        held_ += size;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  static constexpr size_t kMost = 4u << 20;
+  std::mutex mu_;
+  std::vector<std::pair<void*, size_t>> free_;
+  size_t held_ = 0;
+};
+ReportBlocks& report_blocks() {
+  static ReportBlocks* b = new ReportBlocks;  // outlives contexts destroyed at the process's end
+  return *b;
+}
 
 }  // namespace
 
@@ -122,12 +170,13 @@ struct rt_ctx {
       if (group_stream[k]) (void)hipStreamDestroy(group_stream[k]);
     }
     if (aux_stream) (void)hipStreamDestroy(aux_stream);
-    if (report) (void)hipHostFree(report);
+    if (report) report_blocks().give(report, report_size);
   }
-  // Pinned host memory that kernels report into (allocated with the first
-  // workspace), so that a march's host decisions cost one stream
-  // synchronisation and no copies.
+  // Pinned host memory that kernels report into (taken by the first march), so
+  // that a march's host decisions cost one stream synchronisation and no
+  // copies.
   rtk::Report* report = nullptr;
+  size_t report_size = 0;
   Flags* flags = nullptr;
   double* dt_log = nullptr;
   int32_t* nsteps = nullptr;
@@ -281,10 +330,19 @@ int ensure_chunk_graph(rt_ctx* c, double* pool, int interval, int slots) {
   return 0;
 }
 
+int need_report(rt_ctx* c) {
+  if (c->report) return 0;
+  void* p = nullptr;
+  RT_HIP(report_blocks().take(sizeof(rtk::Report) + (size_t)c->P.nb * sizeof(rtk::Report::Member), &p, &c->report_size));
+  c->report = static_cast<rtk::Report*>(p);
+  return 0;
+}
+
 // Sets up the march of all members from S0 to T and gives the number of
 // steps the largest initial signal speed suggests.  Synchronises.
 int march_start(rt_ctx* c, double T, long* nest) {
   Params& P = c->P;
+  if (int rc = need_report(c)) return rc;
   RT_HIP(rtk::launch_reduce(P, 0, c->S0, nullptr, c->partial, c->red_blocks, c->sc(0), c->stream));
   RT_HIP(rtk::launch_march_begin(P, c->sc(0), T, c->ctl, c->acc, c->flags, c->report, c->stream));
   RT_HIP(hipStreamSynchronize(c->stream));
@@ -559,6 +617,7 @@ namespace {
 // state U serves as every step's state; the workspace buffers are scratch.
 int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int reps, hipEvent_t e0, hipEvent_t e1,
                  float out[4]) {
+  if (int rc = need_report(c)) return rc;
   hipStream_t s = c->stream;
   const size_t se = c->state_elems();
   const Params& P = c->P;
@@ -624,7 +683,9 @@ int time_kernels(rt_ctx* c, const double* U, int step_tile, int adj_tile, int re
         &out[2]);
   if (e == hipSuccess) e = timed([&](int) { return rtk::launch_adjoint(P, adj_tile, j, s); }, &out[3]);
   if (!can_fold) out[2] = out[3];
-  return e == hipSuccess ? 0 : fail(RT_EHIP, "kernel timing: %s", hipGetErrorString(e));
+  if (e == hipSuccess) return 0;
+  (void)hipStreamSynchronize(s);
+  return fail(RT_EHIP, "kernel timing: %s", hipGetErrorString(e));
 }
 
 }  // namespace
@@ -720,11 +781,6 @@ int rt_set_workspace(rt_ctx* c, void* dev, size_t bytes, int32_t max_steps) {
   if (reinterpret_cast<uintptr_t>(dev) & 255) return fail(RT_EINVAL, "workspace must be 256-byte aligned");
   const Layout L = layout(c, max_steps);
   if (bytes < L.total) return fail(RT_ENOMEM, "workspace of %zu bytes < %zu needed", bytes, L.total);
-  if (!c->report) {
-    void* p = nullptr;
-    RT_HIP(hipHostMalloc(&p, sizeof(rtk::Report) + (size_t)c->P.nb * sizeof(rtk::Report::Member), hipHostMallocDefault));
-    c->report = static_cast<rtk::Report*>(p);
-  }
   char* w = static_cast<char*>(dev);
   if (c->chunk_exec) {
     RT_HIP(hipGraphExecDestroy(c->chunk_exec));
