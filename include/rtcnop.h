@@ -294,8 +294,8 @@ int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
  * steps: to the rounding of mu's sum).  The default: RT_FUSED_ADJOINT, and
  * the column kernels where they are expected to be faster (the step's always
  * beyond three 32x8 blocks per CU of cells in all).  rt_set_tile and
- * rt_set_tiles set the mask to 0, rt_set_fold(ctx, 1) clears both adjoint
- * bits, rt_autotune sets it to what it measures as fastest. */
+ * rt_set_tiles set the mask to 0, rt_set_fold may clear both adjoint bits,
+ * rt_autotune sets it to what it measures as fastest. */
 enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2, RT_FUSED_ADJOINT = 4 };
 int rt_set_columns(rt_ctx* ctx, int32_t mask);
 int rt_get_columns(const rt_ctx* ctx, int32_t* mask);
@@ -322,7 +322,12 @@ int rt_autotune(rt_ctx* ctx, const double* U, int32_t reps, int32_t* step_tile, 
  * per adjoint step, which also completes the previous step's limiter gather
  * (on = 1), or the two kernels of rt_step_adjoint per step (on = 0); results
  * are identical.  Folding needs the adjoint's tile kernels (see
- * rt_set_columns).  rt_autotune folds when the folded step is more than 10%
+ * rt_set_columns): rt_get_fold gives the setting, which takes effect where
+ * they run.  rt_set_fold(ctx, 1) makes them run if the caller has chosen
+ * kernels (rt_set_tile(s), rt_set_columns, rt_autotune) or if the setting was
+ * 0 by default; rt_set_fold(ctx, 0) then brings the default kernels back if
+ * none were chosen.  Setting what rt_get_fold gave never changes the kernels
+ * of a context whose kernels were not chosen.  rt_autotune folds when the folded step is more than 10%
  * faster than any other on their own (the folded kernel shares the CUs less
  * well with the concurrent re-computation); before it, grids of fewer than
  * 2^16 cells in all are set to fold.  The tile variants before it, where

@@ -104,12 +104,19 @@ constexpr int kSplitGroups = 2;
 // 14.1 / 15.0, 1024x1024 (2048) 32.0 / 38.8.
 constexpr int kDeferTiles = 512;
 
+// The kernels that run in place of the adjoint's tile kernels.
+constexpr int kAdjointMask = RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT;
+
 struct rt_ctx {
   Params P;
   hipStream_t stream;
   int tile;      // tile variant of the step kernel
   int tile_adj;  // tile variant of the adjoint kernel
   int columns = 0;  // RT_COLUMNS_* kernels that run in place of the tile kernels (same results)
+  // rt_create's choice of the adjoint's kernels and of the fold, which
+  // rt_set_fold returns to while the caller has chosen none (chosen)
+  int default_adjoint = 0;
+  bool default_fold = false, chosen = false;
   int step_variant() const { return (columns & RT_COLUMNS_STEP) ? (int)rtk::TILE_COLUMNS : tile; }
   // the adjoint step outside the folded sweep; dtd: with differentiated steps
   int adj_variant(bool dtd) const {
@@ -117,7 +124,7 @@ struct rt_ctx {
     return (columns & RT_FUSED_ADJOINT) ? (int)rtk::TILE_FUSED : tile_adj;
   }
   // the reverse sweep of uniform checkpoints folds the gather
-  bool folds() const { return fold && !(columns & (RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT)); }
+  bool folds() const { return fold && !(columns & kAdjointMask); }
   int red_blocks;
   // workspace
   char* ws = nullptr;
@@ -480,9 +487,10 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   const int small_tile = rtk::step_tile(P, &tile_us);
   c->tile = one_round ? small_tile : rtk::TILE_16x15;
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
-  c->fold = tiny;
+  c->fold = c->default_fold = tiny;
   c->columns = RT_FUSED_ADJOINT | (one_round && tile_us <= rtk::step_cols_us(P) ? 0 : (int)RT_COLUMNS_STEP) |
                (rtk::adj_cols_us(P) < rtk::adj_fused_us(P) ? (int)RT_COLUMNS_ADJOINT : 0);
+  c->default_adjoint = c->columns & kAdjointMask;
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));
   *out = c;
@@ -506,6 +514,7 @@ int rt_set_tile(rt_ctx* c, int32_t tile) {
   c->tile = tile;
   c->tile_adj = tile;
   c->columns = 0;
+  c->chosen = true;
   return 0;
 }
 
@@ -513,6 +522,7 @@ int rt_set_columns(rt_ctx* c, int32_t mask) {
   if (!c) return fail(RT_EINVAL, "null context");
   if (mask & ~(RT_COLUMNS_STEP | RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT)) return fail(RT_EINVAL, "unknown column kernels in mask %d", mask);
   c->columns = mask;
+  c->chosen = true;
   return 0;
 }
 
@@ -528,6 +538,7 @@ int rt_set_tiles(rt_ctx* c, int32_t step_tile, int32_t adj_tile) {
   c->tile = step_tile;
   c->tile_adj = adj_tile;
   c->columns = 0;
+  c->chosen = true;
   return 0;
 }
 
@@ -553,7 +564,13 @@ int rt_set_overlap(rt_ctx* c, int32_t on) {
 int rt_set_fold(rt_ctx* c, int32_t on) {
   if (!c) return fail(RT_EINVAL, "null context");
   c->fold = on != 0;
-  if (on) c->columns &= ~(RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT);
+  // Folding takes the adjoint's tile kernels.  While the kernels are the
+  // context's own, that is undone by the opposite call, and the default setting
+  // changes nothing: f = get, set(!f), set(f) ends where it began.
+  if (!c->chosen)
+    c->columns = (c->columns & ~kAdjointMask) | (c->fold && !c->default_fold ? 0 : c->default_adjoint);
+  else if (on)
+    c->columns &= ~kAdjointMask;
   return 0;
 }
 
@@ -738,6 +755,7 @@ int rt_autotune(rt_ctx* c, const double* U, int32_t reps, int32_t* step_tile, in
   c->tile = bs;
   c->tile_adj = ba;
   c->fold = fold;
+  c->chosen = true;
   c->columns = cols_s < best_s ? RT_COLUMNS_STEP : 0;
   if (!fold && fused_a < best_u) c->columns |= RT_FUSED_ADJOINT;
   if (!fold && cols_a < std::min(best_u, fused_a)) c->columns |= RT_COLUMNS_ADJOINT;

@@ -286,7 +286,8 @@ class Context:
 
     @property
     def fold(self) -> bool:
-        """Reverse sweep with the limiter gather folded into the next adjoint kernel."""
+        """The setting to fold the limiter gather into the next adjoint kernel, for the adjoint's tile kernels
+        (`kernels` says whether they run)."""
         v = ctypes.c_int32()
         _check(load().rt_get_fold(self._h, ctypes.byref(v)), "rt_get_fold")
         return bool(v.value)
@@ -311,7 +312,8 @@ class Context:
         _check(load().rt_set_overlap(self._h, 1 if on else 0), "rt_set_overlap")
 
     def autotune(self, U, reps: int = 20) -> str:
-        """Time every kernel variant on U and keep the fastest (bitwise-identical results)."""
+        """Time every kernel variant on U and keep the fastest (bitwise-identical results).  Returns the fastest
+        tile variants; `kernels` says what runs, the column and fused kernels where they won."""
         self._sync_stream()
         U = self.as_dev(U)
         a, b = ctypes.c_int32(), ctypes.c_int32()
