@@ -291,9 +291,9 @@ int rt_set_tiles(rt_ctx* ctx, int32_t step_tile, int32_t adj_tile);
  * per step and leave no intermediates in memory; differentiated time steps
  * run the fused one (or the tile kernels) also where RT_COLUMNS_ADJOINT is
  * set.  Results are those of every tile variant to the bit (differentiated
- * steps: to the rounding of mu's sum).  The default: RT_FUSED_ADJOINT, and
- * the column kernels where they are expected to be faster (the step's always
- * beyond three 32x8 blocks per CU of cells in all).  rt_set_tile and
+ * steps: to the rounding of mu's sum).  The default is what is expected to be
+ * fastest: RT_FUSED_ADJOINT, but for some grids of fewer than 32 columns, and
+ * the column kernels where they are faster still.  rt_set_tile and
  * rt_set_tiles set the mask to 0, rt_set_fold may clear both adjoint bits,
  * rt_autotune sets it to what it measures as fastest. */
 enum { RT_COLUMNS_STEP = 1, RT_COLUMNS_ADJOINT = 2, RT_FUSED_ADJOINT = 4 };

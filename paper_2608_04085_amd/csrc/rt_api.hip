@@ -463,17 +463,18 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   c->stream = reinterpret_cast<hipStream_t>(stream);
   // Defaults from measurements on MI355X.  Each kernel takes the form whose
   // launch is expected to be shortest (the rules and their times stand with
-  // the kernels).  The step runs single-pass tiles on the smallest grids and
-  // the column kernel, which has no barriers and almost no halo work, where
-  // that is faster, beyond one round of three 32x8 blocks per CU always: given
-  // dt / march step in us, columns against tiles, 8.4 / 10.2 against 7.7 / 9.1
-  // at 256x512, 9.7 / 11.3 against 10.3 / 12.0 at 384x512, 18 / 20 against 22 /
-  // 25 at 512x1024, 87 / 95 against 155 / 172 at 8 x 512x1024.  The adjoint
-  // never runs the tile pair by default: in one launch it is faster at every
-  // size, fused on tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6
-  // against 18.2, 512x512 22.0 against 28.0) or, where its expected time is
-  // less, by columns (512x768 32.0 against 32.7 fused, 512x1024 40 against 44,
-  // 8 x 512x1024 181 against 314 and the pair's 398).  The tile variants that
+  // the kernels).  The step runs tiles, single-pass ones up to one round of
+  // three 32x8 blocks per CU and 16x15 beyond, or the column kernel, which has
+  // no barriers and almost no halo work but needs columns to fill its lanes:
+  // given dt / march step in us, columns against tiles, 8.4 / 10.2 against 7.7 /
+  // 9.1 at 256x512, 9.7 / 11.3 against 10.3 / 12.0 at 384x512, 18 / 20 against
+  // 22 / 25 at 512x1024, 87 / 95 against 155 / 172 at 8 x 512x1024, but 70 / 76
+  // against 42 / 47 at 1024 x 16x64.  The adjoint runs in one launch, fused on
+  // tiles (64x128 6.5 against 7.4 us folded, 256x512 11.6 against 18.2, 512x512
+  // 22.0 against 28.0) or by columns (512x768 32.0 against 32.7 fused, 512x1024
+  // 40 against 44, 8 x 512x1024 181 against 314 and the pair's 398), except on
+  // grids of a few columns, where the pair can be faster (39250 x 3x10 449
+  // against 633 fused and 888 by columns).  The tile variants that
   // rt_get_tiles names for the adjoint, and for the step beyond one round, are
   // the fastest of the tile kernels; rt_autotune measures instead.
   const size_t all_cells = (size_t)P.nx * P.ny * P.nb;
@@ -485,11 +486,14 @@ int rt_create(const rt_grid* grid, const rt_phys* phys, void* stream, rt_ctx** o
   const bool one_round = all_cells <= (size_t)3 * cus * 256;
   double tile_us = 0.0;
   const int small_tile = rtk::step_tile(P, &tile_us);
+  if (!one_round) tile_us = rtk::step_16x15_us(P);
   c->tile = one_round ? small_tile : rtk::TILE_16x15;
   c->tile_adj = tiny ? rtk::TILE_8x8W : (one_round ? rtk::TILE_32x8 : rtk::TILE_16x15);
   c->fold = c->default_fold = tiny;
-  c->columns = RT_FUSED_ADJOINT | (one_round && tile_us <= rtk::step_cols_us(P) ? 0 : (int)RT_COLUMNS_STEP) |
-               (rtk::adj_cols_us(P) < rtk::adj_fused_us(P) ? (int)RT_COLUMNS_ADJOINT : 0);
+  c->columns = tile_us <= rtk::step_cols_us(P) ? 0 : (int)RT_COLUMNS_STEP;
+  const double fused_us = rtk::adj_fused_us(P), cols_us = rtk::adj_cols_us(P);
+  if (rtk::adj_pair_us(P, c->tile_adj) >= std::min(fused_us, cols_us))
+    c->columns |= RT_FUSED_ADJOINT | (cols_us < fused_us ? (int)RT_COLUMNS_ADJOINT : 0);
   c->default_adjoint = c->columns & kAdjointMask;
   const size_t n = c->cells();
   c->red_blocks = (int)std::min<size_t>(256, std::max<size_t>(1, n / 2048));

@@ -615,16 +615,24 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_adj_cols(Params P, AdjArg
 // at the kernel's registers, the k with the least of c_k (rows per segment +
 // over).  That is the measured time of a launch in us less a constant 3: a
 // row costs c_k with k wavefronts on a SIMD, and a segment `over` rows' worth
-// below and above it.  A launch beside another one (beside) takes one
-// wavefront per SIMD and leaves the other its own.
+// below and above it (a whole column kOverWhole).  Strips of many members may
+// be more than fit: each further wavefront of a SIMD then adds `full` per row.
+// That many are by the number of strips, so narrow grids get there with the
+// lanes beyond their width idle: 5x248 x 1095 members, one segment each, step
+// 484 us and adjoint 954 where 16x15 tiles take 155 and 258.  A launch beside
+// another one (beside) takes one wavefront per SIMD and leaves the other its
+// own.
 constexpr int kSimds = 1024;
+constexpr double kOverWhole = 1.2;
 template <int K>
-int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, bool beside, double* us = nullptr) {
+int row_segments(int ny, int strips, int nb, const double (&c)[K], double full, double over, bool beside,
+                 double* us = nullptr) {
   int best = 1;
   double cost = 1e300;
   for (int k = 1; k <= (beside ? 1 : K); ++k) {
     const int segs = std::min(ny, std::max(1, (int)((long)k * kSimds / ((long)strips * nb))));
-    const double t = c[k - 1] * ((ny + segs - 1) / segs + over);
+    const long w = ((long)strips * segs * nb + kSimds - 1) / kSimds;  // wavefronts per SIMD
+    const double t = (w <= K ? c[w - 1] : full * (double)w) * ((ny + segs - 1) / segs + (segs > 1 ? over : kOverWhole));
     if (t < cost) {
       cost = t;
       best = segs;
@@ -635,11 +643,13 @@ int row_segments(int ny, int strips, int nb, const double (&c)[K], double over, 
 }
 // Step, noisy states, launch included, with one, two and three wavefronts per
 // SIMD: 512x1024 19.9, 18.7, 18.6; x 4 members 58.8, 51.6, 52.4; x 8 106, 93.0,
-// 91.3; 64 x 128x256 76.2, 67.8, 62.9; 8 x 1024x2048 382, 348, 345.
-constexpr double kStepRow[3] = {1.23, 2.12, 3.03}, kStepOver = 2.3;
+// 91.3; 64 x 128x256 76.2, 67.8, 62.9; 8 x 1024x2048 382, 348, 345.  Beyond: 3x10
+// x 39250 402, 5x4 x 28130 137, 3x158 x 5817 878.
+constexpr double kStepRow[3] = {1.23, 2.12, 3.03}, kStepFull = 0.92, kStepOver = 2.3;
 // Adjoint, the same with one and two: 512x512 25.9, 29.1; 512x1024 39.6, 38.4;
-// x 4 118, 99.8; x 8 224, 189; 64 x 128x256 163, 135.
-constexpr double kAdjRow[2] = {2.9, 4.6}, kAdjOver = 2.7;
+// x 4 118, 99.8; x 8 224, 189; 64 x 128x256 163, 135.  Beyond: 3x10 x 39250 888,
+// 5x4 x 28130 299, 3x158 x 5817 1902.
+constexpr double kAdjRow[2] = {2.9, 4.6}, kAdjFull = 2.0, kAdjOver = 2.7;
 
 int step_strips(const Params& P) { return row_is_wavefront(P) ? 1 : (P.nx + kStepOwn - 1) / kStepOwn; }
 int adj_strips(const Params& P) { return row_is_wavefront(P) ? 1 : (P.nx + kAdjOwn - 1) / kAdjOwn; }
@@ -650,19 +660,19 @@ double step_cols_us(const Params& P) {
   // a little less than the fit's constant below a few rows: 300x300 7.6,
   // 256x512 9.0, 384x512 10.5
   double us;
-  (void)row_segments(P.ny, step_strips(P), P.nb, kStepRow, kStepOver, false, &us);
+  (void)row_segments(P.ny, step_strips(P), P.nb, kStepRow, kStepFull, kStepOver, false, &us);
   return us - 0.6;
 }
 
 int step_cols_parts(const Params& P) {
   const int strips = step_strips(P);
-  return strips * row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, false);
+  return strips * row_segments(P.ny, strips, P.nb, kStepRow, kStepFull, kStepOver, false);
 }
 
 hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
   if (a.speeds && a.beside) return hipErrorInvalidValue;  // (other segments than step_cols_parts counts)
   const int strips = step_strips(P);
-  const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepOver, a.beside);
+  const int segs = row_segments(P.ny, strips, P.nb, kStepRow, kStepFull, kStepOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
   const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));
@@ -677,14 +687,14 @@ hipError_t launch_step_cols(const Params& P, const StepArgs& a, hipStream_t s) {
 
 double adj_cols_us(const Params& P) {
   double us;
-  (void)row_segments(P.ny, adj_strips(P), P.nb, kAdjRow, kAdjOver, false, &us);
+  (void)row_segments(P.ny, adj_strips(P), P.nb, kAdjRow, kAdjFull, kAdjOver, false, &us);
   return us;
 }
 
 hipError_t launch_adj_cols(const Params& P, const AdjArgs& a, hipStream_t s) {
   if (a.fold.Z != nullptr || a.dtd.mu != nullptr) return hipErrorInvalidValue;
   const int strips = adj_strips(P);
-  const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjOver, a.beside);
+  const int segs = row_segments(P.ny, strips, P.nb, kAdjRow, kAdjFull, kAdjOver, a.beside);
   const long waves = (long)strips * segs * P.nb;
   const int paced = a.beside || waves > kSimds;
   const dim3 grid((unsigned)((waves + kColWaves - 1) / kColWaves));

@@ -160,6 +160,7 @@ int step_cols_parts(const Params& P);
 // The step's tile variant for small grids, and the expected times in us of its
 // launch and of the column kernel's (given dt and march step averaged).
 int step_tile(const Params& P, double* us);
+double step_16x15_us(const Params& P);  // and with 16x15 tiles, for any size
 double step_cols_us(const Params& P);
 
 // prow: background pressure per row (well-balanced variant) or null.
@@ -185,10 +186,11 @@ bool adj_fused_pairs(const Params& P);
 hipError_t launch_adj_fused_and_step(const Params& P, const AdjArgs& a, const StepArgs& st, hipStream_t s);
 // Blocks per member of its grid (AdjArgs::Dtd::count) in a sweep of nb members.
 int adj_fused_blocks(const Params& P, int nb);
-// Expected time of a launch in us, from measurements: what the choice between
-// the two is made by.
+// Expected time of a launch in us, from measurements: what the choice among
+// the adjoint's kernels is made by.
 double adj_fused_us(const Params& P);
 double adj_cols_us(const Params& P);
+double adj_pair_us(const Params& P, int tile);  // the pair on 8x8W or 16x15 tiles (else: never the shortest)
 // Kernel B alone: lambda^n from Z, codes, U^n and lambda^{n+1} of step n.
 hipError_t launch_adj_gather(const Params& P, const AdjArgs& a, hipStream_t s);
 // Differentiated step size, after both adjoint kernels of step n (a.U = U^n,

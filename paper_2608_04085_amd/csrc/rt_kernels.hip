@@ -1007,19 +1007,26 @@ void tile_dims(int tile, int* tx, int* ty, int* nt) {
 // (256x512), 11.8 (384x512); 32x16 8.1 (256x512), with 768 threads, which take
 // its 720 primitives and 612 predicted states in one pass each and its 1072
 // faces in two (512 threads: two, two and three, 8.4; 256x512 gradient 8.56 ->
-// 8.33 ms).
+// 8.33 ms).  Past as many rounds as a CU holds blocks at once each takes longer:
+// 16x8 13.7 in 6 rounds and 36.7 in 20, 32x8 12.0 in 3 and 19.5 in 4, 32x16 12.2
+// in 2 and 47.6 in 10.
 int step_tile(const Params& P, double* us) {
   struct Choice {
     int tile;
     double fixed, per_round;
+    int held;
+    double fixed_past, per_round_past;
   };
-  constexpr Choice choices[] = {
-      {TILE_8x8W, 4.1, 0.73}, {TILE_16x8W, 4.2, 1.17}, {TILE_32x8W, 3.9, 2.5}, {TILE_32x16, 3.0, 5.4}};
+  constexpr Choice choices[] = {{TILE_8x8W, 4.1, 0.73, 4, 4.3, 0.8},
+                                {TILE_16x8W, 4.2, 1.17, 3, 3.0, 1.6},
+                                {TILE_32x8W, 3.9, 2.5, 3, 3.0, 4.4},
+                                {TILE_32x16, 3.0, 5.4, 1, 3.5, 4.45}};
   int best = TILE_8x8W;
   double t = 1e300;
   for (const Choice& c : choices) {
     const long rounds = ((long)step_blocks(P, c.tile) * P.nb + 255) / 256;
-    const double u = c.fixed + c.per_round * (double)rounds;
+    const double u = rounds <= c.held ? c.fixed + c.per_round * (double)rounds
+                                      : c.fixed_past + c.per_round_past * (double)rounds;
     if (u < t) {
       t = u;
       best = c.tile;
@@ -1027,6 +1034,28 @@ int step_tile(const Params& P, double* us) {
   }
   if (us) *us = t;
   return best;
+}
+
+// The step's 16x15 tiles, given dt and march step averaged, us: 5x61 x 2221
+// members (11105 blocks) 93, 16x65536 (4370) 40, 61x120 x 256 (8192) 68, 128x256 x
+// 64 (9216) 77, 24x48 x 2048 (16384) 132.
+double step_16x15_us(const Params& P) { return 5.5 + 0.008 * (double)step_blocks(P, TILE_16x15) * P.nb; }
+
+// The adjoint's tile pair, us, where it can be faster than one launch: grids
+// of fewer columns than the widest tile, beside which the three halo columns
+// to each side that one launch needs are many.  (On wider ones it is at best a
+// tie: 60x58 x 180 members 58 against 63, the gradient 2.59 ms with either.)  8x8
+// tiles with 192 threads (a launch of rounds of 256 blocks): 3x9 x 1064 (9
+// rounds) 19.3, 4x2 x 2689 (11) 23.1, 3x2 x 6943 (28) 46.3; fused 23.9, 21.8, 48.7.
+// 16x15 tiles, whose blocks, rows and cells take their time: 3x10 x 39250 449,
+// 4x13 x 49121 626, 9x481 x 144 76, 16x58 x 1534 117; fused 633, 792, 92, 123.
+double adj_pair_us(const Params& P, int tile) {
+  if (P.nx >= 32) return 1e300;
+  const double blocks = (double)step_blocks(P, tile) * P.nb;
+  if (tile == TILE_8x8W) return 9.5 + 1.2 * ceil(blocks / 256.0);
+  if (tile != TILE_16x15) return 1e300;
+  const double rows = (double)((P.nx + 15) / 16) * P.ny * P.nb, cells = (double)P.nx * P.ny * P.nb;
+  return 8.5 + 1e-3 * (6.2 * blocks + 0.37 * rows + 0.0265 * cells);
 }
 
 int step_blocks(const Params& P, int tile) {

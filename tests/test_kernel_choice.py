@@ -61,3 +61,25 @@ def test_setting_the_fold_and_back_leaves_the_default_kernels(grid):
     for on in (1, 0):
         c.set_fold(on)
         assert c.kernels.split("/")[1] in rtcnop.TILES and c.fold == on
+
+
+# The kernels of grids of which each form is the fastest: measured times of
+# the given-dt step and of the adjoint in us, (columns, tiles) and (columns,
+# fused, tile pair)
+@pytest.mark.parametrize("grid,want", [
+    ((16, 64, 1024), "16x15/fused"),      # 67, 42; 141, 83, 88
+    ((16, 32, 4096), "16x15/fused"),      # 130, 90; 273, 167, 216
+    ((5, 248, 1095), "16x15/16x15"),      # 459, 147; 954, 272, 258
+    ((3, 10, 39250), "16x15/16x15"),      # 385, 297; 888, 633, 449
+    ((9, 481, 144), "16x15/16x15"),       # 73, 40; 159, 92, 76
+    ((3, 9, 1064), "8x8w/8x8w"),          # 22, 11; 42, 24, 19
+    ((24, 48, 2048), "columns/fused"),    # 99, 125; 213, 206, 292
+    ((44, 902, 54), "columns/columns"),   # 59, 78; 125, 186, 205
+    ((56, 2, 9059), "columns/columns"),   # 27, 223; 61, 465, 286
+    ((77, 149, 16), "columns/fused"),     # 14, 15 (16x8); a tile rule of few rounds took the latter
+    ((64, 128, 40), "columns/columns"),
+    ((128, 256, 64), "columns/columns"),
+    ((61, 40, 3), "8x8w/fused"),
+])
+def test_default_kernels_of_narrow_grids_and_large_batches(grid, want):
+    assert Bare(*grid).kernels == want
