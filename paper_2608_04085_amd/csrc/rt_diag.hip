@@ -4,6 +4,8 @@
 // kernels; launched through rt_diag.h by the C ABI.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "rt_diag.h"
 
 namespace rtk {
@@ -17,8 +19,9 @@ constexpr int kSpecThreads = 256;
 //   F[k]    = sum_b Y[b][k mod n1] w^{b k}
 // with w = e^{-2 pi i / n}: n1 + n2 products per coefficient instead of n.
 // Twiddles and Y in LDS; every twiddle is sincospi of its own angle.  The
-// direct kernels below, n products per coefficient, take prime n (n1 = 1) and
-// longer lines, whose tables and Y exceed the default LDS limit of 64 KB.
+// direct kernels below, n products per coefficient, take prime n (n1 = 1),
+// longer lines, whose tables and Y exceed the default LDS limit of 64 KB, and
+// those of a large prime factor where that is faster (row_split, col_split).
 // 256x256: rows 13.5 -> 5.0 us, columns 39.7 -> 5.6, one row's spectrum 11.3 ->
 // 3.4; bound by the LDS reads of the twiddles (two per product).
 constexpr int kSplitMax = 2048;
@@ -31,6 +34,32 @@ int split_of(int n) {
 }
 
 bool splits(int n) { return n <= kSplitMax && split_of(n) > 1; }
+
+// Stages or not, for lines that can be split.  One block does all of a split
+// line, where the direct kernels give 256 coefficients to each block, so with
+// n2 a large prime the split block's chain of products is the longer one and
+// pays only if the chip is full.  A launch takes ns per product of a block's
+// chain, times share per block on a CU once that exceeds 1 (fitted on 64x2042 to
+// 2018x2018, batches of 1 to 16; the direct columns wait for strided loads).
+// Direct and split, us: 2042x64 98.6 and 197, 2042x2 85 and 191, 64x2042 279 and
+// 384, but 8 x 64x2042 787 and 647, 16x1006 143 and 100, 300x302 65 and 25.
+int chunks(int n) { return (n + kSpecThreads - 1) / kSpecThreads; }
+double chain_ns(long blocks, long chain, double ns, double share) {
+  constexpr long kCus = 256;
+  return ns * (double)chain * std::max(1.0, share * (double)((blocks + kCus - 1) / kCus));
+}
+bool row_split(int nx, int ny, int nb) {
+  if (!splits(nx)) return false;
+  const int nk = nx / 2 + 1, n1 = split_of(nx);
+  return chain_ns((long)ny * nb, chunks(nx) * n1 + chunks(nk) * (nx / n1), 46.0, 0.9) <
+         chain_ns((long)chunks(nk) * ny * nb, nx, 45.0, 0.58);
+}
+bool col_split(int ny, int nk, int nb) {
+  if (!splits(ny)) return false;
+  const int n1 = split_of(ny);
+  return chain_ns((long)nk * nb, chunks(ny) * (n1 + ny / n1), 48.0, 0.8) <
+         chain_ns((long)chunks(ny) * nk * nb, ny, 140.0, 0.33);
+}
 
 __device__ __forceinline__ void twiddles(int n, double* tw) {  // [0, n): cos(2 pi k / n), [n, 2 n): sin
   for (int k = threadIdx.x; k < n; k += kSpecThreads) {
@@ -251,7 +280,7 @@ hipError_t launch_power_spectrum_2d(int nx, int ny, int nb, const double* f, lon
                                     double* E, hipStream_t s) {
   if (nx < 1 || nx > kSpecMaxNx || ny < 1 || ny > kSpecMaxNx || nb < 1) return hipErrorInvalidValue;
   const int nk = nx / 2 + 1;
-  if (splits(nx))
+  if (row_split(nx, ny, nb))
     hipLaunchKernelGGL(k_dft_rows_split, dim3(ny, nb), dim3(kSpecThreads), 4 * (size_t)nx * sizeof(double), s, nx, ny,
                        split_of(nx), f, member_stride, nk, C);
   else
@@ -259,7 +288,7 @@ hipError_t launch_power_spectrum_2d(int nx, int ny, int nb, const double* f, lon
                        2 * (size_t)nx * sizeof(double), s, nx, ny, f, member_stride, nk, C);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (splits(ny))
+  if (col_split(ny, nk, nb))
     hipLaunchKernelGGL(k_dft_cols_split, dim3(nk, nb), dim3(kSpecThreads), 4 * (size_t)ny * sizeof(double), s, ny,
                        split_of(ny), nk, C, E);
   else
@@ -274,7 +303,6 @@ hipError_t launch_row_spectrum(int nx, int ny, int nb, const double* f, long lon
   const int nbins = nx / 2 + 1;
   // One block per member does both stages in turn, where the direct kernel
   // has a block per mode: split only while the block's chain is the shorter.
-  auto chunks = [](int n) { return (n + kSpecThreads - 1) / kSpecThreads; };
   const int n1 = split_of(nx);
   if (row >= 0 && splits(nx) && chunks(nx) * n1 + chunks(nbins) * (nx / n1) < nx) {
     hipLaunchKernelGGL(k_one_row_spectrum, dim3(nb), dim3(kSpecThreads), 4 * (size_t)nx * sizeof(double), s, nx,

@@ -1,0 +1,46 @@
+"""GPU: which kernels a call launches where a rule on sizes decides it and
+either choice gives right results, by the names the profiler reports (in a
+file that runs late: a profiler once used stays attached to the process)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_04085_amd.config import RTConfig
+
+pytestmark = pytest.mark.gpu
+
+
+def launched(call):
+    """What call returns, and how often it launched each kernel (names up to the argument list)."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        out = call()
+        torch.cuda.synchronize()
+    names = {}
+    for e in p.key_averages():
+        if "k_" in e.key:
+            k = e.key[e.key.index("k_"):].split("(")[0].split("<")[0]
+            names[k] = names.get(k, 0) + e.count
+    assert names, "the profiler reported no kernel"
+    return out, names
+
+
+# lines with a large prime factor: a few of them (the direct kernels' blocks
+# are more and shorter), many (the chip is full either way), and others
+@pytest.mark.parametrize("nx,ny,nb,rows,cols", [
+    (2042, 64, 1, "k_dft_rows", "k_dft_cols_split"), (2042, 2, 1, "k_dft_rows", "k_dft_cols_power"),
+    (64, 2042, 1, "k_dft_rows_split", "k_dft_cols_power"), (2042, 64, 16, "k_dft_rows_split", "k_dft_cols_split"),
+    (64, 2042, 16, "k_dft_rows_split", "k_dft_cols_split"), (16, 1006, 1, "k_dft_rows_split", "k_dft_cols_split"),
+    (302, 300, 1, "k_dft_rows_split", "k_dft_cols_split"), (256, 256, 1, "k_dft_rows_split", "k_dft_cols_split")])
+def test_two_stage_or_direct_spectra(nx, ny, nb, rows, cols):
+    from paper_2608_04085_amd import rtcnop
+    r = rtcnop.Context(RTConfig(nx=nx, ny=ny, batch=nb), max_steps=8)
+    f = np.random.default_rng(nx + ny).standard_normal((nb, ny, nx))
+    d = torch.from_numpy(f).cuda()
+    got, names = launched(lambda: r.power_spectrum_2d(d))
+    assert names == {rows: 1, cols: 1}
+    # (the bound of the spectra's own test: n^1.5 1.2e-16 at the worst)
+    E = np.abs(np.fft.rfft2(f)) ** 2
+    assert np.all(np.abs(got.cpu().numpy().reshape(E.shape) - E) <= 1e-12 * E.max(axis=(1, 2), keepdims=True))
