@@ -98,11 +98,14 @@ ReportBlocks& report_blocks() {
 constexpr int kMaxGroups = 4;
 // Groups the sweep uses (fewer if the batch has fewer members).
 constexpr int kSplitGroups = 2;
-// Differentiated steps: most tiles of a member whose next launch corrects
-// lambda.  Gradients with a launch of its own / so, ms: 64x128 (128 tiles) 2.41
-// / 2.18, 256x512 (256) 4.48 / 4.10, 512x512 (512) 14.1 / 13.5, 512x1024 (1024)
-// 14.1 / 15.0, 1024x1024 (2048) 32.0 / 38.8.
-constexpr int kDeferTiles = 512;
+// Differentiated steps: most tiles, of all members, of a sweep whose next
+// launch corrects lambda: every block reads all partials of its member, which
+// adds to each round of blocks, against a launch of 4.7 us.  Gradients with a
+// launch of its own / so, ms: 64x128 (128 tiles) 2.41 / 2.18, 256x512 (256) 4.48
+// / 4.10, 512x512 (512) 14.1 / 13.5, 512x1024 (1024) 14.1 / 15.0, 1024x1024
+// (2048) 32.0 / 38.8; 2 x 512x512 (1024) 4.87 / 4.89, 64 x 128x128 (2048) 8.71 /
+// 8.91, 8 x 256x512 (2048) 8.41 / 8.80, 32 x 256x256 (4096) 15.5 / 16.4.
+constexpr long kDeferTiles = 512;
 
 // The kernels that run in place of the adjoint's tile kernels.
 constexpr int kAdjointMask = RT_COLUMNS_ADJOINT | RT_FUSED_ADJOINT;
@@ -1125,10 +1128,10 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
   const bool dtd = c->dt_mode == RT_DT_DIFFERENTIATED;
   // Differentiated steps in the fused kernel: the correction of lambda^{n+1},
   // otherwise a launch of its own (4.7 us), is left to the launch that reads
-  // it, while a member's partials are few enough for every block to read all.
+  // it, while the partials are few enough (kDeferTiles).
   const bool dtd_fused = c->adj_variant(true) == rtk::TILE_FUSED;
   const int dtd_count = dtd_fused ? rtk::adj_fused_blocks(P, P.nb) : rtk::step_blocks(P, c->tile_adj);
-  const bool dtd_deferred = dtd_fused && dtd_count <= kDeferTiles;
+  const bool dtd_deferred = dtd_fused && (long)dtd_count * P.nb <= kDeferTiles;
   auto dtd_args = [&](size_t b0, int n) {  // of members from b0 on
     const size_t half = (size_t)c->dtd_stride * P.nb, o = b0 * (size_t)c->dtd_stride;
     const size_t w = o + (n & 1 ? half : 0), r = o + (n & 1 ? 0 : half);

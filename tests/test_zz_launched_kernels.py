@@ -44,3 +44,27 @@ def test_two_stage_or_direct_spectra(nx, ny, nb, rows, cols):
     # (the bound of the spectra's own test: n^1.5 1.2e-16 at the worst)
     E = np.abs(np.fft.rfft2(f)) ** 2
     assert np.all(np.abs(got.cpu().numpy().reshape(E.shape) - E) <= 1e-12 * E.max(axis=(1, 2), keepdims=True))
+
+
+# differentiated steps: the launch that corrects lambda follows the last
+# adjoint step alone while all tiles of the sweep are few, else every one
+@pytest.mark.parametrize("nx,ny,nb,each", [(64, 128, 1, False), (61, 40, 3, False), (256, 256, 4, False),
+                                           (256, 256, 5, True), (128, 128, 64, True), (520, 1100, 1, True)])
+def test_launches_that_correct_lambda(nx, ny, nb, each):
+    from paper_2608_04085_amd import rtcnop
+    from paper_2608_04085_amd.config import CKPT_UNIFORM
+    cfg = RTConfig(nx=nx, ny=ny, batch=nb)
+    uv = 3e-2 * np.random.default_rng(nx).standard_normal((nb, 2, ny, nx)) * np.linspace(0.1, 1.0, nb)[:, None, None, None]
+    r, tiles = rtcnop.Context(cfg, max_steps=64), rtcnop.Context(cfg, max_steps=64, tile="16x15")
+    for c in (r, tiles):
+        c.set_dt_mode("differentiated")
+    T = 5.4 * float(r.cfl_dt(r.init_state(uv)).min())
+    pol = rtcnop.Policy(CKPT_UNIFORM, 3)
+    pool = torch.empty(r.pool_bytes(CKPT_UNIFORM, 3, 16) + 256, dtype=torch.uint8, device="cuda")
+    got, names = launched(lambda: [x.cpu().numpy() for x in r.grad_u0(uv, T, pol, pool=pool)])
+    assert names["k_dt_correct"] == (int(got[2].max()) if each else 1)
+    # against the tile pair, which differs in the grouping of mu's sum alone:
+    # 1e-16 times the root of its terms, over a few steps
+    want = [x.cpu().numpy() for x in tiles.grad_u0(uv, T, pol, pool=pool)]
+    np.testing.assert_array_equal(got[2], want[2])
+    assert np.max(np.abs(got[1] - want[1])) <= 1e-11 * np.max(np.abs(want[1]))
