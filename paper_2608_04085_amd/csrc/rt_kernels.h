@@ -35,6 +35,7 @@ struct Report {
   struct Member {
     double speed;  // largest signal speed of the initial state
     double ke0;    // KE(0)
+    double left;   // steps of the last one's size to the end time, 0 once there
     int32_t nsteps, pad;
   } member[1];  // nb of them
 };
@@ -208,7 +209,7 @@ hipError_t launch_reduce(const Params& P, int kind, const double* a, const doubl
 // report: also every member's speed, to the host.
 hipError_t launch_march_begin(const Params& P, const double* maxspeed, double T, Ctl* ctl, uint64_t* acc,
                               Flags* flags, Report* report, hipStream_t s);
-// Flags, step counts and KE(0) to the host.
+// Flags, step counts, steps left and KE(0) to the host.
 hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report,
                          hipStream_t s);
 hipError_t launch_cfl_from_speed(const Params& P, const double* maxspeed, double* dt, hipStream_t s);

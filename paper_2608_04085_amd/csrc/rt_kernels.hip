@@ -766,8 +766,10 @@ __global__ void k_report(Params P, const Ctl* ctl, const Flags* flags, const dou
   const int b = threadIdx.x + blockIdx.x * blockDim.x;
   if (b == 0) report->flags = *flags;
   if (b >= P.nb) return;
+  const Ctl c = ctl[b];
   report->member[b].ke0 = ke0[b];
-  report->member[b].nsteps = ctl[b].nsteps;
+  report->member[b].left = c.done ? 0.0 : (c.T - c.t) / c.dt_last;
+  report->member[b].nsteps = c.nsteps;
 }
 
 __global__ void k_copy_final(Params P, const Ctl* ctl, const double* A, const double* Bb, double* U) {

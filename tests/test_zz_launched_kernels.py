@@ -1,6 +1,6 @@
-"""GPU: which kernels a call launches where a rule on sizes decides it and
-either choice gives right results, by the names the profiler reports (in a
-file that runs late: a profiler once used stays attached to the process)."""
+"""GPU: which kernels a call launches, and how often, where a rule decides it
+and either choice gives right results, by the names the profiler reports (in
+a file that runs late: a profiler once used stays attached to the process)."""
 import numpy as np
 import pytest
 import torch
@@ -68,3 +68,34 @@ def test_launches_that_correct_lambda(nx, ny, nb, each):
     want = [x.cpu().numpy() for x in tiles.grad_u0(uv, T, pol, pool=pool)]
     np.testing.assert_array_equal(got[2], want[2])
     assert np.max(np.abs(got[1] - want[1])) <= 1e-11 * np.max(np.abs(want[1]))
+
+
+@pytest.mark.parametrize("nx,ny,nb", [(64, 128, 1), (40, 72, 3)])
+def test_rounds_of_a_march_whose_steps_shrink(nx, ny, nb):
+    # a state at rest of even sound speed and uneven pressure: the flow that
+    # starts takes the steps to less than half of the first
+    from paper_2608_04085_amd import rtcnop
+    cfg = RTConfig(nx=nx, ny=ny, batch=nb)
+    r = rtcnop.Context(cfg, max_steps=1024)
+    x, y = (np.arange(n) / n for n in (nx, ny))
+    lp = np.exp(2.3 * np.sin(4 * np.pi * x) * np.sin(6 * np.pi * y)[:, None])
+    U = r.init_state(torch.zeros(r.shape_uv, dtype=torch.float64))
+    for b in range(nb):
+        U[b, 0] = torch.from_numpy(lp)
+        U[b, 3] = torch.from_numpy(2.5 * lp / 0.4) * (1.0 - 0.3 * b)
+    dt0 = float(r.cfl_dt(U).min())
+    for steps in (20, 100):
+        (UT, _, n, _), names = launched(lambda: r.integrate(U, steps * dt0))
+        assert int(n.max()) > 1.5 * steps
+        # each round ends where the steps left at the last size suggest (2 %
+        # more), so what remains shrinks at least threefold: 100 in five rounds
+        assert names["k_report"] <= 6
+        r.set_graphs(False)
+        want = r.integrate(U, steps * dt0)
+        r.set_graphs(True)
+        assert torch.equal(UT, want[0]) and torch.equal(n, want[2])
+    # a march beyond the step log is still refused
+    few = rtcnop.Context(cfg, max_steps=int(n.max()) - 1)
+    with pytest.raises(rtcnop.RTError) as e:
+        few.integrate(U, 100 * dt0)
+    assert e.value.code == -3
