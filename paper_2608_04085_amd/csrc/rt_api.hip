@@ -882,10 +882,7 @@ int rt_step(rt_ctx* c, const double* U_in, double* U_out, const double* dt, doub
   // every speed that forms dt_next is written by this call's launch: nothing
   // in the workspace has to be as an earlier call left it
   const int variant = c->step_variant(), parts = rtk::step_parts(c->P, variant);
-  if (dt_next) {
-    a.speeds = c->partial;
-    a.speeds_stride = parts;
-  }
+  if (dt_next) a.speeds = c->partial;
   RT_HIP(rtk::launch_step(c->P, variant, a, c->stream));
   if (dt_next) RT_HIP(rtk::launch_cfl_from_parts(c->P, c->partial, parts, dt_next, c->stream));
   return 0;

@@ -305,7 +305,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_step_cols(Params P, StepArgs
   if (!need_speed) return;
   const double bm = wave_max(smax);
   if (a.ctl == nullptr) {
-    if (lane == 0) a.speeds[(size_t)b * a.speeds_stride + t] = bm;
+    if (lane == 0) a.speeds[w] = bm;  // (b * per + t)
     return;
   }
   const int L = a.launch;

@@ -67,14 +67,13 @@ struct StepArgs {
   int32_t snap_interval, snap_slots;
   // Given-dt mode: dt = dt[b * dt_stride + dt_index]; members with
   // dt_index >= nsteps_limit[b] are skipped.  speeds (may be null)
-  // [B][speeds_stride] receives the largest signal speed of U^{n+1} over each
-  // of the step_parts(P, tile) parts of a member (tiles, or strips' segments),
-  // all of them written by the launch.
+  // [B][step_parts(P, tile)] receives the largest signal speed of U^{n+1} over
+  // each part of a member (tile, or strip's segment), all of them written by
+  // the launch.
   const double* dt;
   int32_t dt_stride, dt_index;
   const int32_t* nsteps_limit;
   double* speeds;
-  int32_t speeds_stride;
   Flags* flags;
   bool beside;  // another launch of the kind runs at the same time (column kernels leave it its wavefront slots)
 };
@@ -213,7 +212,7 @@ hipError_t launch_march_begin(const Params& P, const double* maxspeed, double T,
 hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, const double* ke0, Report* report,
                          hipStream_t s);
 hipError_t launch_cfl_from_speed(const Params& P, const double* maxspeed, double* dt, hipStream_t s);
-// From StepArgs::speeds with speeds_stride = count.
+// From StepArgs::speeds, count = step_parts.
 hipError_t launch_cfl_from_parts(const Params& P, const double* speeds, int count, double* dt, hipStream_t s);
 hipError_t launch_copy_final(const Params& P, const Ctl* ctl, const double* A, const double* Bbuf, double* U,
                              double* t_out, int32_t* nsteps_out, const double* log_src, int32_t log_src_cap,

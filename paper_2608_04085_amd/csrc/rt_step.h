@@ -444,7 +444,7 @@ __device__ __forceinline__ void step_tile_body(const Params& P, const StepArgs& 
   // their bits)
   const double bm = block_max<NT>(smax, sRed);
   if (a.ctl == nullptr) {
-    if (tid == 0) a.speeds[(size_t)b * a.speeds_stride + blockIdx.x + (size_t)gridDim.x * blockIdx.y] = bm;
+    if (tid == 0) a.speeds[((size_t)b * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = bm;
     return;
   }
   const int L = a.launch;
