@@ -747,12 +747,20 @@ __global__ void k_march_begin(Params P, const double* ms, double T, Ctl* ctl, ui
           (r == 0 && k == 0) ? (uint64_t)__double_as_longlong(ms[b]) : 0ull;
 }
 
-// CFL step from the speeds of a member's parts; one block per member.
+// CFL step from the speeds of a member's parts; one block per member, W loads
+// of a thread at once (an index past the end reads the last part again).
+template <int W>
 __global__ __launch_bounds__(256) void k_cfl_from_parts(Params P, const double* speeds, int count, double* dt) {
   __shared__ double red[4];
   const double* v = speeds + (size_t)blockIdx.x * count;
   double ms = 0.0;
-  for (int k = threadIdx.x; k < count; k += 256) ms = fmax(ms, v[k]);
+  for (int k = threadIdx.x; k < count; k += 256 * W) {
+    double a[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) a[q] = v[min(k + q * 256, count - 1)];
+#pragma unroll
+    for (int q = 0; q < W; ++q) ms = fmax(ms, a[q]);
+  }
   ms = block_max<256>(ms, red);
   if (threadIdx.x == 0) dt[blockIdx.x] = P.cfl / ms;
 }
@@ -1222,7 +1230,8 @@ hipError_t launch_report(const Params& P, const Ctl* ctl, const Flags* flags, co
 }
 
 hipError_t launch_cfl_from_parts(const Params& P, const double* speeds, int count, double* dt, hipStream_t s) {
-  hipLaunchKernelGGL(k_cfl_from_parts, dim3(P.nb), dim3(256), 0, s, P, speeds, count, dt);
+  if (count <= 256) hipLaunchKernelGGL(k_cfl_from_parts<1>, dim3(P.nb), dim3(256), 0, s, P, speeds, count, dt);
+  else hipLaunchKernelGGL(k_cfl_from_parts<8>, dim3(P.nb), dim3(256), 0, s, P, speeds, count, dt);
   return hipGetLastError();
 }
 

@@ -14,9 +14,11 @@ def host(t):
 
 
 # one part of a member and many, of either step kernel: strips of one-row
-# segments of a narrow grid are more than its 8x8 tiles
+# segments of a narrow grid are more than its 8x8 tiles; more than 256 and
+# more than 2048 parts, which a block reads at once
 @pytest.mark.parametrize("nx,ny,nb,tile", [(3, 2, 2, None), (5, 300, 1, "columns"), (64, 128, 3, None),
-                                           (250, 254, 1, "16x15"), (130, 250, 9, "columns"), (61, 40, 3, "8x8")])
+                                           (250, 254, 1, "16x15"), (130, 250, 9, "columns"), (61, 40, 3, "8x8"),
+                                           (1000, 1100, 1, "columns"), (500, 300, 1, "8x8")])
 def test_cfl_step_of_the_result_whatever_the_workspace_holds(nx, ny, nb, tile):
     from paper_2608_04085_amd import rtcnop
     cfg = RTConfig(nx=nx, ny=ny, batch=nb)
