@@ -309,7 +309,8 @@ int rt_set_graphs(rt_ctx* ctx, int32_t on);
  * snapshots (the size rt_pool_bytes returns); with room for one, the sweep
  * runs on one stream; on small grids the steps ride in the adjoint's
  * launches instead, all on the context's stream.  RT_CKPT_REVOLVE with two
- * or more members (column kernels: other than three) runs the binomial plan
+ * or more members (column kernels: not with three, whose halves are one and
+ * two) runs the binomial plan
  * for members [0, B/2) on the context's stream and for [B/2, B) on the second
  * one, one action later, each on its own slice of every buffer.  Results are
  * identical either way; on = 0 runs everything on the context's stream. */
@@ -320,7 +321,7 @@ int rt_get_tile(const rt_ctx* ctx, int32_t* tile);
 int rt_autotune(rt_ctx* ctx, const double* U, int32_t reps, int32_t* step_tile, int32_t* adj_tile);
 /* The reverse sweep of RT_CKPT_STORE_ALL / RT_CKPT_UNIFORM runs one kernel
  * per adjoint step, which also completes the previous step's limiter gather
- * (on = 1), or the two kernels of rt_step_adjoint per step (on = 0); results
+ * (on = 1), or the kernels of rt_step_adjoint per step (on = 0); results
  * are identical.  Folding needs the adjoint's tile kernels (see
  * rt_set_columns): rt_get_fold gives the setting, which takes effect where
  * they run.  rt_set_fold(ctx, 1) makes them run if the caller has chosen
@@ -349,9 +350,11 @@ int rt_get_fold(const rt_ctx* ctx, int32_t* on);
  * member's last, adds (mu_n - mu_last) d dt_n / dU^n at the cell holding the
  * largest speed (the first such cell in storage order on a tie, the y speed
  * on a tie between x and y).  The number of steps is taken as locally
- * constant.  This mode always runs two kernels per adjoint step plus one
- * small kernel; it is deterministic for a given adjoint tile, and tiles
- * differ only in the rounding of mu's sum. */
+ * constant.  This mode never folds and never runs the column adjoint (see
+ * rt_set_columns); a small kernel corrects lambda after each adjoint step, or,
+ * where all tiles of the sweep are few, the next adjoint launch does.  It is
+ * deterministic for a given adjoint tile, and tiles differ only in the rounding
+ * of mu's sum. */
 enum { RT_DT_FROZEN = 0, RT_DT_DIFFERENTIATED = 1 };
 int rt_set_dt_mode(rt_ctx* ctx, int32_t mode);
 int rt_get_dt_mode(const rt_ctx* ctx, int32_t* mode);
@@ -361,8 +364,9 @@ int rt_get_dt_mode(const rt_ctx* ctx, int32_t* mode);
  * out[0] a step at a given dt (as re-computed in the reverse sweep), out[1]
  * a step with the CFL reduction (as in the march), out[2] one folded
  * adjoint step (one kernel that also completes the previous step's limiter
- * gather), out[3] one rt_step_adjoint (two kernels), out[4] the adjoint step
- * in the sweep's current mode (out[2] or out[3]).  The well-balanced variant
+ * gather), out[3] one rt_step_adjoint (one launch of the column or the fused
+ * kernel, two of the tile kernels), out[4] the adjoint step in the sweep's
+ * current mode (out[2] or out[3]).  The well-balanced variant
  * has no folded form: there out[2] repeats out[3].  out holds 5 doubles.
  * Synchronises the stream; the workspace serves as scratch. */
 int rt_kernel_times(rt_ctx* ctx, const double* U, int32_t reps, double* out);

@@ -1330,11 +1330,12 @@ int grad_objective(rt_ctx* c, const double* uv0, double T, const rt_ckpt_policy*
     // Column kernels of the two groups go side by side, one wavefront per SIMD
     // each: sized to fill the chip alone, each would wait for the other's
     // wavefronts to end (2 x 512x1024 11.3 ms per gradient, side by side 10.1,
-    // one stream 10.3; 8 x 512x1024 108, 104, 105).  Three members leave one
-    // group with half the other's work and are faster in one (3 x 500x700 15.8
-    // against 16.6, 3 x 512x1024 14.1 and 14.8; five and seven split as well).
+    // one stream 10.3; 8 x 512x1024 108, 104, 105).  Where one group has half
+    // the other's work (three members), one stream is faster (3 x 500x700 15.8
+    // against 16.6, 3 x 512x1024 14.1 and 14.8; five and seven members split).
     const bool columns = c->adj_variant(dtd) == rtk::TILE_COLUMNS;
-    const bool split = c->overlap && P.nb >= 2 && !(columns && P.nb == 3);
+    const int fewest = P.nb / kSplitGroups, most = (P.nb + kSplitGroups - 1) / kSplitGroups;  // members of a group
+    const bool split = c->overlap && P.nb >= 2 && !(columns && most >= 2 * fewest);
     const int ng = split ? std::min(P.nb, kSplitGroups) : 1;
     const bool beside = columns && split;
     const size_t N = (size_t)P.nx * P.ny, sm = 4 * N;

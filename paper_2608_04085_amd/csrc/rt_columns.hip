@@ -7,14 +7,16 @@
 // (4 of 64) and two rows around a segment.  The expressions are those of the
 // tile kernels, so the results are the same to the bit.
 //
-// k_step_cols is bound by VALU issue: about 460 instructions per row and
-// wavefront at a given dt (500 in the march) where the 16x15 tiles take 845
-// per 64 cells plus their barriers.  Two rows per loop turn save 3-6 % (what
-// a row hands to the next changes registers by name, not by moves), and 4 %
-// more come from wavefronts that keep pace (below).  Tiles against columns,
-// us: 8 x 1024x2048 550 -> 315 given dt and 590 -> 338 in the march; 8 x
-// 512x1024 153 -> 79 and 172 -> 89; 64 x 128x256 79 -> 55 and 95 -> 60;
-// 1024x2048 68 -> 47 and 77 -> 51.
+// k_step_cols is bound by VALU issue: 494 instructions per row and wavefront
+// at a given dt (532 in the march), 567 (610) per 64 cells with the lanes
+// beside the strips, where the 16x15 tiles take 845 plus their barriers.  Two
+// rows per loop turn save 3-6 % (what a row hands to the next changes registers
+// by name, not by moves), and 4 % more come from wavefronts that keep pace
+// (below).  Tiles against columns, us, of 50 launches in a row: 8 x 1024x2048 529
+// -> 309 given dt and 588 -> 334 in the march; 8 x 512x1024 131 -> 78 and 147 ->
+// 85; 64 x 128x256 72 -> 52 and 80 -> 58; 1024x2048 69 -> 43 and 77 -> 48 (noisy
+// states, which part the lanes' branches, up to 7 % more by columns; under a long
+// load the clock falls to 1.8 GHz, 8 x 1024x2048 to 365 and 390).
 //
 // k_adj_cols is the whole adjoint of a step in one launch: about 940 VALU
 // instructions per row and wavefront, and no intermediates in memory (the
@@ -29,8 +31,8 @@
 // its upwind side by exact products (1100 -> 990 instructions, 201 -> 194).
 // Two rows per loop turn and even pace: 194 -> 181.  (Reading a phase's LDS
 // values a phase ahead is worth nothing.)  Tiles against columns, us: 8 x
-// 1024x2048 1510 -> 685, 8 x 512x1024 398 -> 181, 64 x 128x256 198 -> 127,
-// 512x1024 46 -> 36.
+// 1024x2048 1512 -> 656, 8 x 512x1024 392 -> 180, 64 x 128x256 190 -> 123,
+// 512x1024 45 -> 36.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

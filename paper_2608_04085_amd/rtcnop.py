@@ -276,7 +276,9 @@ class Context:
     def kernel_times(self, U, reps: int = 100) -> dict:
         """Per-launch microseconds of the selected variants (HIP events on the
         context's stream): given-dt step, march step, folded adjoint step
-        (the reverse sweep's kernel), rt_step_adjoint (two kernels)."""
+        (of the tile kernels), rt_step_adjoint ("adjoint_two_kernel_us", which
+        is one launch of the column or the fused kernel where those run), and
+        which of the two the reverse sweep runs."""
         self._sync_stream()
         U = self.as_dev(U)
         out = (ctypes.c_double * 5)()

@@ -58,7 +58,7 @@ def fwd_64x128(T: float = 2.0, reps: int = 5) -> dict:
     ke = rt.kinetic_energy(UT) / rt.kinetic_energy(U0)
     el = float(np.median(times))
     return {"workload": "fwd_64x128", "T": T, "nsteps": int(n.item()), "R": float(ke.item()),
-            "cell_updates_per_s": cfg.cells * int(n.item()) / el, "seconds": el, "tiles": rt.tile}
+            "cell_updates_per_s": cfg.cells * int(n.item()) / el, "seconds": el, "tiles": rt.kernels}
 
 
 def ensemble_64x128x256(T: float = 2.0, reps: int = 2) -> dict:
@@ -77,7 +77,7 @@ def ensemble_64x128x256(T: float = 2.0, reps: int = 2) -> dict:
     return {"workload": "ensemble_64x128x256", "T": T, "batch": 64, "nsteps_min": int(ns.min()),
             "nsteps_max": int(ns.max()), "R_gaussian": R[:32].tolist(), "R_fourier_kx_phase": R[32:].tolist(),
             "aggregate_cell_updates_per_s": float(cfg.nx * cfg.ny * ns.sum() / el), "seconds": el,
-            "tiles": rt.tile}
+            "tiles": rt.kernels}
 
 
 def _revolve_pool(rt: Context, budget_bytes: int) -> torch.Tensor:
@@ -103,7 +103,7 @@ def grad_1024x2048(T: float = 3.0, budget_gb: float = 64.0) -> dict:
     return {"workload": "grad_1024x2048", "T": T, "nsteps": int(n.item()), "R": float(R.item()),
             "forward_seconds": t_fwd, "gradient_seconds": t_grad, "adjoint_over_forward": t_grad / t_fwd,
             "pool_slots": int(pool.numel() // (8 * 4 * cfg.cells)), "peak_row": row,
-            "top5_kx_energy_fraction": cnop.top5_fraction(E), "tiles": rt.tile}
+            "top5_kx_energy_fraction": cnop.top5_fraction(E), "tiles": rt.kernels}
 
 
 def cnop_8x512x1024(T: float = 1.0, iters: int = 50, budget_gb: float = 16.0, groups: int = 2) -> dict:
@@ -140,7 +140,7 @@ def cnop_8x512x1024(T: float = 1.0, iters: int = 50, budget_gb: float = 16.0, gr
             "forward_batch_seconds": t_fwd, "fd_iters_per_s_extrapolated": 1.0 / fd_iter_s,
             "adjoint_vs_fd_speedup": fd_iter_s / (el / iters),
             "R_initial": R_init, "R_final": [float(x) for x in R.tolist()], "best_R": float(max(R.tolist())),
-            "chi_final": chi, "gradient_evals_per_group": search.grads, "tiles": rt.tile}
+            "chi_final": chi, "gradient_evals_per_group": search.grads, "tiles": rt.kernels}
 
 
 def _fd_ratio(rtb: Context, uv: torch.Tensor, dofs: np.ndarray, h: float, T: float) -> np.ndarray:
@@ -236,7 +236,7 @@ def paper_cnop_128(T: float = 2.0, iters: int = 20, restarts: int = 4) -> dict:
     rt.autotune(rt.init_state(uv), reps=10)
     pol = Policy(CKPT_UNIFORM, 32)
     out = {"workload": "paper_cnop_128", "T": T, "eps": 1e-6, "restarts": restarts, "iters": iters,
-           "tiles": rt.tile}
+           "tiles": rt.kernels}
     for name, mem in (("lbfgs_m10", 10), ("spg_m0", 0)):
         t0 = time.perf_counter()
 
